@@ -27,7 +27,7 @@
 //   rows = 4 heads x (3 terms + 1 spare), the factor 2^(e - 4 k) in the row's block scale.
 // The terms leave 2^-12 of x at most (better than binary16); e follows the largest |x| of the head in that group, so
 // no operand overflows or flushes whatever the magnitude of keys, queries and values.  The three rows of a head are
-// summed after the instruction (scores) or once at the end (E V).
+// summed after the instruction.
 // Zero-points never touch the tiles: sum_c q_c (s_c code + z_c) = sum_c (q_c s_c) (code - 1.5) + sum_c q_c (z_c + 1.5 s_c),
 // and likewise for the values per token.  Scores live in the log2 domain: x = q.k * log2(e)/sqrt(d).
 #include <hip/hip_runtime.h>
@@ -178,7 +178,8 @@ __device__ __forceinline__ void split_fp8x3(const float (&x)[8], uint32_t sc_bit
     const float sc = as_f32(sc_bits - ((uint32_t)(4 * k) << 23));
 #pragma unroll
     for (int v = 0; v < 2; ++v) {
-      short2_t w = __builtin_bit_cast(short2_t, r[4 * v]);  // any register: both halves are written below
+      short2_t w;
+      asm volatile("" : "=v"(w));  // any free register: both halves are written below (a live value would be copied first)
       w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, r[4 * v], r[4 * v + 1], sc, false);
       w = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w, r[4 * v + 2], r[4 * v + 3], sc, true);
       const uint32_t bits = __builtin_bit_cast(uint32_t, w);
@@ -271,26 +272,28 @@ struct WaveState {
   float m[NB];          // reference maximum of this lane's head (equal in the 16 lanes of the row), log2 domain
   float l[NB];          // per-lane partial sum of p
   float pz[NB];         // per-lane partial sum of p * (value zero-point + 1.5 value scale)
-  float4_t acc[NB][8];  // E V of channel 16 n + jd: registers 0..2 = the three term rows of the head, register 3 = what
-                        // the fp16 window contributed (the matrix cores add the zero term row to it)
+  float acc[NB][8];     // E V of channel 16 n + jd
 };
 
-// q K^T of one group for all heads (Alg. 1 line 7): scores in the log2 domain, sc[nb][n] = head 4 nb + hd, token 16 n + jd.
-// qa = this lane's 8 query values (head 4 nb + ha, channels c0 ..) times log2(e) / sqrt(d); qh = the same as binary16 pairs.
+// q K^T of one group for all heads (Alg. 1 line 7): sc[nb][n] = q.k of head 4 nb + hd, token 16 n + jd (the factor
+// log2(e) / sqrt(d) enters with the reference maximum, see exponent()).
+// qh = this lane's 8 query values (head 4 nb + ha, channels c0 ..) in binary16 pairs.
+// off[nb] = what the zero-points and the centring of the codes add to every score of the head: sc leaves it out.
+// valid: tokens of the group that exist (only the newest group of a sequence may be partial; the loop over the others passes
+// the constant).
 template <int NB, int BITS>
-__device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, const float (&qa)[NB][8], const uint32_t (&qh)[NB][4],
-                                         const Roles& lr, float (&sc)[NB][8]) {
+__device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, const uint32_t (&qh)[NB][4], const Roles& lr,
+                                         float (&sc)[NB][8], float (&off)[NB]) {
   const uint32_t S[4] = {g.ks.x, g.ks.y, g.ks.z, g.ks.w};
   const uint32_t Z[4] = {g.kz.x, g.kz.y, g.kz.z, g.kz.w};
   v8i_t A[NB];
   int scale_a[NB];
-  float4_t c0[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     float x[8], bz = 0.0f, mx = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      x[i] = fmaf(qa[nb][i], (float)as_h2(S[i >> 1])[i & 1], 0.0f);  // (the fused form reads the binary16 operand as it is)
+      x[i] = fmaf((float)as_h2(qh[nb][i >> 1])[i & 1], (float)as_h2(S[i >> 1])[i & 1], 0.0f);  // exact; the fused form reads binary16 operands as they are
       mx = fmaxf(mx, fabsf(x[i]));
     }
     // sum_c q_c (z_c + 1.5 s_c): what the zero-points and the centring of the codes add to every score of the group.
@@ -313,10 +316,8 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
       lds_order();
     }
     scale_a[nb] = (int)eb - 7 - 4 * lr.ua;
-    // the head's zero-point term enters as the C operand of its first term row: fetch it from a lane that holds head hd
-    // in the operand role (lane 4 hd)
-    c0[nb] = float4_t{__builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * lr.hd, __builtin_bit_cast(int, bz))), 0.f,
-                      0.f, 0.f};
+    // the head's zero-point term, from a lane that holds head hd in the operand role (lane 4 hd)
+    off[nb] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(16 * lr.hd, __builtin_bit_cast(int, bz)));
   }
   if (NB == 2) {
     lds_order();
@@ -324,6 +325,7 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
     for (int nb = 0; nb < NB; ++nb) A[nb] = get_operand(nb == 0 ? lr.ex_qk : lr.ex_pv, lr.rd);
     lds_order();
   }
+  const float4_t zero = {0.f, 0.f, 0.f, 0.f};
   if constexpr (BITS == 2 && NB == 1) {
     // All eight matrix instructions first, each into registers of its own, then the sums of the term rows: written
     // as one loop the compiler reuses the result registers and every instruction waits for the one before (a dozen
@@ -333,7 +335,7 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
     for (int m = 0; m < 4; ++m) {
       const uint32_t w[4] = {g.kw[m].x, g.kw[m].y, g.kw[m].z, g.kw[m].w};
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf) dq[2 * m + hf] = mfma_codes(A[0], w[2 * hf], w[2 * hf + 1], c0[0], scale_a[0], lr.pick);
+      for (int hf = 0; hf < 2; ++hf) dq[2 * m + hf] = mfma_codes(A[0], w[2 * hf], w[2 * hf + 1], zero, scale_a[0], lr.pick);
     }
 #pragma unroll
     for (int n = 0; n < 8; ++n) sc[0][n] = (dq[n][0] + dq[n][1]) + dq[n][2];
@@ -347,7 +349,7 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) {
-          const float4_t d = mfma_codes(A[nb], w[2 * hf], w[2 * hf + 1], c0[nb], scale_a[nb], lr.pick);
+          const float4_t d = mfma_codes(A[nb], w[2 * hf], w[2 * hf + 1], zero, scale_a[nb], lr.pick);
           sc[nb][2 * m + hf] = (d[0] + d[1]) + d[2];
         }
     } else {
@@ -356,7 +358,7 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) d[hf][nb] = mfma_codes_high(A[nb], w[2 * hf], w[2 * hf + 1], c0[nb], scale_a[nb], lr.pick);
+        for (int nb = 0; nb < NB; ++nb) d[hf][nb] = mfma_codes_high(A[nb], w[2 * hf], w[2 * hf + 1], zero, scale_a[nb], lr.pick);
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
@@ -381,13 +383,18 @@ __device__ __forceinline__ void qk_phase(const KeyRegs<BITS>& g, int valid, cons
 // last lines adds the correction to sums that are shifted by the TRUE maximum: there the slack is 0, which makes the
 // reference the running maximum itself.)
 constexpr float kSlack = 5.0f;
+// What 2 is raised to for a score (its head's offset off apart) and the reference m: s kAlpha + base.
+__device__ __forceinline__ float exponent_base(float off, float m) { return fmaf(off, kAlpha, -m); }
+__device__ __forceinline__ float exponent(float s, float base) { return fmaf(s, kAlpha, base); }
+
 template <int NB>
-__device__ __forceinline__ void update_reference(const float (&sc)[NB][8], WaveState<NB>& st, float slack) {
+__device__ __forceinline__ void update_reference(const float (&sc)[NB][8], const float (&off)[NB], WaveState<NB>& st, float slack) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     float mloc = sc[nb][0];
 #pragma unroll
     for (int n = 1; n < 8; ++n) mloc = fmaxf(mloc, sc[nb][n]);
+    mloc = (mloc + off[nb]) * kAlpha;
     if (__builtin_amdgcn_ballot_w64(mloc > st.m[nb] + slack) != 0) {
       const float mnew = fmaxf(st.m[nb], row_allmax(mloc));
       const float f = mnew == -INFINITY ? 1.0f : exp2f(st.m[nb] - mnew);  // 0 when the old reference is -inf
@@ -403,23 +410,27 @@ __device__ __forceinline__ void update_reference(const float (&sc)[NB][8], WaveS
 // p = 2^(x - m), its sums, and E V of one group (Alg. 1 lines 9-10).  MASKED: tokens from `fp16_from` on count in the
 // sums of p but not in E V: their values are taken from the fp16 window (pv_window_tail).
 template <int NB, int BITS, bool MASKED = false>
-__device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (&sc)[NB][8], const Roles& lr,
+__device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (&sc)[NB][8], const float (&off)[NB], const Roles& lr,
                                          WaveState<NB>& st, int fp16_from = kGroup) {
   const uint32_t SZ[8] = {g.sz[0].x, g.sz[0].y, g.sz[0].z, g.sz[0].w, g.sz[1].x, g.sz[1].y, g.sz[1].z, g.sz[1].w};
   v8i_t A[NB];
   int scale_a[NB];
+  // z + 1.5 s of the lane's tokens: what the zero-point and the centring of the codes give for every channel
+  float mid[8];
+#pragma unroll
+  for (int n = 0; n < 8; ++n) mid[n] = fmaf((float)as_h2(SZ[n])[0], Rec<BITS>::kCentre, (float)as_h2(SZ[n])[1]);
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     float y[8], mx = 0.0f;
+    const float base = exponent_base(off[nb], st.m[nb]);
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
-      const float p = __builtin_amdgcn_exp2f(sc[nb][n] - st.m[nb]);
+      const float p = __builtin_amdgcn_exp2f(exponent(sc[nb][n], base));
       const half2_t sz = as_h2(SZ[n]);
       st.l[nb] += p;
       const bool coded = !MASKED || 16 * n + lr.jd < fp16_from;
       y[n] = coded ? fmaf(p, (float)sz[0], 0.0f) : 0.0f;  // p * value scale: the weight of the token's codes
-      // sum_t p_t (z_t + 1.5 s_t): the zero-points and the centring of the codes, the same for every channel
-      st.pz[nb] = coded ? fmaf(y[n], Rec<BITS>::kCentre, fmaf(p, (float)sz[1], st.pz[nb])) : st.pz[nb];
+      st.pz[nb] = coded ? fmaf(p, mid[n], st.pz[nb]) : st.pz[nb];
       mx = fmaxf(mx, y[n]);
     }
     const uint32_t eb = block_exponent(row_umax(as_bits(mx)));  // over the 128 tokens of the head
@@ -445,26 +456,32 @@ __device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (
     }
     lds_order();
   }
+  // Every instruction starts from zero and its three term rows are added to the state at once: one register per channel
+  // and head block instead of four (NB = 1: 8 for 32) for three additions, and the sum over the groups is rounded like
+  // any binary32 sum rather than truncated by the matrix cores' adder.
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const uint32_t w[4] = {g.vw[m].x, g.vw[m].y, g.vw[m].z, g.vw[m].w};
+    float4_t d[2][NB];
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        st.acc[nb][2 * m + hf] = BITS == 2 ? mfma_codes(A[nb], w[2 * hf], w[2 * hf + 1], st.acc[nb][2 * m + hf], scale_a[nb], lr.pick)
-                                           : mfma_codes_high(A[nb], w[2 * hf], w[2 * hf + 1], st.acc[nb][2 * m + hf], scale_a[nb], lr.pick);
-  }
-  if constexpr (BITS == 4) {  // the low plane
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const uint32_t w[4] = {g.vw[4 + m].x, g.vw[4 + m].y, g.vw[4 + m].z, g.vw[4 + m].w};
+      for (int nb = 0; nb < NB; ++nb) {
+        const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+        d[hf][nb] = BITS == 2 ? mfma_codes(A[nb], w[2 * hf], w[2 * hf + 1], zero, scale_a[nb], lr.pick)
+                              : mfma_codes_high(A[nb], w[2 * hf], w[2 * hf + 1], zero, scale_a[nb], lr.pick);
+      }
+    if constexpr (BITS == 4) {  // the low plane
+      const uint32_t wl[4] = {g.vw[4 + m].x, g.vw[4 + m].y, g.vw[4 + m].z, g.vw[4 + m].w};
 #pragma unroll
       for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-          st.acc[nb][2 * m + hf] = mfma_codes(A[nb], w[2 * hf], w[2 * hf + 1], st.acc[nb][2 * m + hf], scale_a[nb], lr.pick);
+        for (int nb = 0; nb < NB; ++nb) d[hf][nb] = mfma_codes(A[nb], wl[2 * hf], wl[2 * hf + 1], d[hf][nb], scale_a[nb], lr.pick);
     }
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) st.acc[nb][2 * m + hf] += (d[hf][nb][0] + d[hf][nb][1]) + d[hf][nb][2];
   }
 }
 
@@ -475,7 +492,7 @@ __device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (
 // from one lane quad per block of 4 slots.  The result goes to the spare row of the accumulators through `out`, this
 // wave's [NB * 4][128] slice of the combine buffer.
 template <int NB>
-__device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win, const float (&sc)[NB][8], int from,
+__device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win, const float (&sc)[NB][8], const float (&off)[NB], int from,
                                                const Roles& lr, WaveState<NB>& st, int lane, float (*out)[kHeadDim]) {
   half_t* pb = reinterpret_cast<half_t*>(lr.ex_pv);  // [NB * 4 heads][128 tokens]
 #pragma unroll
@@ -483,7 +500,7 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 #pragma unroll
     for (int n = 0; n < 8; ++n) {
       const int j = 16 * n + lr.jd;
-      pb[(nb * 4 + lr.hd) * kGroup + j] = j >= from ? (half_t)__builtin_amdgcn_exp2f(sc[nb][n] - st.m[nb]) : (half_t)0.0f;
+      pb[(nb * 4 + lr.hd) * kGroup + j] = j >= from ? (half_t)__builtin_amdgcn_exp2f(exponent(sc[nb][n], exponent_base(off[nb], st.m[nb]))) : (half_t)0.0f;
     }
   lds_order();
   const int quad = lane >> 2, hrow = lane & 3;
@@ -516,7 +533,7 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
         for (int nb = 0; nb < NB; ++nb) acc[nb][ch] = mfma_bcast(A[nb][hf], bop, acc[nb][ch], bq);
       }
   }
-  // (lane = channel, registers = heads) -> (row = head, lane = channel % 16, channel block n)
+  // (lane = channel, registers = heads) -> (row = head, lane = channel % 16, register = channel block n)
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -528,7 +545,7 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int n = 0; n < 8; ++n) st.acc[nb][n][3] += out[nb * 4 + lr.hd][16 * n + lr.jd];
+    for (int n = 0; n < 8; ++n) st.acc[nb][n] += out[nb * 4 + lr.hd][16 * n + lr.jd];
   lds_order();
   // the spare term row of every head of this exchange region reads as zero again
   uint32_t* ex = reinterpret_cast<uint32_t*>(lr.ex_pv);
@@ -886,18 +903,32 @@ __device__ __forceinline__ void merge_rows(const float* __restrict__ part, const
 // B * avg_splits in proportion to its number of groups, rounded up from a quarter on, so that the long and the short
 // sequences of a batch end together; a batch of equal lengths gives avg_splits to every sequence.  Integer
 // arithmetic only: every wave of the launch that needs the number gets the same one from the same counters.
-__device__ __forceinline__ int sequence_splits(const kvlinc_cache& c, int nq_b, int avg_splits, int max_splits,
+__device__ __forceinline__ int groups_of(int nq) { return (nq + kGroup - 1) / kGroup; }
+
+// Groups of the whole batch, in every lane.  `head`: this lane's share of the first 64 sequences, n_quant[lane] requested
+// ahead by the caller (0 beyond the batch).
+__device__ __forceinline__ int batch_groups(const kvlinc_cache& c, int head, int lane) {
+  uint32_t total = groups_of(head);
+  for (int i = lane + 64; i < c.B; i += 64) total += groups_of(c.n_quant[i]);
+  total += dpp_u<kRowRor1>(total);
+  total += dpp_u<kRowRor2>(total);
+  total += dpp_u<kRowRor4>(total);
+  total += dpp_u<kRowRor8>(total);
+  const auto a = __builtin_amdgcn_permlane16_swap(total, total, false, false);
+  total = a[0] + a[1];
+  const auto b = __builtin_amdgcn_permlane32_swap(total, total, false, false);
+  return (int)(b[0] + b[1]);
+}
+
+// count = the sequence's groups (the same in every lane), total = the batch's.  ceil(avg count B / total - 1/4) is the
+// number of k >= 0 with 4 avg count B - total > 4 k total: the 64 lanes try one k each (max_splits is at most 32).
+__device__ __forceinline__ int sequence_splits(const kvlinc_cache& c, int count, int total, int avg_splits, int max_splits,
                                                int lane) {
   if (c.B == 1) return avg_splits;
-  int total = 0;
-  for (int i = lane; i < c.B; i += 64) total += (c.n_quant[i] + kGroup - 1) / kGroup;
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) total += __shfl_xor(total, m, 64);
-  const int count = (nq_b + kGroup - 1) / kGroup;
   int s = avg_splits;
-  if (total > 0) {  // ceil(avg count B / total - 1/4)
+  if (total > 0) {
     const long long num = 4ll * avg_splits * count * c.B - total;
-    s = num <= 0 ? 0 : (int)((unsigned long long)(num + 4ll * total - 1) / (unsigned long long)(4ll * total));
+    s = __builtin_popcountll(__builtin_amdgcn_ballot_w64(num > 4ll * total * lane));
   }
   s = min(s, min(max_splits, (count + kWaves - 1) / kWaves));  // at least one group per wave
   return __builtin_amdgcn_readfirstlane(max(s, 1));            // the same in every lane: keep it in a scalar register
@@ -923,7 +954,7 @@ __device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
 // BITS: so is the one for caches with 4-bit codes (it holds twice the tile words in registers).
 // FEW_HEADS: and the one for fewer than 4 query heads per kv head (see correction_workgroup).
 template <int NB, bool SLIDING = false, int BITS = 2, bool FEW_HEADS = false>
-__global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void decode_main_kernel(kvlinc_cache c, const half_t* __restrict__ q,
+__global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(kvlinc_cache c, const half_t* __restrict__ q,
                                                                    float* __restrict__ part, float* __restrict__ corr,
                                                                    half_t* __restrict__ out, int max_splits,
                                                                    int avg_splits, int gq, int corr_first) {
@@ -973,7 +1004,11 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
     const int n_seq = min(kCorrSeqs, c.B - b_first);
     // A sequence without quantized tokens has S = P = 0 (the states only change at a flush), so its parts come out
     // as zero without looking at n_quant.
+    // (the counters are requested first and looked at last: by then they have long arrived)
+    const int nq_head = lane < c.B ? c.n_quant[lane] : 0;
+    const int nq_mine = c.n_quant[b_first + min(lane, n_seq - 1)];
     correction_workgroup<FEW_HEADS>(c, q, corr, gq, g, r, b_first, n_seq, NB, lane, wave, lds);
+    const int total = batch_groups(c, nq_head, lane);
     // count this workgroup in at each of its sequences; merge those it completes
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -984,7 +1019,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
     __syncthreads();
     for (int s = 0; s < n_seq; ++s) {
       const int b = b_first + s, bh = b * c.H_kv + g;
-      const int n_splits = sequence_splits(c, c.n_quant[b], avg_splits, max_splits, lane);
+      const int n_splits = sequence_splits(c, groups_of(__builtin_amdgcn_readlane(nq_mine, s)), total, avg_splits, max_splits, lane);
       if (sFlags[s] == n_splits + n_parts - 1) {
         for (int h = wave; h < gq; h += kWaves)
           merge_rows(part, corr, max_splits, n_splits, b * c.H_q + g * gq + h, lane, (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);
@@ -1047,9 +1082,11 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
   }
   const int nq = c.n_quant[b];
   const int nr = c.n_res[b];
-  const int count = (nq + kGroup - 1) / kGroup;
+  const int count = groups_of(nq);
   {
-    const int mine = sequence_splits(c, nq, avg_splits, max_splits, lane);
+    int total = 0;
+    if (c.B > 1) total = batch_groups(c, lane < c.B ? c.n_quant[lane] : 0, lane);
+    const int mine = sequence_splits(c, count, total, avg_splits, max_splits, lane);
     if (sp >= mine) return;  // this sequence uses fewer splits than the grid provides
     if (mine != n_splits) {  // lengths differ within the batch: plan again, request the right first record
       n_splits = mine;
@@ -1074,12 +1111,12 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
   for (int nb = 0; nb < NB; ++nb) {
     st.m[nb] = -INFINITY; st.l[nb] = 0.f; st.pz[nb] = 0.f;
 #pragma unroll
-    for (int n = 0; n < 8; ++n) st.acc[nb][n] = float4_t{0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < 8; ++n) st.acc[nb][n] = 0.f;
   }
 
   if (my_half >= 0 && nr > 64 * my_half) {
     // this wave's half of the window first, then its results move to the row role: (lane = channel, registers = heads)
-    // -> (row = head, lane = channel % 16, register 3 of channel block n), through this wave's part of the combine buffer
+    // -> (row = head, lane = channel % 16, register = channel block n), through this wave's part of the combine buffer
     WindowState<NB> ws;
     window_half<NB>(c, q, bh, b, g, gq, my_half, nr, lane, ws);
 #pragma unroll
@@ -1093,7 +1130,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
       }
       lds_order();
 #pragma unroll
-      for (int n = 0; n < 8; ++n) st.acc[nb][n][3] = sAcc[wave][nb * 4 + lr.hd][16 * n + lr.jd];
+      for (int n = 0; n < 8; ++n) st.acc[nb][n] = sAcc[wave][nb * 4 + lr.hd][16 * n + lr.jd];
       lds_order();
       const float m_mine = lr.hd == 0 ? ws.m[nb][0] : lr.hd == 1 ? ws.m[nb][1] : lr.hd == 2 ? ws.m[nb][2] : ws.m[nb][3];
       const float l_mine = lr.hd == 0 ? lsum[0] : lr.hd == 1 ? lsum[1] : lr.hd == 2 ? lsum[2] : lsum[3];
@@ -1103,20 +1140,14 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
   }
 
   if (idx < count) {
-    // q of the head this lane builds operands for (head 4 nb + ha), channels c0 .. c0 + 7, in the log2 domain; heads
-    // beyond gq read as 0
-    float qa[NB][8];
+    // q of the head this lane builds operands for (head 4 nb + ha), channels c0 .. c0 + 7; heads beyond gq read as 0
     uint32_t qh[NB][4];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
       const int h = nb * 4 + lr.ha;
       uint4 raw = make_uint4(0, 0, 0, 0);
       if (h < gq) raw = *reinterpret_cast<const uint4*>(q + ((long long)b * c.H_q + g * gq + h) * kHeadDim + lr.c0);
-      const uint32_t r[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) qa[nb][i] = (float)as_h2(r[i >> 1])[i & 1] * kAlpha;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) qh[nb][i] = as_u32(half2_t{(half_t)qa[nb][2 * i], (half_t)qa[nb][2 * i + 1]});
+      qh[nb][0] = raw.x; qh[nb][1] = raw.y; qh[nb][2] = raw.z; qh[nb][3] = raw.w;
     }
     // While a group is consumed the wave's next record is already requested: its key part right after the scores,
     // its value part right after E V.  The wave's last group is a copy of the loop body without requests (a request
@@ -1131,27 +1162,27 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
       const int nxt = group_of_round(++rd);
       if (nxt >= count) break;
       const uint32_t* src = rec0 + (long long)nxt * kRecordWords;
-      float sc[NB][8];
-      qk_phase<NB, BITS>(kr, min(kGroup, nq - idx * kGroup), qa, qh, lr, sc);
+      float sc[NB][8], off[NB];
+      qk_phase<NB, BITS>(kr, kGroup, qh, lr, sc, off);
       load_keys(kr, src, lr);
-      update_reference<NB>(sc, st, slack);
-      pv_phase<NB, BITS>(vr, sc, lr, st);
+      update_reference<NB>(sc, off, st, slack);
+      pv_phase<NB, BITS>(vr, sc, off, lr, st);
       load_values(vr, src, lr);
       idx = nxt;
     }
     if (idx < count_plain) {  // the wave's last group: nothing more to request
-      float sc[NB][8];
-      qk_phase<NB, BITS>(kr, min(kGroup, nq - idx * kGroup), qa, qh, lr, sc);
-      update_reference<NB>(sc, st, slack);
-      pv_phase<NB, BITS>(vr, sc, lr, st);
+      float sc[NB][8], off[NB];
+      qk_phase<NB, BITS>(kr, min(kGroup, nq - idx * kGroup), qh, lr, sc, off);
+      update_reference<NB>(sc, off, st, slack);
+      pv_phase<NB, BITS>(vr, sc, off, lr, st);
       idx = count;
     }
     if (SLIDING && idx < count) {  // sliding value window: the newest group, whose tokens from n_res on have fp16 values
-      float sc[NB][8];
-      qk_phase<NB, BITS>(kr, kGroup, qa, qh, lr, sc);
-      update_reference<NB>(sc, st, slack);
-      pv_phase<NB, BITS, true>(vr, sc, lr, st, nr);
-      pv_window_tail<NB>(reinterpret_cast<const half_t*>(c.v_res) + (long long)bh * c.R * kHeadDim, sc, nr, lr, st, lane, sAcc[wave]);
+      float sc[NB][8], off[NB];
+      qk_phase<NB, BITS>(kr, kGroup, qh, lr, sc, off);
+      update_reference<NB>(sc, off, st, slack);
+      pv_phase<NB, BITS, true>(vr, sc, off, lr, st, nr);
+      pv_window_tail<NB>(reinterpret_cast<const half_t*>(c.v_res) + (long long)bh * c.R * kHeadDim, sc, off, nr, lr, st, lane, sAcc[wave]);
     }
   }
 
@@ -1175,7 +1206,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
     if (lr.jd == 0) { sM[wave][h] = st.m[nb]; sL[wave][h] = l; }
 #pragma unroll
     for (int n = 0; n < 8; ++n)
-      sAcc[wave][h][16 * n + lr.jd] = ((st.acc[nb][n][0] + st.acc[nb][n][1]) + (st.acc[nb][n][2] + st.acc[nb][n][3])) + pz;
+      sAcc[wave][h][16 * n + lr.jd] = st.acc[nb][n] + pz;
   }
   __syncthreads();
   const bool direct = sDirect != 0;
@@ -1227,9 +1258,10 @@ __global__ __launch_bounds__(kThreads, BITS == 4 ? 2 : (NB == 1 ? 3 : 2)) void d
 // Splits per (sequence, kv head).  Measured on MI355X (256 compute units): the launch is fastest when all its
 // workgroups, the correction workgroups included, are resident at once at about two per compute unit -- a second
 // generation of workgroups pays the start-up and the merge tail again, and a compute unit that hosts a correction
-// workgroup next to two streaming ones finishes late.  The kernel for more than 4 query heads per kv head holds only
-// two workgroups per compute unit, and there four splits measured better than three.  At most 32 splits (the merge
-// walks the splits serially), at least one group per wave.
+// workgroup next to two streaming ones finishes late.  The kernel for more than 4 query heads per kv head spends more on
+// a group: there the streaming workgroups alone make up the two per compute unit (32 sequences of 32k tokens, 7 heads:
+// 3 splits 84.0 us, 4 76.5, 5 76.9 a step).  At most 32 splits (the merge walks the splits serially), at least one group
+// per wave.
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   constexpr int kTargetWorkgroups = 512, kMaxSplits = 32;
   const long long cap = (long long)c.max_groups * kGroup + c.R;
@@ -1255,8 +1287,9 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // more groups per wave): then the streaming workgroups go first, the longest of them decide when the launch ends,
   // and the correction fills the places the short sequences leave.
   const long long all_corr = c.S16 != nullptr ? (long long)c.H_kv * kCorrParts * ((c.B + kCorrSeqs - 1) / kCorrSeqs) : 0;
-  const long long resident = 256 * (gq <= 4 ? 3 : 2);
-  int corr_first = (2 * all_corr > resident && groups >= 16 * kWaves * s) ? 0 : 1;
+  // (More than 4 heads per kv head: the correction takes the third place of a compute unit, and going last it does not
+  // hold up the streaming workgroups: 77.5 -> 76.5 us a step for the shape above.)
+  int corr_first = ((gq > 4 || 2 * all_corr > 768) && groups >= 16 * kWaves * s) ? 0 : 1;
   // One or a few long sequences: about one streaming workgroup per compute unit.  The streaming workgroups that
   // would share a compute unit with a correction workgroup finish late (measured 3.6 us at a context of 128k), so
   // the correction workgroups pair up on compute units of their own (two runs of the grid lead with them) and the
