@@ -146,43 +146,62 @@ __device__ inline bool store_window_row(half_t* __restrict__ k_win, half_t* __re
 // One-token append: is the new row of any kv head of sequence b non-finite (key) or beyond fp16 once rotated (value)?
 // The caller's waves share the heads: wave `first` of `stride` takes the heads first, first + stride, ..., eight per
 // batch; the verdicts of the waves still have to be combined.  g: a head whose row may be read in place of a missing one.
+template <int N>
+struct NewRows {
+  uint32_t k[N], v[N];
+};
+template <int N>
+__device__ inline void request_new_rows(NewRows<N>& r, const kvlinc_cache& c, int b, int g, const half_t* __restrict__ k_new,
+                                        const half_t* __restrict__ v_new, int lane, int g0, int stride) {
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int g2 = g0 + stride * u;
+    const long long row = ((long long)b * c.H_kv + (g2 < c.H_kv ? g2 : g)) * kHeadDim + 2 * lane;
+    r.k[u] = *reinterpret_cast<const uint32_t*>(k_new + row);
+    r.v[u] = *reinterpret_cast<const uint32_t*>(v_new + row);
+  }
+}
+template <int N>
+__device__ inline bool new_rows_bad(const NewRows<N>& r, int lane) {
+  constexpr int kBatch = N < 4 ? N : 4;
+  bool refuse = false;
+  // A rotated value is at most sum_i |v_i| / sqrt(128): rows whose sum of magnitudes stays below
+  // 65504 sqrt(128) cannot overflow fp16 and need no rotation here (a non-finite v makes the sum non-finite).
+  float mag[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    refuse |= nonfinite_pair(r.k[u]);
+    const half2_t h = as_h2(r.v[u]);
+    mag[u] = fabsf((float)h[0]) + fabsf((float)h[1]);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) mag[u] = wave_allsum(mag[u]);
+#pragma unroll
+  for (int u0 = 0; u0 < N; u0 += kBatch) {
+    bool small = true;
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) small &= mag[u0 + u] < 741000.0f;
+    if (small) continue;
+    float x0[kBatch], x1[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const half2_t h = as_h2(r.v[u0 + u]);
+      x0[u] = (float)h[0];
+      x1[u] = (float)h[1];
+    }
+    fwht128_wave_multi<kBatch>(x0, x1, lane);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) refuse |= nonfinite_bits((half_t)x0[u]) || nonfinite_bits((half_t)x1[u]);
+  }
+  return refuse;
+}
 __device__ inline bool new_rows_of_all_heads_bad(const kvlinc_cache& c, int b, int g, const half_t* __restrict__ k_new,
                                                  const half_t* __restrict__ v_new, int lane, int first, int stride) {
   bool refuse = false;
   for (int g0 = first; g0 < c.H_kv; g0 += stride * 8) {
-    uint32_t chk_k[8], chk_v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int g2 = g0 + stride * u;
-      const long long row = ((long long)b * c.H_kv + (g2 < c.H_kv ? g2 : g)) * kHeadDim + 2 * lane;
-      chk_k[u] = *reinterpret_cast<const uint32_t*>(k_new + row);
-      chk_v[u] = *reinterpret_cast<const uint32_t*>(v_new + row);
-    }
-    // A rotated value is at most sum_i |v_i| / sqrt(128): rows whose sum of magnitudes stays below
-    // 65504 sqrt(128) cannot overflow fp16 and need no rotation here (a non-finite v makes the sum non-finite).
-    float mag[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      refuse |= nonfinite_pair(chk_k[u]);
-      const half2_t h = as_h2(chk_v[u]);
-      mag[u] = fabsf((float)h[0]) + fabsf((float)h[1]);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) mag[u] = wave_allsum(mag[u]);
-#pragma unroll
-    for (int u0 = 0; u0 < 8; u0 += 4) {
-      if (mag[u0] < 741000.0f && mag[u0 + 1] < 741000.0f && mag[u0 + 2] < 741000.0f && mag[u0 + 3] < 741000.0f) continue;
-      float x0[4], x1[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const half2_t h = as_h2(chk_v[u0 + u]);
-        x0[u] = (float)h[0];
-        x1[u] = (float)h[1];
-      }
-      fwht128_wave_multi<4>(x0, x1, lane);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) refuse |= nonfinite_bits((half_t)x0[u]) || nonfinite_bits((half_t)x1[u]);
-    }
+    NewRows<8> r;
+    request_new_rows(r, c, b, g, k_new, v_new, lane, g0, stride);
+    refuse |= new_rows_bad(r, lane);
   }
   return refuse;
 }
@@ -425,11 +444,15 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
 struct StateLds {
   half_t Wt[kRank / 2][kRowH];        // W_k of the half, [feature][channel]
   half_t ph[2][kRank / 2][kRowH];     // high / low term of phi s of the group, [feature][8 (token % 16) + token / 16]
-  float red[kWaves][kRank / 2];
+  float red[2][kWaves][kRank / 2];    // sums of phi and of phi (z + ctr s) over each wave's tokens
 };
 
+// Which channel a lane's column of tile ct is.  QUAD: four neighbouring channels per lane, so that a row of S moves in
+// 16-byte pieces -- a flush, which loads and stores S for every group (a step of 144 sequences of 1280 tokens 82.2 -> 81.2 us).
+// The other order reads the value tile in whole lines and adds to S in whole lines: the walk over many groups (one prompt of
+// 131072 tokens 505 us, 559 us with QUAD).
 struct StateAcc {
-  float4_t acc[2][4];  // S[32 (w / 2) + 16 ft + 4 kq + r][64 (w % 2) + 16 ct + l16]
+  float4_t acc[2][4];  // S[32 (w / 2) + 16 ft + 4 kq + r][channel 64 (w % 2) + ...], ... = 16 ct + l16, or 4 l16 + ct (QUAD)
   float P[8], Z[8];    // sums over this lane's tokens of phi and of phi (z + ctr s), feature 16 fo + l16
 };
 
@@ -441,7 +464,7 @@ struct KeyError {
 };
 template <int BITS>
 struct ValueCodes {
-  uint4 v[BITS / 2][2];  // value tile, channel blocks 4 (w % 2) .. + 3
+  uint2 v[BITS / 2][4];  // value tile: the two words of the lane's channel of tile ct, quarter kq
 };
 struct ValueScales {
   uint4 mine;   // (s, z) of the lane's four tokens
@@ -464,13 +487,25 @@ __device__ __forceinline__ void load_key_rows(KeyError<BITS>& e, const half_t* _
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) e.k[kk] = *reinterpret_cast<const uint4*>(row + 32 * kk + 8 * kq);
 }
-template <int BITS>
+template <int BITS, bool QUAD>
 __device__ __forceinline__ void load_value_codes(ValueCodes<BITS>& r, const uint32_t* rec, int wave, int lane) {
 #pragma unroll
-  for (int pl = 0; pl < BITS / 2; ++pl)
+  for (int pl = 0; pl < BITS / 2; ++pl) {
+    const uint32_t* tile = rec + Rec<BITS>::kValueTile + kPlaneWords * pl;
+    if constexpr (QUAD) {
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-      r.v[pl][m] = reinterpret_cast<const uint4*>(rec + Rec<BITS>::kValueTile + kPlaneWords * pl)[(2 * (wave & 1) + m) * 64 + lane];
+      for (int ct = 0; ct < 4; ++ct)  // channel 16 n + j, n = 4 (w % 2) + l16 / 4, j = 4 (l16 % 4) + ct
+        r.v[pl][ct] = *reinterpret_cast<const uint2*>(
+            tile + ((2 * (wave & 1) + ((lane >> 3) & 1)) * 64 + 4 * (lane & 3) + ct + 16 * (lane >> 4)) * 4 + 2 * ((lane >> 2) & 1));
+    } else {
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const uint4 t = reinterpret_cast<const uint4*>(tile)[(2 * (wave & 1) + m) * 64 + lane];
+        r.v[pl][2 * m] = make_uint2(t.x, t.y);
+        r.v[pl][2 * m + 1] = make_uint2(t.z, t.w);
+      }
+    }
+  }
 }
 template <int BITS>
 __device__ __forceinline__ void load_value_scales(ValueScales& r, const uint32_t* rec, int wave, int lane) {
@@ -696,8 +731,7 @@ __device__ __forceinline__ void state_update(const ValueCodes<BITS>& vc, float i
         half8_t op;
 #pragma unroll
         for (int pl = 0; pl < BITS / 2; ++pl) {
-          const uint4 v = vc.v[pl][ct >> 1];
-          const uint32_t w = (ct & 1) ? (wd ? v.w : v.z) : (wd ? v.y : v.x);
+          const uint32_t w = wd ? vc.v[pl][ct].y : vc.v[pl][ct].x;
           const half8_t o = codes_operand(fp4_codes(b ? w << 1 : w, pick), BITS == 4 && pl == 0 ? 4.0f : 1.0f);
           op = pl == 0 ? o : op + o;
         }
@@ -716,22 +750,38 @@ __device__ __forceinline__ void state_update(const ValueCodes<BITS>& vc, float i
   }
 }
 
-// Start: W_k of the half into LDS, the state rows of this wave into registers (fresh: a chunk that starts from zero).
-// P_old: P of feature tid (threads 0 .. 127).
-__device__ __forceinline__ void load_states(const kvlinc_cache& c, long long bh, int g, int fp, bool fresh, StateLds& L, StateAcc& st, float& P_old, int wave, int lane) {
-  const int tid = 64 * wave + lane, l16 = lane & 15, kq = lane >> 4;
-  const half_t* W0 = reinterpret_cast<const half_t*>(c.Wk) + ((long long)g * 2 + fp) * kHeadDim * (kRank / 2);
-  {  // transposed into LDS: a lane's B operand (8 channels of one feature) is then one 16-byte read.  Thread: feature
-     // tid % 128 (consecutive lanes read consecutive halfs of a row of W), 8 channels per step.
-    const int f = tid & 127, c0 = 8 * (tid >> 7);
+// W_k of the half goes to LDS transposed: a lane's B operand (8 channels of one feature) is then one 16-byte read.  Thread:
+// two features (a wave reads whole rows of W_k), 16 channels.  Requested first, put down when it has arrived.
+struct WkRegs {
+  uint32_t x[16];
+};
+__device__ __forceinline__ void request_wk(WkRegs& w, const kvlinc_cache& c, int g, int fp, int tid) {
+  const uint32_t* W0 = reinterpret_cast<const uint32_t*>(c.Wk) + ((long long)g * 2 + fp) * kHeadDim * (kRank / 4) +
+                       (16 * (tid >> 6)) * (kRank / 4) + (tid & 63);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      half8_t w;
+  for (int i = 0; i < 16; ++i) w.x[i] = W0[i * (kRank / 4)];
+}
+__device__ __forceinline__ void put_wk(const WkRegs& w, StateLds& L, int tid) {
+  const int f = 2 * (tid & 63), c0 = 16 * (tid >> 6);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) w[e] = W0[(long long)(c0 + 32 * i + e) * (kRank / 2) + f];
-      *reinterpret_cast<half8_t*>(&L.Wt[f][c0 + 32 * i]) = w;
+  for (int i = 0; i < 16; i += 8) {
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      lo[e] = __builtin_amdgcn_perm(w.x[i + 2 * e + 1], w.x[i + 2 * e], 0x05040100u);
+      hi[e] = __builtin_amdgcn_perm(w.x[i + 2 * e + 1], w.x[i + 2 * e], 0x07060302u);
     }
+    *reinterpret_cast<uint4*>(&L.Wt[f][c0 + i]) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    *reinterpret_cast<uint4*>(&L.Wt[f + 1][c0 + i]) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
   }
+}
+
+template <bool QUAD>
+__device__ __forceinline__ int state_channel(int wave, int l16, int ct) { return 64 * (wave & 1) + (QUAD ? 4 * l16 + ct : 16 * ct + l16); }
+// The state rows of this wave into registers (fresh: a chunk that starts from zero).  P_old: P of feature tid (threads 0 .. 127).
+template <bool QUAD>
+__device__ __forceinline__ void load_states(const kvlinc_cache& c, long long bh, int fp, bool fresh, StateAcc& st, float& P_old, int wave, int lane) {
+  const int tid = 64 * wave + lane, l16 = lane & 15, kq = lane >> 4;
 #pragma unroll
   for (int fo = 0; fo < 8; ++fo) st.P[fo] = st.Z[fo] = 0.0f;
   const half_t* tiles = reinterpret_cast<const half_t*>(c.S16) + bh * kRank * kHeadDim;
@@ -739,15 +789,25 @@ __device__ __forceinline__ void load_states(const kvlinc_cache& c, long long bh,
   for (int ft = 0; ft < 2; ++ft) {
     const int frow = (kRank / 2) * fp + 32 * (wave >> 1) + 16 * ft + 4 * kq;  // first of the 4 rows of S this lane holds
     const int tile = ((frow >> 6) * 2 + (wave & 1)) * 16 + ((frow & 63) >> 2);
+    if (fresh) {
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      if (fresh) {
-        st.acc[ft][ct] = float4_t{0.f, 0.f, 0.f, 0.f};
-      } else if (c.S != nullptr) {
+      for (int ct = 0; ct < 4; ++ct) st.acc[ft][ct] = float4_t{0.f, 0.f, 0.f, 0.f};
+    } else if (c.S != nullptr) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) st.acc[ft][ct][r] = c.S[(bh * kRank + frow + r) * kHeadDim + 64 * (wave & 1) + 16 * ct + l16];
-      } else {
-        const half4_t t16 = *reinterpret_cast<const half4_t*>(tiles + ((long long)tile * 64 + 16 * ct + l16) * 4);
+      for (int r = 0; r < 4; ++r) {
+        const float* row = c.S + (bh * kRank + frow + r) * kHeadDim;
+        if constexpr (QUAD) {
+          const float4 v = *reinterpret_cast<const float4*>(row + state_channel<true>(wave, l16, 0));
+          st.acc[ft][0][r] = v.x; st.acc[ft][1][r] = v.y; st.acc[ft][2][r] = v.z; st.acc[ft][3][r] = v.w;
+        } else {
+#pragma unroll
+          for (int ct = 0; ct < 4; ++ct) st.acc[ft][ct][r] = row[state_channel<false>(wave, l16, ct)];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct) {
+        const half4_t t16 = *reinterpret_cast<const half4_t*>(tiles + ((long long)tile * 64 + (state_channel<QUAD>(wave, l16, ct) & 63)) * 4);
 #pragma unroll
         for (int r = 0; r < 4; ++r) st.acc[ft][ct][r] = (float)t16[r];
       }
@@ -761,27 +821,29 @@ __device__ __forceinline__ void load_states(const kvlinc_cache& c, long long bh,
 // copy (if the cache keeps one), row-major, and to the binary16 tiles the decode kernel reads: tile (64-feature block, channel
 // half hh, feature step fb) holds S[64 block + 4 fb + k][64 hh + l] at [l][k].  An entry beyond the binary16 range is stored as
 // +-65504 and reported in the status word.  share: this is one chunk's share, added to the fp32 state with atomic additions.
-__device__ __forceinline__ void store_states(const kvlinc_cache& c, long long bh, int fp, bool share, StateLds& L, StateAcc& st, float P_old, int wave, int lane) {
-  const int tid = 64 * wave + lane, l16 = lane & 15, kq = lane >> 4;
-  float* redP = reinterpret_cast<float*>(&L.ph[0][0][0]);  // [kWaves][kRank / 2] (phi is not wanted any more)
-  lds_barrier();
+// share_phi_sums first, then a barrier, then store_states.
+__device__ __forceinline__ void share_phi_sums(StateLds& L, StateAcc& st, int wave, int lane) {
+  const int l16 = lane & 15;
 #pragma unroll
   for (int fo = 0; fo < 8; ++fo) {
     st.P[fo] = rows_sum(st.P[fo]);
     st.Z[fo] = rows_sum(st.Z[fo]);
   }
-  if (kq == 0) {
+  if (lane < 16) {
 #pragma unroll
     for (int fo = 0; fo < 8; ++fo) {
-      redP[wave * (kRank / 2) + 16 * fo + l16] = st.P[fo];
-      L.red[wave][16 * fo + l16] = st.Z[fo];
+      L.red[0][wave][16 * fo + l16] = st.P[fo];
+      L.red[1][wave][16 * fo + l16] = st.Z[fo];
     }
   }
-  lds_barrier();
+}
+template <bool QUAD>
+__device__ __forceinline__ void store_states(const kvlinc_cache& c, long long bh, int fp, bool share, const StateLds& L, const StateAcc& st, float P_old, int wave, int lane) {
+  const int tid = 64 * wave + lane, l16 = lane & 15, kq = lane >> 4;
   if (tid < kRank / 2) {
     float add = 0.0f;
 #pragma unroll
-    for (int w2 = 0; w2 < kWaves; ++w2) add += redP[w2 * (kRank / 2) + tid];
+    for (int w2 = 0; w2 < kWaves; ++w2) add += L.red[0][w2][tid];
     float* dst = c.P + bh * kRank + (kRank / 2) * fp + tid;
     if (share) __hip_atomic_fetch_add(dst, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     else *dst = P_old + add;
@@ -795,22 +857,29 @@ __device__ __forceinline__ void store_states(const kvlinc_cache& c, long long bh
     float z[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w2 = 0; w2 < kWaves; ++w2) {
-      const float4 zz = *reinterpret_cast<const float4*>(&L.red[w2][fl]);
+      const float4 zz = *reinterpret_cast<const float4*>(&L.red[1][w2][fl]);
       z[0] += zz.x; z[1] += zz.y; z[2] += zz.z; z[3] += zz.w;
     }
+    half_t t16[4][4];
 #pragma unroll
-    for (int ct = 0; ct < 4; ++ct) {
-      half4_t t16;
+    for (int r = 0; r < 4; ++r) {
+      float* row = c.S + (bh * kRank + frow + r) * kHeadDim;
+      float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float v = st.acc[ft][ct][r] + z[r];
-        float* dst = c.S + (bh * kRank + frow + r) * kHeadDim + 64 * (wave & 1) + 16 * ct + l16;
-        if (share) __hip_atomic_fetch_add(dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        else if (c.S != nullptr) *dst = v;
-        out_of_range |= !(fabsf(v) <= 65504.0f);
-        t16[r] = (half_t)fminf(fmaxf(v, -65504.0f), 65504.0f);
+      for (int ct = 0; ct < 4; ++ct) {
+        v[ct] = st.acc[ft][ct][r] + z[r];
+        out_of_range |= !(fabsf(v[ct]) <= 65504.0f);
+        t16[ct][r] = (half_t)fminf(fmaxf(v[ct], -65504.0f), 65504.0f);
+        if (share) __hip_atomic_fetch_add(row + state_channel<QUAD>(wave, l16, ct), v[ct], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        else if (!QUAD && c.S != nullptr) row[state_channel<QUAD>(wave, l16, ct)] = v[ct];
       }
-      if (!share) *reinterpret_cast<half4_t*>(tiles + ((long long)tile * 64 + 16 * ct + l16) * 4) = t16;
+      if (QUAD && c.S != nullptr) *reinterpret_cast<float4*>(row + state_channel<true>(wave, l16, 0)) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    if (!share) {
+#pragma unroll
+      for (int ct = 0; ct < 4; ++ct)  // (QUAD: neighbouring pieces, which the compiler joins)
+        *reinterpret_cast<half4_t*>(tiles + ((long long)tile * 64 + (state_channel<QUAD>(wave, l16, ct) & 63)) * 4) =
+            half4_t{t16[ct][0], t16[ct][1], t16[ct][2], t16[ct][3]};
     }
   }
   if (!share && __builtin_amdgcn_ballot_w64(out_of_range) != 0 && lane == 0) atomicOr(c.status, KVLINC_ST_STATE_RANGE);
@@ -877,8 +946,11 @@ __device__ void states_item(const kvlinc_cache& c, StatesLds& L, int item, const
     };
     request_keys(j_first);
     load_value_scales<BITS>(vs, rec0 + (long long)j_first * R::kWords, wave, lane);
-    load_value_codes<BITS>(vc, rec0 + (long long)j_first * R::kWords, wave, lane);
-    load_states(c, bh, g, fp, chunked, L.st, acc, P_old, wave, lane);
+    load_value_codes<BITS, false>(vc, rec0 + (long long)j_first * R::kWords, wave, lane);
+    WkRegs wk;
+    request_wk(wk, c, g, fp, tid);
+    load_states<false>(c, bh, fp, chunked, acc, P_old, wave, lane);
+    put_wk(wk, L.st, tid);
     if (tid < 64) store_key_affine<BITS>(L.ka[0], k_s, k_z, tid);
     lds_barrier();
     for (int j = j_first; j < j_last; ++j) {
@@ -895,9 +967,11 @@ __device__ void states_item(const kvlinc_cache& c, StatesLds& L, int item, const
       if (tid < 64) store_key_affine<BITS>(L.ka[par ^ 1], k_s, k_z, tid);
       lds_barrier();
       state_update<BITS>(vc, inv_F, acc, L.st, pick, wave, lane);
-      load_value_codes<BITS>(vc, rec0 + (long long)nxt * R::kWords, wave, lane);
+      load_value_codes<BITS, false>(vc, rec0 + (long long)nxt * R::kWords, wave, lane);
     }
-    store_states(c, bh, fp, chunked, L.st, acc, P_old, wave, lane);
+    share_phi_sums(L.st, acc, wave, lane);
+    lds_barrier();
+    store_states<false>(c, bh, fp, chunked, L.st, acc, P_old, wave, lane);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the additions of every wave are done before this owner counts itself in)
   }
   __syncthreads();
@@ -992,8 +1066,9 @@ struct TokenLds {
   __align__(16) uint32_t img[Rec<BITS>::kWords];
   __align__(16) KeyAffine ka;
   float row[kWaves][kHeadDim];  // new rows read ahead
-  int light[kListCap], heavy[kListCap];
+  int light[kListCap], heavy[kListCap], heavy_nq[kListCap], heavy_nr[kListCap];
   int n_light, n_heavy, last_flag;
+  int refuse[kWaves];
   // the item that thread w looked at is a light one whose new row wave w has read ahead; the sequence's counters as that
   // thread read them
   int ahead[kWaves], ahead_nq[kWaves], ahead_nr[kWaves], ahead_n[kWaves];
@@ -1001,83 +1076,128 @@ struct TokenLds {
 
 // The window of one (sequence, kv head) is full: its 128 tokens become a group.  Two owners, one per half of phi; both
 // quantize the group (the record feeds both halves of the state update), each writes half of the record.
+// Bound: latency, a chain of loads and phases on a few compute units.  So everything is requested at once, in the order in
+// which it is wanted; the verdict on the new rows, the staged values and the keys' minima share the first barrier; and the owner
+// counts itself in as soon as it has read the window, so that the answer is there when the states are done.  Measured (144
+// sequences of 1280 tokens, where nearly every launch has one that flushes): 16.3 us from the start of the launch, 20.5 us when
+// the rows, the window and the states were requested one after the other and the count came last.
 template <int BITS>
-__device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, const half_t* __restrict__ k_new,
-                           const half_t* __restrict__ v_new, const int32_t* __restrict__ n_new, int tid) {
+__device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, int nq, int nr, const half_t* __restrict__ k_new,
+                           const half_t* __restrict__ v_new, int tid) {
   using R = Rec<BITS>;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
   const int fp = item % kParts, p = item / kParts;
   const int b = p / c.H_kv, g = p % c.H_kv;
   const long long bh = p;
-  const Counters s = read_counters(c, b, n_new, 1, 0);
-  const AppendPlan plan = s.plan;
+  const AppendPlan plan = plan_append(nq, nr, 1, c.R, 0, c.max_groups);
   const half_t* k_res = reinterpret_cast<const half_t*>(c.k_res) + bh * c.R * kHeadDim;
   const bool states_live = c.S16 != nullptr;
-  // (The loads of the window and of the states are issued before the new rows are looked at: they are wanted in any case
-  // but a refusal, and nothing is stored to global memory before the verdict.)
-  stage_window_values<kWaves>(reinterpret_cast<const half_t*>(c.v_res) + bh * c.R * kHeadDim, kGroup, L.st.ph[0], tid);
+  // (Nothing is stored to global memory before the verdict on the new rows.)
+  NewRows<1> rows;  // of the first eight heads, one per wave
+  request_new_rows(rows, c, b, g, k_new, v_new, lane, wave, kWaves);
+  KeyTile<kWaves> keys;
+#pragma unroll
+  for (int i = 0; i < 32 / kWaves; ++i)
+    keys.raw[i] = *reinterpret_cast<const uint4*>(k_res + (long long)key_token<kWaves>(i, wave, lane) * kHeadDim + 8 * l16);
   StateAcc acc;
   float P_old = 0.0f;
   KeyError<BITS> ke;
-  if (states_live) {
-    load_states(c, bh, g, fp, false, L.st, acc, P_old, wave, lane);
-    load_key_rows<BITS>(ke, k_res + (long long)state_row_token(wave, l16) * kHeadDim, kq);
-  }
-  // A flush changes live state (S, P, the window's first slot) in every kv head: the new row of every kv head of this
-  // sequence is looked at first; the verdict is the same in all workgroups of the sequence.
-  if (__syncthreads_or(new_rows_of_all_heads_bad(c, b, g, k_new, v_new, lane, wave, kWaves))) {
-    if (tid == 0) {
-      if (fp == 0) atomicOr(c.status, KVLINC_ST_NONFINITE);
-      bool clean;
-      if (arrive(c, b, 1, true, &clean)) finish(c, b, s.nq, s.n, plan, false);
-    }
-    return;
-  }
-  quantize_group<BITS, kWaves>(k_res, k_res, k_res, L.st.ph[0], kGroup, kGroup, L.q, L.img, wave, lane);
+  WkRegs wk;
   {
-    uint4* rec = reinterpret_cast<uint4*>(c.groups + (bh * c.max_groups + s.nq / kGroup) * R::kWords);
+    WindowValues<kWaves> win;
+    request_window_values<kWaves>(win, reinterpret_cast<const half_t*>(c.v_res) + bh * c.R * kHeadDim, kGroup, tid);
+    if (states_live) {
+      load_key_rows<BITS>(ke, k_res + (long long)state_row_token(wave, l16) * kHeadDim, kq);
+      request_wk(wk, c, g, fp, tid);
+      load_states<true>(c, bh, fp, false, acc, P_old, wave, lane);
+    }
+    // A flush changes live state (S, P, the window's first slot) in every kv head: the new row of every kv head of this
+    // sequence is looked at first; the verdict is the same in all workgroups of the sequence.
+    bool bad = new_rows_bad(rows, lane);
+    if (c.H_kv > kWaves) bad |= new_rows_of_all_heads_bad(c, b, g, k_new, v_new, lane, wave + kWaves, kWaves);
+    const bool refuse = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 0) L.refuse[wave] = refuse ? 1 : 0;
+    key_minmax<kWaves>(keys, kGroup, L.q, wave, lane);
+    put_window_values<kWaves>(win, kGroup, L.st.ph[0], tid);
+  }
+  lds_barrier();
+  {
+    int refused = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) refused |= L.refuse[w];
+    if (refused != 0) {
+      if (tid == 0) {
+        if (fp == 0) atomicOr(c.status, KVLINC_ST_NONFINITE);
+        bool clean;
+        if (arrive(c, b, 1, true, &clean)) finish(c, b, nq, 1, plan, false);
+      }
+      return;
+    }
+  }
+  // the record (its image in LDS): key parameters by two waves, values by all, then the key codes
+  if (tid < kGroup) {
+    key_params<BITS, kWaves>(L.q, tid, L.img);
+    const half_t* img16 = reinterpret_cast<const half_t*>(L.img);
+    const float s = (float)img16[2 * R::kKeyScale + tid], z = (float)img16[2 * R::kKeyZero + tid];
+    L.ka.s[tid] = s;
+    L.ka.mid[tid] = __builtin_fmaf(s, R::kCentre, z);
+  }
+  {
+    const RowLane rl = row_lane(lane);
+    Row w;
+    load_row(w, L.st.ph[0][value_pass_token(wave, rl)], rl.q);
+    half2_t h[16];
+    row_pairs(w, h);
+    quantize_value_pass<BITS>(h, wave, rl, lane, L.img);
+  }
+  lds_barrier();
+  key_codes<BITS, kWaves>(keys, kGroup, L.q, wave, lane, L.img);
+  if (states_live) {
+    put_wk(wk, L.st, tid);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(ke.k[kk].x), "+v"(ke.k[kk].y), "+v"(ke.k[kk].z), "+v"(ke.k[kk].w));  // (they have arrived, too)
+  }
+  lds_barrier();
+  // every wave has the window's rows: count this part in.  The arrival that completes the sequence stores the new row -- raw key,
+  // rotated value -- in slot 0 for all its kv heads and commits.
+  int before = 0;
+  if (tid == 0) before = __hip_atomic_fetch_add(c.split_done + (long long)b * c.H_kv, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  {
+    uint4* rec = reinterpret_cast<uint4*>(c.groups + (bh * c.max_groups + nq / kGroup) * R::kWords);
     constexpr int kHalf = R::kWords / 8;
     for (int i = kHalf * fp + tid; i < kHalf * (fp + 1); i += kThreads) rec[i] = reinterpret_cast<const uint4*>(L.img)[i];
   }
+  ValueCodes<BITS> vc;
+  float inv_F = 1.0f;
+  const uint32_t pick = code_bits_mask();
   if (states_live) {
-    ValueCodes<BITS> vc;
     ValueScales vs;
     load_key_codes<BITS>(ke, L.img, wave, lane);
     load_value_scales<BITS>(vs, L.img, wave, lane);
-    load_value_codes<BITS>(vc, L.img, wave, lane);
-    const uint32_t pick = code_bits_mask();
-    if (tid < 64) store_key_affine<BITS>(L.ka, L.img[R::kKeyScale + tid], L.img[R::kKeyZero + tid], tid);
-    lds_barrier();
+    load_value_codes<BITS, true>(vc, L.img, wave, lane);
+    const float F = scale_factor(vs, inv_F);
     float4_t d[8];
     state_logits<BITS>(ke, L.ka, L.st, pick, lane, d);
-    float inv_F;
-    const float F = scale_factor(vs, inv_F);
     state_softmax<BITS>(d, vs, F, kGroup, acc, L.st, wave, lane);
-    lds_barrier();
-    state_update<BITS>(vc, inv_F, acc, L.st, pick, wave, lane);
-    store_states(c, bh, fp, false, L.st, acc, P_old, wave, lane);
+    share_phi_sums(L.st, acc, wave, lane);
   }
-  // count this part in; the arrival that completes the sequence stores the new row -- raw key, rotated value -- in slot 0
-  // for all its kv heads (only now have all parts staged the window's old rows) and commits
-  __syncthreads();
-  if (tid == 0) {
-    bool clean;
-    const bool last = arrive(c, b, 1, false, &clean);
-    L.last_flag = last ? (clean ? 2 : 1) : 0;
-  }
-  __syncthreads();
+  if (tid == 0) L.last_flag = (before & (kFaultVote - 1)) == kParts * c.H_kv - 1 ? (before < kFaultVote ? 2 : 1) : 0;
+  lds_barrier();
   const int flag = L.last_flag;
+  if (states_live) {
+    state_update<BITS>(vc, inv_F, acc, L.st, pick, wave, lane);
+    store_states<true>(c, bh, fp, false, L.st, acc, P_old, wave, lane);
+  }
   if (flag == 2) {
     for (int g2 = wave; g2 < c.H_kv; g2 += kWaves) {
       const long long bh2 = (long long)b * c.H_kv + g2;
       store_window_row(reinterpret_cast<half_t*>(c.k_res) + bh2 * c.R * kHeadDim,
-                       reinterpret_cast<half_t*>(c.v_res) + bh2 * c.R * kHeadDim, s.nr - plan.n_flush, k_new + bh2 * kHeadDim,
+                       reinterpret_cast<half_t*>(c.v_res) + bh2 * c.R * kHeadDim, nr - plan.n_flush, k_new + bh2 * kHeadDim,
                        v_new + bh2 * kHeadDim, lane);
     }
   }
-  __syncthreads();
-  if (flag != 0 && tid == 0) finish(c, b, s.nq, s.n, plan, flag == 2);
+  if (flag != 0 && tid == 0) finish(c, b, nq, 1, plan, flag == 2);
 }
 
 // Items as in append_states_kernel, without chunks.
@@ -1139,7 +1259,10 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
             if (arrive(c, b, 1, false, &clean)) finish(c, b, s.nq, s.n, s.plan, clean);
           }
         } else {
-          L.heavy[atomicAdd(&L.n_heavy, 1)] = (int)(p * kParts) + own;
+          const int at = atomicAdd(&L.n_heavy, 1);
+          L.heavy[at] = (int)(p * kParts) + own;
+          L.heavy_nq[at] = s.nq;
+          L.heavy_nr[at] = s.nr;
         }
       }
     }
@@ -1160,7 +1283,7 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
       // the kernel, where every launch -- most of them flush nothing -- would pay for it)
       int tid_here = tid;
       asm volatile("" : "+v"(tid_here));
-      flush_item<BITS>(c, L, L.heavy[i], k_new, v_new, n_new, tid_here);
+      flush_item<BITS>(c, L, L.heavy[i], L.heavy_nq[i], L.heavy_nr[i], k_new, v_new, tid_here);
       __syncthreads();
     }
     __syncthreads();

@@ -408,27 +408,40 @@ __device__ __forceinline__ void key_codes(KeyTile<NW>& k, int valid, const Quant
 // Window values live 4 slots per channel; this brings the first `rows` slots into LDS rows of kRowH halfs (threads of a
 // workgroup of 64 NW; a barrier has to follow).
 template <int NW>
-__device__ __forceinline__ void stage_window_values(const half_t* __restrict__ v_win, int rows, half_t (*st)[kRowH], int tid) {
-  const int n = ((rows + 3) >> 2) * 64;  // 16-byte pieces: 4 slots of 2 channels
-  constexpr int kSteps = 2048 / (64 * NW);
-  uint4 w[kSteps];
+struct WindowValues {
+  uint4 w[2048 / (64 * NW)];  // 16-byte pieces: 4 slots of 2 channels
+};
+template <int NW>
+__device__ __forceinline__ void request_window_values(WindowValues<NW>& r, const half_t* __restrict__ v_win, int rows, int tid) {
+  const int n = ((rows + 3) >> 2) * 64;
 #pragma unroll
-  for (int i = 0; i < kSteps; ++i) {
+  for (int i = 0; i < 2048 / (64 * NW); ++i) {
     const int it = tid + 64 * NW * i;
-    w[i] = make_uint4(0, 0, 0, 0);
-    if (it < n) w[i] = *reinterpret_cast<const uint4*>(v_win + ((long long)(it >> 6) * kHeadDim + 2 * (it & 63)) * 4);
+    r.w[i] = make_uint4(0, 0, 0, 0);
+    if (it < n) r.w[i] = *reinterpret_cast<const uint4*>(v_win + ((long long)(it >> 6) * kHeadDim + 2 * (it & 63)) * 4);
   }
+}
+template <int NW>
+__device__ __forceinline__ void put_window_values(const WindowValues<NW>& r, int rows, half_t (*st)[kRowH], int tid) {
+  const int n = ((rows + 3) >> 2) * 64;
 #pragma unroll
-  for (int i = 0; i < kSteps; ++i) {
+  for (int i = 0; i < 2048 / (64 * NW); ++i) {
     const int it = tid + 64 * NW * i;
     if (it < n) {
+      const uint4 w = r.w[i];
       uint32_t* row = reinterpret_cast<uint32_t*>(&st[4 * (it >> 6)][2 * (it & 63)]);
-      row[0] = __builtin_amdgcn_perm(w[i].z, w[i].x, 0x05040100u);
-      row[kRowH / 2] = __builtin_amdgcn_perm(w[i].z, w[i].x, 0x07060302u);
-      row[kRowH] = __builtin_amdgcn_perm(w[i].w, w[i].y, 0x05040100u);
-      row[3 * kRowH / 2] = __builtin_amdgcn_perm(w[i].w, w[i].y, 0x07060302u);
+      row[0] = __builtin_amdgcn_perm(w.z, w.x, 0x05040100u);
+      row[kRowH / 2] = __builtin_amdgcn_perm(w.z, w.x, 0x07060302u);
+      row[kRowH] = __builtin_amdgcn_perm(w.w, w.y, 0x05040100u);
+      row[3 * kRowH / 2] = __builtin_amdgcn_perm(w.w, w.y, 0x07060302u);
     }
   }
+}
+template <int NW>
+__device__ __forceinline__ void stage_window_values(const half_t* __restrict__ v_win, int rows, half_t (*st)[kRowH], int tid) {
+  WindowValues<NW> r;
+  request_window_values<NW>(r, v_win, rows, tid);
+  put_window_values<NW>(r, rows, st, tid);
 }
 
 // The record of one group into the LDS image img (Rec<BITS>::kWords).  Tokens 0 .. nrg - 1 come from the window (raw keys
