@@ -68,17 +68,19 @@ def _load():
 lib = _load()
 
 
+# A generation step of a small batch takes about as long on the GPU as these calls take on the host: addresses go through the
+# declared argument types as plain integers, and the current stream is asked for as a raw handle.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     if hasattr(stream, "cuda_stream"):
-        return ctypes.c_void_p(stream.cuda_stream)
-    return ctypes.c_void_p(int(stream))
+        return stream.cuda_stream
+    return int(stream)
 
 
 def _struct(cache):
@@ -198,8 +200,12 @@ class KVLincCache:
         import torch
         if out is None:
             out = torch.empty_like(q)
-        ws = self.workspace(max_context)
-        rc = kvlinc_decode_attention(self, q, out, ws, ws.numel() * 4, max_context, stream)
+        # the library checks the size before it launches anything: asked for only where the workspace at hand does not do
+        ws = self._ws
+        rc = KVLINC_EWORKSPACE if ws is None else kvlinc_decode_attention(self, q, out, ws, ws.numel() * 4, max_context, stream)
+        if rc == KVLINC_EWORKSPACE:
+            ws = self.workspace(max_context)
+            rc = kvlinc_decode_attention(self, q, out, ws, ws.numel() * 4, max_context, stream)
         if rc != KVLINC_OK:
             raise KVLincError("kvlinc_decode_attention: " + kvlinc_strerror(rc))
         return out
