@@ -45,6 +45,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kAlpha = kLog2e * 0.08838834764831845f;  // log2(e) / sqrt(128)
 
 typedef int v8i_t __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef short short2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 
@@ -56,9 +57,12 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void st_coherent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
-__device__ __forceinline__ float ld_coherent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+__device__ __forceinline__ float2 ld_coherent2(const float* p) {  // two neighbours, 8-byte aligned
+  const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  return __builtin_bit_cast(float2, v);
 }
+// Four neighbours, 16-byte aligned, at `bytes` beyond a wave-uniform base (the same load: sc0 sc1).
+constexpr int kCoherentLoad = 1 | 16;
 
 __device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ uint32_t as_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -205,7 +209,6 @@ __device__ __forceinline__ void put_terms(uint32_t* ex, int at, const uint32_t (
 #pragma unroll
   for (int k = 0; k < 3; ++k) *reinterpret_cast<u32x2_t*>(ex + at + 32 * k) = u32x2_t{t[k][0], t[k][1]};
 }
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ v8i_t get_operand(const uint32_t* ex, int at) {
   const u32x4_t a = *reinterpret_cast<const u32x4_t*>(ex + at), b = *reinterpret_cast<const u32x4_t*>(ex + at + 4);
   return v8i_t{(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)b[0], (int)b[1], (int)b[2], (int)b[3]};
@@ -780,14 +783,18 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
 }
 
 // ---- merge the splits of one (sequence, query head), add the correction, rotate back (Alg. 1 lines 13-15; Eq. 5;
-// Sec. 3.1).  Run by one wave of the split that arrives last; lane l owns channels 2l and 2l+1. ----------------------
+// Sec. 3.1).  Run by one wave of the split that arrives last. ----------------------------------------------------------
 
-// MB = splits whose partial results are requested together; LOCAL: the partial results are this workgroup's own and
-// lie in LDS (plain loads), everything else alike
-template <int MB, bool LOCAL = false>
+// Lane j holds (m, l) of split j, so that the weights of all splits come from one load and one reduction; the rows are
+// requested all at once, two splits per load, 16 bytes a lane.  (A walk over the splits in batches of 8 that each waited for
+// their own m took 4.5 us for the 30 splits of a sequence of 131072 tokens; a step 27.6 -> 25.0 us.)
+// NP: loads, at least n_splits / 2; LOCAL: the partial results are this workgroup's own and lie in LDS (plain loads, one split).
+// Lane l ends up with the channels 4 (l % 32) + 2 (l / 32), + 1.
+template <int NP, bool LOCAL = false>
 __device__ __forceinline__ void merge_row(const float* __restrict__ p0, const float* __restrict__ corr, int n_splits,
                                           int row, int lane, bool literal, half_t* __restrict__ out) {
   // p0: the row's partial results, n_splits of kPartStride floats
+  const int half = lane >> 5, ch0 = 4 * (lane & 31) + 2 * half;
   // correction parts first (their values are needed last): {Cd_r, m_r, Z_r, -, Cn_r[128]}
   float c_cd[kCorrParts], c_m[kCorrParts], c_z[kCorrParts], c_x[kCorrParts], c_y[kCorrParts];
   if (corr != nullptr) {
@@ -795,42 +802,46 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ p0, const fl
 #pragma unroll
     for (int r = 0; r < kCorrParts; ++r) {
       const float* pr = cr + r * kPartStride;
-      c_cd[r] = ld_coherent(pr); c_m[r] = ld_coherent(pr + 1); c_z[r] = ld_coherent(pr + 2);
-      c_x[r] = ld_coherent(pr + 4 + 2 * lane); c_y[r] = ld_coherent(pr + 5 + 2 * lane);
+      const float2 cm = ld_coherent2(pr), z = ld_coherent2(pr + 2), xy = ld_coherent2(pr + 4 + ch0);
+      c_cd[r] = cm.x; c_m[r] = cm.y; c_z[r] = z.x;
+      c_x[r] = xy.x; c_y[r] = xy.y;
     }
   }
-  // running merge over batches of splits, every batch requested at once
-  float M = -INFINITY, n0 = 0.f, n1 = 0.f, den = 0.f;
-  for (int j0 = 0; j0 < n_splits; j0 += MB) {
-    float mj[MB], lj[MB], ax[MB], ay[MB];
+  float2 ml;
+  u32x4_t a[NP];
+  if (LOCAL) {
+    ml = make_float2(p0[0], p0[1]);
+  } else {
+    ml = ld_coherent2(p0 + (long long)min(lane, n_splits - 1) * kPartStride);
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p0), 0, n_splits * kPartStride * 4, 0x00027000);
 #pragma unroll
-    for (int k = 0; k < MB; ++k) {
-      const float* pj = p0 + (long long)(j0 + k < n_splits ? j0 + k : n_splits - 1) * kPartStride;
-      if (LOCAL) {
-        mj[k] = pj[0]; lj[k] = pj[1];
-        ax[k] = pj[4 + 2 * lane]; ay[k] = pj[5 + 2 * lane];
-      } else {
-        mj[k] = ld_coherent(pj); lj[k] = ld_coherent(pj + 1);
-        ax[k] = ld_coherent(pj + 4 + 2 * lane); ay[k] = ld_coherent(pj + 5 + 2 * lane);
-      }
+    for (int k = 0; k < NP; ++k)
+      a[k] = __builtin_amdgcn_raw_buffer_load_b128(rows, min(2 * k + half, n_splits - 1) * (kPartStride * 4) + 16 + 16 * (lane & 31), 0, kCoherentLoad);
+  }
+  float M, den, n0 = 0.f, n1 = 0.f;
+  if (LOCAL) {
+    M = ml.x;
+    den = ml.y;
+    n0 = p0[4 + ch0]; n1 = p0[5 + ch0];
+  } else {
+    // (the lanes beyond n_splits hold a copy of the last split: its m does not change the maximum, its weight is cleared)
+    M = wave_allmax(ml.x);
+    const float w = lane < n_splits && ml.x != -INFINITY ? exp2f(ml.x - M) : 0.f;
+    den = wave_allsum(w * ml.y);
+    float n[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      const float w0 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k)), w1 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k + 1));
+      const float wk = half != 0 ? w1 : w0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) n[i] = fmaf(wk, as_f32(a[k][i]), n[i]);
     }
-    float Mb = M;
+    // the even splits of the lower 32 lanes and the odd ones of the upper: the lower lanes finish the first two channels
 #pragma unroll
-    for (int k = 0; k < MB; ++k)
-      if (j0 + k < n_splits) Mb = fmaxf(Mb, mj[k]);
-    if (Mb == -INFINITY) continue;
-    const float f = exp2f(M - Mb);  // 0 while nothing has been merged yet
-    n0 *= f; n1 *= f; den *= f;
-#pragma unroll
-    for (int k = 0; k < MB; ++k) {
-      if (j0 + k < n_splits && mj[k] != -INFINITY) {
-        const float w = exp2f(mj[k] - Mb);
-        n0 = fmaf(w, ax[k], n0);
-        n1 = fmaf(w, ay[k], n1);
-        den = fmaf(w, lj[k], den);
-      }
+    for (int i = 0; i < 2; ++i) {
+      const auto t = __builtin_amdgcn_permlane32_swap(as_bits(n[i]), as_bits(n[i + 2]), false, false);
+      (i == 0 ? n0 : n1) = as_f32(t[0]) + as_f32(t[1]);
     }
-    M = Mb;
   }
   float y0 = 0.f, y1 = 0.f;
   if (M != -INFINITY) {
@@ -871,7 +882,7 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ p0, const fl
     y0 = (fa * n0 + fb * cn0) / d;
     y1 = (fa * n1 + fb * cn1) / d;
   }
-  // y = y_rot H^T: butterflies over the 128 channels, two per lane
+  // y = y_rot H^T: butterflies over the 128 channels, two per lane (bit 1 of the channel is bit 5 of the lane)
   {
     const float a = y0 + y1, bb = y0 - y1;
     y0 = a; y1 = bb;
@@ -884,18 +895,17 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ p0, const fl
     }
   }
   const half2_t r = {(half_t)(y0 * 0.08838834764831845f), (half_t)(y1 * 0.08838834764831845f)};
-  *reinterpret_cast<uint32_t*>(out + (long long)row * kHeadDim + 2 * lane) = as_u32(r);
+  *reinterpret_cast<uint32_t*>(out + (long long)row * kHeadDim + ch0) = as_u32(r);
 }
 
-// ---- launch 1 -------------------------------------------------------------------------------------------------------
-
-
+constexpr int kMaxSplits = 32;  // splits a sequence may take at most: a lane of the merge, and a pair of its registers, each
 __device__ __forceinline__ void merge_rows(const float* __restrict__ part, const float* __restrict__ corr,
                                            int max_splits, int n_splits, int row, int lane, bool literal,
                                            half_t* __restrict__ out) {
   const float* p0 = part + (long long)row * max_splits * kPartStride;
-  if (n_splits <= 4) merge_row<4>(p0, corr, n_splits, row, lane, literal, out);
-  else merge_row<8>(p0, corr, n_splits, row, lane, literal, out);
+  if (n_splits <= 4) merge_row<2>(p0, corr, n_splits, row, lane, literal, out);
+  else if (n_splits <= 12) merge_row<6>(p0, corr, n_splits, row, lane, literal, out);
+  else merge_row<kMaxSplits / 2>(p0, corr, n_splits, row, lane, literal, out);
 }
 
 // Splits the groups of a sequence are cut into.  The host fixes the average over the batch (avg_splits) and the most
@@ -1238,7 +1248,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   if (direct) {
     __syncthreads();
     for (int h = wave; h < gq; h += kWaves)
-      merge_row<4, true>(own + h * kPartStride, corr, 1, b * c.H_q + g * gq + h, lane,
+      merge_row<1, true>(own + h * kPartStride, corr, 1, b * c.H_q + g * gq + h, lane,
                          (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);
     if (tid == 0 && n_parts != 0) c.split_done[bh] = 0;  // the arrivals of the correction workgroups
     return;
@@ -1260,10 +1270,11 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
 // generation of workgroups pays the start-up and the merge tail again, and a compute unit that hosts a correction
 // workgroup next to two streaming ones finishes late.  The kernel for more than 4 query heads per kv head spends more on
 // a group: there the streaming workgroups alone make up the two per compute unit (32 sequences of 32k tokens, 7 heads:
-// 3 splits 84.0 us, 4 76.5, 5 76.9 a step).  At most 32 splits (the merge walks the splits serially), at least one group
-// per wave.
+// 3 splits 84.0 us, 4 76.5, 5 76.9 a step).  At most 32 splits (the merge holds a row of each
+// in registers; 40 to 64 for one sequence of 131072 tokens, two workgroups per compute unit: 28.2 to 30.8 us a step against 25.0 with 30),
+// at least one group per wave.
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
-  constexpr int kTargetWorkgroups = 512, kMaxSplits = 32;
+  constexpr int kTargetWorkgroups = 512;
   const long long cap = (long long)c.max_groups * kGroup + c.R;
   const long long ctx = (max_context > 0 && max_context < cap) ? max_context : cap;
   long long groups = (ctx + kGroup - 1) / kGroup;
