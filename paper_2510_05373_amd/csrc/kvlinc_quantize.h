@@ -65,6 +65,18 @@ __device__ __forceinline__ void row_pairs(const Row& r, half2_t (&h)[16]) {  // 
   }
 }
 
+// Sum and difference of the two binary16 numbers of a register in binary32, one instruction each.
+__device__ __forceinline__ float pair_sum(half2_t h) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(as_u32(h)));
+  return r;
+}
+__device__ __forceinline__ float pair_difference(half2_t h) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(as_u32(h)));
+  return r;
+}
+
 // Rotation of 16 rows by a wave.  Stage order h = 1, 2, ..., 64 with (x[i], x[i+h]) <- (x[i] + x[i+h], x[i] - x[i+h]) for
 // (i & h) == 0, in binary32, then the binary32 scale and one rounding to fp16.  Five stages pair registers of one lane,
 // two pair neighbouring lanes (other + own in the lower lane, other - own in the upper: one move and one exact
@@ -73,9 +85,8 @@ __device__ __forceinline__ void rotate_rows(half2_t (&h)[16], int q) {
   float x[32];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    const float a = (float)h[i][0], b = (float)h[i][1];
-    x[2 * i] = a + b;
-    x[2 * i + 1] = a - b;
+    x[2 * i] = pair_sum(h[i]);
+    x[2 * i + 1] = pair_difference(h[i]);
   }
 #pragma unroll
   for (int s = 2; s <= 4; s <<= 1) {
@@ -179,12 +190,14 @@ __device__ inline uint32_t threshold2(float z, float s, int k) {
   return s == 0.0f ? 0x7bffu : bits;   // 65504: no finite x is above it
 }
 
-// Bit pairs of the codes of two elements (one register of binary16): hi in bits 15 / 31, lo in bits 13 / 29; a code 0, 1,
-// 2, 3 is (1,1), (1,0), (0,0), (0,1).  The sign of T_k - x tells x > T_k (never confused by zeros: T_k is not -0).
-__device__ __forceinline__ uint32_t symbols2(half2_t x, half2_t t1, half2_t t2, half2_t t3) {
-  const uint32_t d1 = as_u32(t1 - x), d2 = as_u32(t2 - x), d3 = as_u32(t3 - x);
-  const uint32_t lo = (~d1 | d3) >> 2;
-  return (~d2 & 0x80008000u) | (lo & 0x20002000u);
+// Bit pairs of the codes of four elements (two registers of binary16): hi in bit 7, lo in bit 5 of every byte; a code 0, 1,
+// 2, 3 is (1,1), (1,0), (0,0), (0,1).  The sign of T_k - x tells x > T_k (never confused by zeros: T_k is not -0).  sel: the
+// order of the bytes (1, 3 = the elements of xa, 5, 7 = those of xb).
+__device__ __forceinline__ uint32_t symbols2(half2_t xa, half2_t xb, half2_t t1a, half2_t t2a, half2_t t3a, half2_t t1b, half2_t t2b,
+                                             half2_t t3b, uint32_t sel) {
+  const uint32_t la = ~as_u32(t1a - xa) | as_u32(t3a - xa), lb = ~as_u32(t1b - xb) | as_u32(t3b - xb);
+  const uint32_t d2 = __builtin_amdgcn_perm(as_u32(t2b - xb), as_u32(t2a - xa), sel), lo = __builtin_amdgcn_perm(lb, la, sel);
+  return (~d2 & 0x80808080u) | ((lo >> 2) & 0x20202020u);
 }
 // The same for four 2-bit codes (digits), one per byte in bits `at`, `at` + 1: hi in bit 7, lo in bit 5 of every byte.
 template <int AT>
@@ -267,7 +280,7 @@ __device__ __forceinline__ bool quantize_value_pass(const half2_t (&h)[16], int 
     const half2_t t1 = as_h2(dpp_u<0x00>(mine)), t2 = as_h2(dpp_u<0x55>(mine)), t3 = as_h2(dpp_u<0xAA>(mine));
 #pragma unroll
     for (int k = 0; k < 8; ++k)
-      out[k] = __builtin_amdgcn_perm(symbols2(h[2 * k + 1], t1, t2, t3), symbols2(h[2 * k], t1, t2, t3), 0x07050301u);
+      out[k] = symbols2(h[2 * k], h[2 * k + 1], t1, t2, t3, t1, t2, t3, 0x07050301u);
     put_value_bytes(out, pass, rl, img + R::kValueTile);
   } else {
     uint32_t low[8];
@@ -369,6 +382,12 @@ __device__ __forceinline__ void key_codes(KeyTile<NW>& k, int valid, const Quant
       inv_s[e] = __builtin_amdgcn_rcpf(s[e]);
     }
   }
+  if (BITS == 2 && valid < kGroup) {  // padding tokens: -65504, above no T_k
+    constexpr uint32_t kLowest = 0xFBFFFBFFu;
+#pragma unroll
+    for (int i = 0; i < 32 / NW; ++i)
+      if (key_token<NW>(i, wave, lane) >= valid) k.raw[i] = make_uint4(kLowest, kLowest, kLowest, kLowest);
+  }
   const int wbase = 16 * (sub >> 2) * 4 + ((sub >> 1) & 1);
 #pragma unroll
   for (int i = 0; i < 32 / NW; i += 2) {
@@ -377,12 +396,10 @@ __device__ __forceinline__ void key_codes(KeyTile<NW>& k, int valid, const Quant
     for (int d = 0; d < 2; ++d) {
       const uint4 r = k.raw[i + d];
       const uint32_t x[4] = {r.x, r.y, r.z, r.w};
-      const bool live = valid == kGroup || key_token<NW>(i + d, wave, lane) < valid;  // padding tokens: code 0
+      const bool live = BITS == 2 || valid == kGroup || key_token<NW>(i + d, wave, lane) < valid;  // padding tokens: code 0
       if constexpr (BITS == 2) {
-        uint32_t y[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) y[v] = symbols2(as_h2(live ? x[v] : 0xFBFFFBFFu), t[0][v], t[1][v], t[2][v]);  // (-65504: above no T_k)
-        const uint32_t y01 = __builtin_amdgcn_perm(y[1], y[0], 0x07030501u), y23 = __builtin_amdgcn_perm(y[3], y[2], 0x07030501u);
+        const uint32_t y01 = symbols2(as_h2(x[0]), as_h2(x[1]), t[0][0], t[1][0], t[2][0], t[0][1], t[1][1], t[2][1], 0x07030501u);
+        const uint32_t y23 = symbols2(as_h2(x[2]), as_h2(x[3]), t[0][2], t[1][2], t[2][2], t[0][3], t[1][3], t[2][3], 0x07030501u);
         const uint32_t even = __builtin_amdgcn_perm(y23, y01, 0x05040100u), odd = __builtin_amdgcn_perm(y23, y01, 0x07060302u);
         word[d][0] = (odd | (even >> 4)) >> (sub & 1);
       } else {
