@@ -92,8 +92,8 @@ __device__ inline void fwht128_wave_multi(float (&x0)[NV], float (&x1)[NV], int 
 // only in a bulk append of few sequences, whose groups are then shared out in chunks).  Each owner reads the sequence's
 // counters once and counts itself in at the sequence's first split_done entry when it is done -- with a vote in the
 // upper half of the counter if it found a fault; the counters change only in the arrival that completes the count
-// (kParts n_chunks H_kv), i.e. after every reader has read them, and only if nobody voted against.  The scan launch
-// that precedes a bulk append raises bit 30 of the same entry for a sequence with a non-finite new row: it reads as a
+// (kParts n_chunks H_kv), i.e. after every reader has read them, and only if nobody voted against.  The launch that
+// quantizes an append of several rows raises bit 30 of the same entry for a sequence with a non-finite new row: it reads as a
 // vote.  The completing arrival leaves the entry at zero, as the decode kernel, which uses the same entries in the
 // same way, expects.
 constexpr int kFaultVote = 1 << 16;
