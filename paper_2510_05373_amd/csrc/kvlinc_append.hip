@@ -427,7 +427,7 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
 // by ordinary binary32 additions, and the codes are centred (the other part is the same for all channels of a row and is
 // added once per call).
 //
-// Nothing but phi and W_k passes through LDS: a lane reads the raw keys of its token and the tile words of its key codes
+// Nothing but phi, W_k and the key scales passes through LDS: a lane reads the raw keys of its token and the tile words of its key codes
 // straight into the layout of the A operand and forms the key error there; the value tile is the B operand of the S
 // update as it lies in memory (the nibble hi|0|lo|1 is the FP4 number code - 1.5, one conversion gives two binary16
 // numbers).  Tokens are dealt to the waves and to the rows of their tiles so that the four tokens a lane holds of a result

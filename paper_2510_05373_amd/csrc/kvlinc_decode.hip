@@ -61,7 +61,7 @@ __device__ __forceinline__ float2 ld_coherent2(const float* p) {  // two neighbo
   const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return __builtin_bit_cast(float2, v);
 }
-// Four neighbours, 16-byte aligned, at `bytes` beyond a wave-uniform base (the same load: sc0 sc1).
+// Cache policy of a buffer load that is coherent in the same way: sc0 and sc1.
 constexpr int kCoherentLoad = 1 | 16;
 
 __device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
