@@ -571,8 +571,8 @@ __device__ __forceinline__ void store_key_affine(KeyAffine& a, uint32_t scales, 
                                                              __builtin_fmaf((float)s[1], Rec<BITS>::kCentre, (float)z[1]));
 }
 
-// logits of the wave's 16 tokens: d[ft][r] = token row 4 kq + r, feature 16 ft + l16.  (Rows of tokens that do not exist come
-// out finite and are dropped by the softmax.)
+// logits of the wave's 16 tokens: d[ft][r] = token row 4 kq + r, feature 16 ft + l16.  (Rows of tokens that do not exist hold
+// anything, NaN included: see state_softmax.)
 template <int BITS>
 __device__ __forceinline__ void state_logits(const KeyError<BITS>& e, const KeyAffine& ka, const StateLds& L, uint32_t pick, int lane, float4_t (&d)[8]) {
   const int l16 = lane & 15, kq = lane >> 4;
@@ -661,6 +661,17 @@ __device__ __forceinline__ void state_softmax(float4_t (&d)[8], const ValueScale
   const int l16 = lane & 15, kq = lane >> 4, jj = 4 * (wave >> 1) + kq;
   const uint32_t szw[4] = {sz.mine.x, sz.mine.y, sz.mine.z, sz.mine.w};
   float m[4], sum[4], inv[4], wz[4], ws[4];
+  // A token that does not exist was given the key of the last one against the padding's code 0: an error of any size, beyond
+  // binary16 where a channel spans more than 65504, and a NaN logit then.  Its weight of 0 would not remove that: its logits
+  // are made zero (only in the newest group of a static build).
+  if (valid < kGroup) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool live = 16 * (4 * (wave & 1) + r) + jj < valid;
+#pragma unroll
+      for (int ft = 0; ft < 8; ++ft) d[ft][r] = live ? d[ft][r] : 0.0f;
+    }
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r)
     m[r] = fmaxf(fmaxf(fmaxf(d[0][r], d[1][r]), fmaxf(d[2][r], d[3][r])), fmaxf(fmaxf(d[4][r], d[5][r]), fmaxf(d[6][r], d[7][r])));
@@ -933,7 +944,7 @@ __device__ void states_item(const kvlinc_cache& c, StatesLds& L, int item, const
     uint32_t k_s = 0, k_z = 0;  // scales and zero-points of two channels (threads 0 .. 63)
     const uint32_t pick = code_bits_mask();
     const int my_t = state_row_token(wave, l16);
-    // (Every lane requests, a token beyond the last one that of the last: a load that only some lanes or waves issue makes the
+    // (Every lane requests, a token beyond the last one the key of the last: a load that only some lanes or waves issue makes the
     // compiler wait for all loads at the next use of any, a trip to memory per group.)
     auto request_keys = [&](int j) {
       const int u = min(j * kGroup + my_t, plan.n_flush - 1);

@@ -99,6 +99,27 @@ def test_static_window_sizes(kv, R, keep, n):
     assert int(cache.status.item()) == 0 and not cache.split_done.any()
 
 
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("n_flush", [2, 37, 128 + 100, 256 + 127])
+def test_padding_tokens_leave_the_states_alone_whatever_the_keys_span(kv, n_flush, bits):
+    """A partial last group with channels that span more than binary16's largest number, their maximum in the last token that
+    is quantized: the distance of its key from the padding's code 0 overflows, and nothing of that may reach S, P.  (The
+    adapters of these channels are small, so that the errors of the real tokens, half a step at most, leave ordinary logits.)"""
+    import torch
+    n, R, wide = n_flush + 32, 32, {5: (-40000.0, 30000.0), 77: (-65504.0, 65504.0)}
+    K, V = tl.gen_kv(64, 2, 2, [n, n])
+    Wk = synth.adapters_k(64, 2).copy()
+    for c, (low, high) in wide.items():
+        K[:, :, (n_flush - 1) // 128 * 128, c] = low
+        K[:, :, n_flush - 1, c] = high
+        Wk[:, :, c] = (Wk[:, :, c].astype(np.float32) * 2.0 ** -10).astype(np.float16)
+    cache = kv.KVLincCache(2, 2, 2, 512, R=R, Wq=tl.to_dev(synth.adapters_q(64, 2)), Wk=tl.to_dev(Wk), bits=bits)
+    cache.append(tl.to_dev(K), tl.to_dev(V), keep_residual=32)
+    torch.cuda.synchronize()
+    assert int(cache.status.item()) == 0
+    tl.check_cache_against_oracle(cache, K, V, [n, n], [(b, g) for b in range(2) for g in range(2)], Wk=Wk, keep=32)
+
+
 @pytest.mark.parametrize("sliding", [False, True])
 def test_no_row_of_a_refused_append_reaches_the_window(kv, sliding):
     """A fault in the last row of one head: nothing live changes, and no non-finite value is stored anywhere."""
