@@ -474,8 +474,7 @@ struct ValueScales {
 __device__ __forceinline__ int state_row_token(int wave, int rho) { return 16 * (4 * (wave & 1) + (rho & 3)) + 4 * (wave >> 1) + (rho >> 2); }
 
 template <int BITS>
-__device__ __forceinline__ void load_key_codes(KeyError<BITS>& e, const uint32_t* rec, int wave, int lane) {
-  const int t = state_row_token(wave, lane & 15), kq = lane >> 4;
+__device__ __forceinline__ void load_key_codes(KeyError<BITS>& e, const uint32_t* rec, int t, int kq) {
 #pragma unroll
   for (int pl = 0; pl < BITS / 2; ++pl)
 #pragma unroll
@@ -571,8 +570,8 @@ __device__ __forceinline__ void store_key_affine(KeyAffine& a, uint32_t scales, 
                                                              __builtin_fmaf((float)s[1], Rec<BITS>::kCentre, (float)z[1]));
 }
 
-// logits of the wave's 16 tokens: d[ft][r] = token row 4 kq + r, feature 16 ft + l16.  (Rows of tokens that do not exist hold
-// anything, NaN included: see state_softmax.)
+// logits of the wave's 16 tokens: d[ft][r] = token row 4 kq + r, feature 16 ft + l16.  (All rows are finite: a token that does
+// not exist is a copy of the last one, see states_item.)
 template <int BITS>
 __device__ __forceinline__ void state_logits(const KeyError<BITS>& e, const KeyAffine& ka, const StateLds& L, uint32_t pick, int lane, float4_t (&d)[8]) {
   const int l16 = lane & 15, kq = lane >> 4;
@@ -661,17 +660,6 @@ __device__ __forceinline__ void state_softmax(float4_t (&d)[8], const ValueScale
   const int l16 = lane & 15, kq = lane >> 4, jj = 4 * (wave >> 1) + kq;
   const uint32_t szw[4] = {sz.mine.x, sz.mine.y, sz.mine.z, sz.mine.w};
   float m[4], sum[4], inv[4], wz[4], ws[4];
-  // A token that does not exist was given the key of the last one against the padding's code 0: an error of any size, beyond
-  // binary16 where a channel spans more than 65504, and a NaN logit then.  Its weight of 0 would not remove that: its logits
-  // are made zero (only in the newest group of a static build).
-  if (valid < kGroup) {
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const bool live = 16 * (4 * (wave & 1) + r) + jj < valid;
-#pragma unroll
-      for (int ft = 0; ft < 8; ++ft) d[ft][r] = live ? d[ft][r] : 0.0f;
-    }
-  }
 #pragma unroll
   for (int r = 0; r < 4; ++r)
     m[r] = fmaxf(fmaxf(fmaxf(d[0][r], d[1][r]), fmaxf(d[2][r], d[3][r])), fmaxf(fmaxf(d[4][r], d[5][r]), fmaxf(d[6][r], d[7][r])));
@@ -944,14 +932,16 @@ __device__ void states_item(const kvlinc_cache& c, StatesLds& L, int item, const
     uint32_t k_s = 0, k_z = 0;  // scales and zero-points of two channels (threads 0 .. 63)
     const uint32_t pick = code_bits_mask();
     const int my_t = state_row_token(wave, l16);
-    // (Every lane requests, a token beyond the last one the key of the last: a load that only some lanes or waves issue makes the
-    // compiler wait for all loads at the next use of any, a trip to memory per group.)
+    // (Every lane requests: a load that only some lanes or waves issue makes the compiler wait for all loads at the next use of
+    // any, a trip to memory per group.  A lane whose token does not exist takes the last one's key and codes, an ordinary
+    // key error; its weight is 0.  The padding's own codes would not do: their distance from a key can leave binary16, and
+    // a weight of 0 does not remove the NaN that comes of it.)
     auto request_keys = [&](int j) {
-      const int u = min(j * kGroup + my_t, plan.n_flush - 1);
+      const int u = min(j * kGroup + my_t, plan.n_flush - 1), t = u - j * kGroup;
       const half_t* row = u < s.nr ? k_res + (long long)u * kHeadDim : k_src + (long long)(u - s.nr) * kHeadDim;
       const uint32_t* rec = rec0 + (long long)j * R::kWords;
       load_key_rows<BITS>(ke, row, kq);
-      load_key_codes<BITS>(ke, rec, wave, lane);
+      load_key_codes<BITS>(ke, rec, t, kq);
       k_s = rec[R::kKeyScale + lane];
       k_z = rec[R::kKeyZero + lane];
     };
@@ -1184,7 +1174,7 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
   const uint32_t pick = code_bits_mask();
   if (states_live) {
     ValueScales vs;
-    load_key_codes<BITS>(ke, L.img, wave, lane);
+    load_key_codes<BITS>(ke, L.img, state_row_token(wave, l16), kq);
     load_value_scales<BITS>(vs, L.img, wave, lane);
     load_value_codes<BITS, true>(vc, L.img, wave, lane);
     const float F = scale_factor(vs, inv_F);
