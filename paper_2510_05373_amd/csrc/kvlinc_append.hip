@@ -664,12 +664,13 @@ __device__ __forceinline__ void state_softmax(float4_t (&d)[8], const ValueScale
   for (int r = 0; r < 4; ++r)
     m[r] = fmaxf(fmaxf(fmaxf(d[0][r], d[1][r]), fmaxf(d[2][r], d[3][r])), fmaxf(fmaxf(d[4][r], d[5][r]), fmaxf(d[6][r], d[7][r])));
   row16_max(m);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) m[r] *= -kLog2e;  // (its rounding is the same for all features of a token and cancels)
+  // (The difference first: it is never positive, whatever its rounding.  fma(d, log2(e), -m log2(e)) saves an instruction per
+  // element, 1 to 1.8 % of a prompt, but leaves the rounding of m log2(e) in the exponent, which passes what a power of two can
+  // hold where adapters in the hundreds make logits of 1e9.)
 #pragma unroll
   for (int ft = 0; ft < 8; ++ft)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) d[ft][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(d[ft][r], kLog2e, m[r]));
+    for (int r = 0; r < 4; ++r) d[ft][r] = __builtin_amdgcn_exp2f((d[ft][r] - m[r]) * kLog2e);
 #pragma unroll
   for (int r = 0; r < 4; ++r) sum[r] = ((d[0][r] + d[1][r]) + (d[2][r] + d[3][r])) + ((d[4][r] + d[5][r]) + (d[6][r] + d[7][r]));
 #pragma unroll

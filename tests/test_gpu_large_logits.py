@@ -1,6 +1,6 @@
 """GPU parity where logits are so large (1e6 to 1e13) that one unit in their last place is more than a softmax can tell apart:
 any finite keys and queries have to give finite outputs, and where the answer does not hang on such a unit -- all tokens alike,
-or one far ahead -- the right ones."""
+or one far ahead -- the right ones; likewise for the feature maps under large adapters."""
 import numpy as np
 import pytest
 
@@ -85,3 +85,21 @@ def test_large_centres_that_cancel(kv, gq, bits, sliding, step):
         for c in range(64):
             K[0, 0, 128 * group + c, c] = levels * step
     _decode_and_check(kv, K, V, np.full((1, gq, 128), -32768.0, dtype=np.float16), bits, sliding)
+
+
+# Key errors of up to half a step (1e4) times adapters of up to 6e4: logits of 1e9 to 1e10, of which the largest is ahead of the
+# next by far more than one unit in its last place (256 to 1024), so that phi is 1 for one feature of each half.
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("one_by_one", [False, True])
+def test_feature_maps_under_large_adapters(kv, bits, one_by_one):
+    n = 300
+    r = np.random.default_rng(86)
+    K = r.uniform(-60000.0, 60000.0, (1, 1, n, 128)).astype(np.float16)
+    _, V = tl.gen_kv(86, 1, 1, [n])
+    Wk = r.uniform(-60000.0, 60000.0, (1, 2, 128, 128)).astype(np.float16)
+    cache = kv.KVLincCache(1, 4, 1, 512, Wq=tl.to_dev(synth.adapters_q(86, 4)), Wk=tl.to_dev(Wk), bits=bits)
+    for t in range(n) if one_by_one else (slice(0, n),):
+        rows = slice(t, t + 1) if one_by_one else t
+        cache.append(tl.to_dev(K[:, :, rows]), tl.to_dev(V[:, :, rows]))
+    assert int(cache.status.item()) == 0
+    tl.check_cache_against_oracle(cache, K, V, [n], [(0, 0)], Wk=Wk)
