@@ -359,14 +359,14 @@ template <bool SLIDING, int BITS>
 __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
                                                                             const half_t* __restrict__ v_new,
                                                                             const int32_t* __restrict__ n_new, int T, int keep,
-                                                                            int per_pair) {
+                                                                            int per_pair, int first_pair) {
   using R = Rec<BITS>;
   __shared__ __align__(16) half_t st[kGroup][kRowH];  // rotated rows of the window
   __shared__ __align__(16) uint32_t img[R::kWords];
   __shared__ QuantLds<kQuantWaves> L;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int p = blockIdx.x / per_pair, j = blockIdx.x % per_pair;
+  const int p = first_pair + blockIdx.x / per_pair, j = blockIdx.x % per_pair;
   const int b = p / c.H_kv;
   const long long bh = p;
   const Counters s = read_counters(c, b, n_new, T, keep);
@@ -1335,15 +1335,26 @@ int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_
     if (want > 64) want = 64;
     if (groups_most >= 64 && want > 1) n_chunks = (int)want;
   }
-  void (*quantize)(kvlinc_cache, const half_t*, const half_t*, const int32_t*, int, int, int) =
+  void (*quantize)(kvlinc_cache, const half_t*, const half_t*, const int32_t*, int, int, int, int) =
       c.bits == 4 ? (sliding ? append_quantize_kernel<true, 4> : append_quantize_kernel<false, 4>)
                   : (sliding ? append_quantize_kernel<true, 2> : append_quantize_kernel<false, 2>);
   void (*states)(kvlinc_cache, const half_t*, const half_t*, const int32_t*, int, int, int) =
       c.bits == 4 ? (sliding ? append_states_kernel<true, 4> : append_states_kernel<false, 4>)
                   : (sliding ? append_states_kernel<true, 2> : append_states_kernel<false, 2>);
   if (launch_with_lds(states, sizeof(StatesLds)) != KVLINC_OK) return KVLINC_EHIP;
-  const int per_pair = (int)groups_most + 1;  // groups of a pair at most, and the rows that stay in the window
-  hipLaunchKernelGGL(quantize, dim3((unsigned)(pairs * per_pair)), dim3(64 * kQuantWaves), 0, stream, c, kk, vv, n_new, T, keep, per_pair);
+  int per_pair = (int)groups_most + 1;  // groups of a pair at most, and the rows that stay in the window
+  // A launch has to stay below 2^32 threads (8.4 million pairs, if none takes more than one group).  The states may only be
+  // launched behind records that are there: a failed launch ends the call.
+  constexpr int kQuantThreads = 64 * kQuantWaves;
+  const int pairs_most = (int)(((1ll << 32) - 1) / kQuantThreads / per_pair);
+  kvlinc_cache cache = c;
+  for (long long first = 0; first < pairs; first += pairs_most) {
+    int first_pair = (int)first;
+    const long long n_pairs = pairs - first < pairs_most ? pairs - first : pairs_most;
+    void* args[] = {&cache, &kk, &vv, &n_new, &T, &keep, &per_pair, &first_pair};
+    if (hipLaunchKernel(reinterpret_cast<const void*>(quantize), dim3((unsigned)(n_pairs * per_pair)), dim3(kQuantThreads), args, 0, stream) != hipSuccess)
+      return KVLINC_EHIP;
+  }
   const long long n_items = (long long)kParts * n_chunks * 8 * ((pairs + 7) / 8);
   const int grid = (int)(n_items < 256 ? n_items : 256);
   hipLaunchKernelGGL(states, dim3(grid), dim3(kThreads), sizeof(StatesLds), stream, c, kk, vv, n_new, T, keep, n_chunks);

@@ -141,3 +141,27 @@ def test_no_row_of_a_refused_append_reaches_the_window(kv, sliding):
             assert all(torch.equal(a, b) for a, b in zip(after, before))
             assert torch.isfinite(cache.k_res.float()).all() and torch.isfinite(cache.v_res.float()).all()
             assert not cache.split_done.any()
+
+
+def test_more_pairs_than_one_launch_holds(kv):
+    """2^23 + 5 (sequence, kv head) pairs: an append of several rows, or one that keeps a residual, takes two workgroups of 256
+    threads for each, and a launch holds fewer than 2^32 threads.  (100 GB of cache.)"""
+    import torch
+    B = 2 ** 23 + 5
+    if torch.cuda.mem_get_info()[0] < 130e9:
+        pytest.skip("needs 130 GB of free device memory")
+    cache = kv.KVLincCache(B, 1, 1, 128, R=4)
+    k = torch.randn(B, 1, 1, 128, device="cuda", dtype=torch.float16)
+    v = torch.randn(B, 1, 1, 128, device="cuda", dtype=torch.float16)
+    k[-2, 0, 0, 9] = float("inf")
+    cache.append(k, v, keep_residual=4)
+    assert int(cache.status.item()) == kv.KVLINC_ST_NONFINITE and not cache.split_done.any()
+    want = torch.ones(B, dtype=torch.int32, device="cuda")
+    want[-2] = 0
+    assert torch.equal(cache.n_res, want) and not cache.n_quant.any()
+    k[-2] = 0
+    assert torch.equal(cache.k_res[:, 0, 0], k[:, 0, 0])
+    for b in (0, 2 ** 22, 2 ** 23 - 1, 2 ** 23, B - 1):
+        tl.check_pair_against_oracle(cache, b, 0, k[b, 0].cpu().numpy(), v[b, 0].cpu().numpy(), 0, 1)
+    del cache, k, v
+    torch.cuda.empty_cache()
