@@ -69,7 +69,8 @@ lib = _load()
 
 
 # A generation step of a small batch takes about as long on the GPU as these calls take on the host: addresses go through the
-# declared argument types as plain integers, and the current stream is asked for as a raw handle.
+# declared argument types as plain integers, and the current stream is asked for as a raw handle (through torch's own shortcut,
+# which is not part of its public interface: without it the public call serves).
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -77,7 +78,10 @@ def _ptr(t):
 def _stream(stream):
     if stream is None:
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
     return int(stream)

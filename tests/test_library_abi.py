@@ -186,3 +186,14 @@ def test_split_policy_of_the_workloads():
         c0 = fake_struct(B=cfg["B"], H_q=cfg["H_q"], H_kv=cfg["H_kv"], max_groups=(n + 512) // 128, S=0, S16=0, P=0,
                          Wq=0, Wk=0)
         assert kb.kvlinc_decode_workspace_bytes(c0, n) % (cfg["B"] * cfg["H_q"] * 132 * 4) == 0
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_the_private_shortcut(monkeypatch, missing):
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1230))
+    assert kb._stream(None) == 0x1230
+    assert kb._stream(types.SimpleNamespace(cuda_stream=0x4560)) == 0x4560 and kb._stream(0x7890) == 0x7890
