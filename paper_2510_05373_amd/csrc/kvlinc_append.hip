@@ -2,8 +2,8 @@
 // tile packing, and the update of the linear-correction states (Sec. 3.1, Obs. 3; Sec. 2, Eq. 1; Sec. 3.2, Eq. 5-6;
 // Sec. 3.3: the cache is quantized only after attention has used the new token).
 //
-// A one-token append is one launch (append_token_kernel): most of them only store a row, a sequence whose window is full
-// has its group quantized and its states updated by two workgroups per kv head.  An append of several rows is two
+// An append of one token, or of a few, is one launch (append_token_kernel): most of them only store rows, a sequence whose
+// window is full has its group quantized and its states updated by two workgroups per kv head.  An append of more rows is two
 // launches: append_quantize_kernel, one workgroup per group of 128 tokens, writes the records (and looks at every new row
 // and stores those that stay in an empty window); append_states_kernel then walks the groups of a (sequence, kv head), adds
 // their contributions to the states and commits the counters.
@@ -143,22 +143,46 @@ __device__ inline bool store_window_row(half_t* __restrict__ k_win, half_t* __re
                           *reinterpret_cast<const uint32_t*>(vs + 2 * lane), lane);
 }
 
-// One-token append: is the new row of any kv head of sequence b non-finite (key) or beyond fp16 once rotated (value)?
-// The caller's waves share the heads: wave `first` of `stride` takes the heads first, first + stride, ..., eight per
-// batch; the verdicts of the waves still have to be combined.  g: a head whose row may be read in place of a missing one.
+// An append of few rows: at most kFewRows a call, and at most kFewRowsOfAllHeads of them over the kv heads of a sequence (each
+// workgroup that flushes looks at all of these; so does each wave that stores, where the values slide).  Measured, us a call in
+// one launch and in the two that more rows take (2 bits, correction; every sequence flushes once in 128 / T calls):
+//   1 kv head, 64 sequences       2 rows  5.0   9.1    8 rows  7.5  10.3
+//   8 kv heads, 144 sequences     2 rows  9.5  18.0    8 rows 23.8  26.5
+//   the same, sliding values      2 rows 13.0  50.2    8 rows 30.7  55.8
+//   32 kv heads, 32 sequences     6 rows 18.9  21.9    8 rows 28.9  24.1
+constexpr int kFewRows = 8, kFewRowsOfAllHeads = 192;
+
+// Is a new row of any kv head of sequence b non-finite (key) or beyond fp16 once rotated (value)?  (n: new rows of the
+// sequence, ROWS: what T may be at most; row i of the sequence is row i % n of head i / n.)  The caller's waves share the rows:
+// wave `first` of `stride` takes the rows first, first + stride, ..., eight per batch; the verdicts of the waves still have to
+// be combined.  g: a head whose row may be read in place of a missing one.
 template <int N>
 struct NewRows {
   uint32_t k[N], v[N];
 };
-template <int N>
+template <int ROWS, int N>
 __device__ inline void request_new_rows(NewRows<N>& r, const kvlinc_cache& c, int b, int g, const half_t* __restrict__ k_new,
-                                        const half_t* __restrict__ v_new, int lane, int g0, int stride) {
+                                        const half_t* __restrict__ v_new, int T, int n, int lane, int i0, int stride) {
 #pragma unroll
   for (int u = 0; u < N; ++u) {
-    const int g2 = g0 + stride * u;
-    const long long row = ((long long)b * c.H_kv + (g2 < c.H_kv ? g2 : g)) * kHeadDim + 2 * lane;
-    r.k[u] = *reinterpret_cast<const uint32_t*>(k_new + row);
-    r.v[u] = *reinterpret_cast<const uint32_t*>(v_new + row);
+    const int i = i0 + stride * u;
+    const int g2 = ROWS == 1 ? i : i / n;
+    const bool exists = g2 < c.H_kv;
+    long long row = (long long)b * c.H_kv + (exists ? g2 : g);
+    if (ROWS > 1) row = row * T + (exists ? i - g2 * n : 0);
+    r.k[u] = *reinterpret_cast<const uint32_t*>(k_new + row * kHeadDim + 2 * lane);
+    r.v[u] = *reinterpret_cast<const uint32_t*>(v_new + row * kHeadDim + 2 * lane);
+  }
+}
+// All T rows of one (sequence, kv head).
+template <int ROWS>
+__device__ inline void request_rows_of_pair(NewRows<ROWS>& r, int p, const half_t* __restrict__ k_new, const half_t* __restrict__ v_new, int T, int lane) {
+#pragma unroll
+  for (int u = 0; u < ROWS; ++u) {
+    if (u >= T) break;
+    const long long row = (long long)p * T + u;
+    r.k[u] = *reinterpret_cast<const uint32_t*>(k_new + row * kHeadDim + 2 * lane);
+    r.v[u] = *reinterpret_cast<const uint32_t*>(v_new + row * kHeadDim + 2 * lane);
   }
 }
 template <int N>
@@ -195,15 +219,47 @@ __device__ inline bool new_rows_bad(const NewRows<N>& r, int lane) {
   }
   return refuse;
 }
+template <int ROWS>
 __device__ inline bool new_rows_of_all_heads_bad(const kvlinc_cache& c, int b, int g, const half_t* __restrict__ k_new,
-                                                 const half_t* __restrict__ v_new, int lane, int first, int stride) {
+                                                 const half_t* __restrict__ v_new, int T, int n, int lane, int first, int stride) {
   bool refuse = false;
-  for (int g0 = first; g0 < c.H_kv; g0 += stride * 8) {
+  for (int i0 = first; i0 < c.H_kv * n; i0 += stride * 8) {
     NewRows<8> r;
-    request_new_rows(r, c, b, g, k_new, v_new, lane, g0, stride);
+    request_new_rows<ROWS>(r, c, b, g, k_new, v_new, T, n, lane, i0, stride);
     refuse |= new_rows_bad(r, lane);
   }
   return refuse;
+}
+
+// The same by one wave for the first n of the T rows of every kv head of sequence b, 32 rows on their way at a time (8 of them and a
+// sum for each row took 20 us a launch for 32 kv heads of 2 rows, where this takes 12.5).  A row of magnitudes up to 5788 = 0x6DA7 cannot leave
+// fp16 when it is rotated (128 * 5788 < 65504 sqrt(128)); where one is larger, the wave takes the way above.
+__device__ inline bool few_rows_of_all_heads_bad(const kvlinc_cache& c, int b, const half_t* __restrict__ k_new,
+                                                 const half_t* __restrict__ v_new, int T, int n, int lane) {
+  typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+  constexpr int kBatch = 32;
+  const long long first = (long long)b * c.H_kv * T;
+  ushort2_t k_max = {0, 0}, v_max = {0, 0};
+  int at = 0;  // row within its head
+  for (int i0 = 0; i0 < c.H_kv * T; i0 += kBatch) {
+    uint32_t k[kBatch], v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      // (rows from n on, and beyond the last head, are not the caller's: the sequence's first row instead)
+      const long long row = first + (at < n && i0 + u < c.H_kv * T ? i0 + u : 0);
+      if (++at == T) at = 0;
+      k[u] = *reinterpret_cast<const uint32_t*>(k_new + row * kHeadDim + 2 * lane);
+      v[u] = *reinterpret_cast<const uint32_t*>(v_new + row * kHeadDim + 2 * lane);
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      k_max = __builtin_elementwise_max(k_max, __builtin_bit_cast(ushort2_t, k[u] & 0x7fff7fffu));
+      v_max = __builtin_elementwise_max(v_max, __builtin_bit_cast(ushort2_t, v[u] & 0x7fff7fffu));
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64(k_max[0] >= 0x7c00 || k_max[1] >= 0x7c00) != 0) return true;
+  if (__builtin_amdgcn_ballot_w64(v_max[0] > 0x6da7 || v_max[1] > 0x6da7) == 0) return false;
+  return new_rows_of_all_heads_bad<kFewRows>(c, b, 0, k_new, v_new, T, n, lane, 0, 1);
 }
 
 struct Counters {
@@ -220,28 +276,30 @@ __device__ inline Counters read_counters(const kvlinc_cache& c, int b, const int
   return r;
 }
 
-// An append of one token that quantizes nothing: one wave stores the new row of one (sequence, kv head) behind the window's
-// tokens.  The slot is dead storage until the counters advance, and they do not advance if any head of the sequence
+// An append of few rows that quantizes nothing: one wave stores the new rows of one (sequence, kv head) behind the window's
+// tokens.  The slots are dead storage until the counters advance, and they do not advance if any head of the sequence
 // votes against.
-// known: the sequence's counters as read before, and the lane's elements of the pair's (only) new row, read ahead into
-// row_k, row_v.
-template <bool SLIDING>
+// known: the sequence's counters as read before, and the lane's elements of the pair's new rows, read ahead into `rows`.
+template <bool SLIDING, int ROWS>
 __device__ inline void light_item(const kvlinc_cache& c, int p, const half_t* __restrict__ k_new,
-                                  const half_t* __restrict__ v_new, const int32_t* __restrict__ n_new, int lane,
-                                  const Counters* known = nullptr, uint32_t row_k = 0, uint32_t row_v = 0) {
+                                  const half_t* __restrict__ v_new, const int32_t* __restrict__ n_new, int T, int lane,
+                                  const Counters* known, NewRows<ROWS>& rows) {
   const int b = p / c.H_kv;
-  const bool have_row = known != nullptr;
-  const Counters s = have_row ? *known : read_counters(c, b, n_new, 1, 0);
+  if (known == nullptr) request_rows_of_pair(rows, p, k_new, v_new, T, lane);
+  const Counters s = known != nullptr ? *known : read_counters(c, b, n_new, T, 0);
   half_t* k_win = reinterpret_cast<half_t*>(c.k_res) + (long long)p * c.R * kHeadDim;
   half_t* v_win = reinterpret_cast<half_t*>(c.v_res) + (long long)p * c.R * kHeadDim;
   bool row_bad = false;
   // With the sliding value window the value slots behind the key window are live (the values of the newest group's
   // last tokens): nothing may be written there before the new rows of ALL kv heads of the sequence have been looked at
-  // (one kv head: the row is looked at before it is stored anyway).
-  if (SLIDING && c.H_kv > 1) row_bad = __builtin_amdgcn_ballot_w64(new_rows_of_all_heads_bad(c, b, p % c.H_kv, k_new, v_new, lane, 0, 1)) != 0;
-  if (s.n > 0 && !row_bad) {
-    if (have_row) row_bad = store_window_row(k_win, v_win, s.nr, row_k, row_v, lane);
-    else row_bad = store_window_row(k_win, v_win, s.nr, k_new + (long long)p * kHeadDim, v_new + (long long)p * kHeadDim, lane);
+  // (a single row: it is looked at before it is stored anyway).
+  if (SLIDING && c.H_kv * s.n > 1)
+    row_bad = __builtin_amdgcn_ballot_w64(ROWS == 1 ? new_rows_of_all_heads_bad<1>(c, b, p % c.H_kv, k_new, v_new, 1, 1, lane, 0, 1)
+                                                    : few_rows_of_all_heads_bad(c, b, k_new, v_new, T, s.n, lane)) != 0;
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    if (r >= s.n || row_bad) break;
+    row_bad = store_window_row(k_win, v_win, s.nr + r, rows.k[r], rows.v[r], lane);
   }
   if (lane == 0) {
     if (row_bad) atomicOr(c.status, KVLINC_ST_NONFINITE);
@@ -1060,7 +1118,7 @@ __global__ __launch_bounds__(kThreads) void append_states_kernel(kvlinc_cache c,
   }
 }
 
-// ---- an append of one token ----------------------------------------------------------------------------------------
+// ---- an append of one token, or of few ------------------------------------------------------------------------------
 template <int BITS>
 struct TokenLds {
   StateLds st;
@@ -1068,7 +1126,7 @@ struct TokenLds {
   __align__(16) uint32_t img[Rec<BITS>::kWords];
   __align__(16) KeyAffine ka;
   float row[kWaves][kHeadDim];  // new rows read ahead
-  int light[kListCap], heavy[kListCap], heavy_nq[kListCap], heavy_nr[kListCap];
+  int light[kListCap], heavy[kListCap], heavy_nq[kListCap], heavy_nr[kListCap];  // (heavy_nr: n_res + 256 n)
   int n_light, n_heavy, last_flag;
   int refuse[kWaves];
   // the item that thread w looked at is a light one whose new row wave w has read ahead; the sequence's counters as that
@@ -1076,32 +1134,37 @@ struct TokenLds {
   int ahead[kWaves], ahead_nq[kWaves], ahead_nr[kWaves], ahead_n[kWaves];
 };
 
-// The window of one (sequence, kv head) is full: its 128 tokens become a group.  Two owners, one per half of phi; both
-// quantize the group (the record feeds both halves of the state update), each writes half of the record.
+// The window of one (sequence, kv head) is full, or the n new rows fill it: its 128 tokens become a group, the last 128 - nr of
+// them from the new rows.  Two owners, one per half of phi; both quantize the group (the record feeds both halves of the state
+// update), each writes half of the record.
 // Bound: latency, a chain of loads and phases on a few compute units.  So everything is requested at once, in the order in
 // which it is wanted; the verdict on the new rows, the staged values and the keys' minima share the first barrier; and the owner
 // counts itself in as soon as it has read the window, so that the answer is there when the states are done.  Measured (144
 // sequences of 1280 tokens, where nearly every launch has one that flushes): 16.3 us from the start of the launch, 20.5 us when
 // the rows, the window and the states were requested one after the other and the count came last.
-template <int BITS>
-__device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, int nq, int nr, const half_t* __restrict__ k_new,
-                           const half_t* __restrict__ v_new, int tid) {
+template <bool SLIDING, int BITS, int ROWS>
+__device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, int nq, int nr, int n, const half_t* __restrict__ k_new,
+                           const half_t* __restrict__ v_new, int T, int tid) {
   using R = Rec<BITS>;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kq = lane >> 4;
   const int fp = item % kParts, p = item / kParts;
   const int b = p / c.H_kv, g = p % c.H_kv;
   const long long bh = p;
-  const AppendPlan plan = plan_append(nq, nr, 1, c.R, 0, c.max_groups);
+  const AppendPlan plan = plan_append(nq, nr, n, c.R, 0, c.max_groups);
   const half_t* k_res = reinterpret_cast<const half_t*>(c.k_res) + bh * c.R * kHeadDim;
+  auto key_row = [&](int t) {  // (one row: it only arrives at a full window)
+    return ROWS == 1 || t < nr ? k_res + (long long)t * kHeadDim : k_new + (bh * T + t - nr) * kHeadDim;
+  };
   const bool states_live = c.S16 != nullptr;
   // (Nothing is stored to global memory before the verdict on the new rows.)
-  NewRows<1> rows;  // of the first eight heads, one per wave
-  request_new_rows(rows, c, b, g, k_new, v_new, lane, wave, kWaves);
+  constexpr int kAhead = ROWS == 1 ? 1 : 4;
+  NewRows<kAhead> rows;  // the first 8 (32) of the sequence's rows
+  request_new_rows<ROWS>(rows, c, b, g, k_new, v_new, T, n, lane, wave, kWaves);
   KeyTile<kWaves> keys;
 #pragma unroll
   for (int i = 0; i < 32 / kWaves; ++i)
-    keys.raw[i] = *reinterpret_cast<const uint4*>(k_res + (long long)key_token<kWaves>(i, wave, lane) * kHeadDim + 8 * l16);
+    keys.raw[i] = *reinterpret_cast<const uint4*>(key_row(key_token<kWaves>(i, wave, lane)) + 8 * l16);
   StateAcc acc;
   float P_old = 0.0f;
   KeyError<BITS> ke;
@@ -1110,14 +1173,14 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
     WindowValues<kWaves> win;
     request_window_values<kWaves>(win, reinterpret_cast<const half_t*>(c.v_res) + bh * c.R * kHeadDim, kGroup, tid);
     if (states_live) {
-      load_key_rows<BITS>(ke, k_res + (long long)state_row_token(wave, l16) * kHeadDim, kq);
+      load_key_rows<BITS>(ke, key_row(state_row_token(wave, l16)), kq);
       request_wk(wk, c, g, fp, tid);
       load_states<true>(c, bh, fp, false, acc, P_old, wave, lane);
     }
     // A flush changes live state (S, P, the window's first slot) in every kv head: the new row of every kv head of this
     // sequence is looked at first; the verdict is the same in all workgroups of the sequence.
     bool bad = new_rows_bad(rows, lane);
-    if (c.H_kv > kWaves) bad |= new_rows_of_all_heads_bad(c, b, g, k_new, v_new, lane, wave + kWaves, kWaves);
+    if (c.H_kv * n > kAhead * kWaves) bad |= new_rows_of_all_heads_bad<ROWS>(c, b, g, k_new, v_new, T, n, lane, wave + kAhead * kWaves, kWaves);
     const bool refuse = __builtin_amdgcn_ballot_w64(bad) != 0;
     if (lane == 0) L.refuse[wave] = refuse ? 1 : 0;
     key_minmax<kWaves>(keys, kGroup, L.q, wave, lane);
@@ -1132,7 +1195,7 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
       if (tid == 0) {
         if (fp == 0) atomicOr(c.status, KVLINC_ST_NONFINITE);
         bool clean;
-        if (arrive(c, b, 1, true, &clean)) finish(c, b, nq, 1, plan, false);
+        if (arrive(c, b, 1, true, &clean)) finish(c, b, nq, n, plan, false);
       }
       return;
     }
@@ -1147,10 +1210,21 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
   }
   {
     const RowLane rl = row_lane(lane);
+    const int t = value_pass_token(wave, rl);
     Row w;
-    load_row(w, L.st.ph[0][value_pass_token(wave, rl)], rl.q);
+    load_row(w, L.st.ph[0][t], rl.q);
     half2_t h[16];
     row_pairs(w, h);
+    if (ROWS > 1 && __builtin_amdgcn_ballot_w64(t >= nr) != 0) {  // (the slots from nr on hold something else)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) w.p[m] = make_uint4(0, 0, 0, 0);
+      if (t >= nr) load_row(w, v_new + (bh * T + t - nr) * kHeadDim, rl.q);
+      half2_t fresh[16];
+      row_pairs(w, fresh);
+      rotate_rows(fresh, rl.q);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) h[e] = t < nr ? h[e] : fresh[e];
+    }
     quantize_value_pass<BITS>(h, wave, rl, lane, L.img);
   }
   lds_barrier();
@@ -1161,8 +1235,8 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
     for (int kk = 0; kk < 4; ++kk) asm volatile("" : "+v"(ke.k[kk].x), "+v"(ke.k[kk].y), "+v"(ke.k[kk].z), "+v"(ke.k[kk].w));  // (they have arrived, too)
   }
   lds_barrier();
-  // every wave has the window's rows: count this part in.  The arrival that completes the sequence stores the new row -- raw key,
-  // rotated value -- in slot 0 for all its kv heads and commits.
+  // every wave has the window's rows: count this part in.  The arrival that completes the sequence stores the new rows -- raw key,
+  // rotated value -- that stay in the window, from slot 0 on, for all its kv heads and commits.
   int before = 0;
   if (tid == 0) before = __hip_atomic_fetch_add(c.split_done + (long long)b * c.H_kv, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   {
@@ -1192,24 +1266,29 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
     store_states<true>(c, bh, fp, false, L.st, acc, P_old, wave, lane);
   }
   if (flag == 2) {
-    for (int g2 = wave; g2 < c.H_kv; g2 += kWaves) {
+    for (int i = wave; i < c.H_kv * n; i += kWaves) {
+      const int g2 = ROWS == 1 ? i : i / n, r = i - g2 * n, u = nr + r;
+      // (Sliding value window: the values of the new rows that were quantized stay in their slots u; the key that is stored along
+      // with them lands in a dead one.)
+      if (ROWS > 1 && !SLIDING && u < kGroup) continue;
       const long long bh2 = (long long)b * c.H_kv + g2;
-      store_window_row(reinterpret_cast<half_t*>(c.k_res) + bh2 * c.R * kHeadDim,
-                       reinterpret_cast<half_t*>(c.v_res) + bh2 * c.R * kHeadDim, nr - plan.n_flush, k_new + bh2 * kHeadDim,
-                       v_new + bh2 * kHeadDim, lane);
+      store_window_row(reinterpret_cast<half_t*>(c.k_res) + bh2 * c.R * kHeadDim, reinterpret_cast<half_t*>(c.v_res) + bh2 * c.R * kHeadDim,
+                       u % kGroup, k_new + (bh2 * T + r) * kHeadDim, v_new + (bh2 * T + r) * kHeadDim, lane);
     }
   }
-  if (flag != 0 && tid == 0) finish(c, b, nq, 1, plan, flag == 2);
+  if (flag != 0 && tid == 0) finish(c, b, nq, n, plan, flag == 2);
 }
 
 // Items as in append_states_kernel, without chunks.
-template <bool SLIDING, int BITS>
+// ROWS: 1, or kFewRows for an append of 2 .. kFewRows rows (a kernel of its own, so that the generation step carries none of it).
+template <bool SLIDING, int BITS, int ROWS>
 __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
                                                                  const half_t* __restrict__ v_new,
-                                                                 const int32_t* __restrict__ n_new) {
+                                                                 const int32_t* __restrict__ n_new, int rows_T) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   TokenLds<BITS>& L = *reinterpret_cast<TokenLds<BITS>*>(lds_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int T = ROWS == 1 ? 1 : rows_T;
   const uint32_t n_pairs = (uint32_t)c.B * (uint32_t)c.H_kv;  // at most 2^24
   const uint32_t n_items = kParts * 8u * ((n_pairs + 7u) / 8u);
   const uint32_t G = gridDim.x;
@@ -1221,17 +1300,22 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
     }
     if (tid < kWaves) L.ahead[tid] = 0;
     __syncthreads();
-    // Wave w requests the new row of the pair of the item that thread w looks at in the first round while the sequence's
-    // counters are on their way (most such appends only store that row into the window).  The row goes straight to LDS,
+    // Wave w requests the new rows of the pair of the item that thread w looks at in the first round while the sequence's
+    // counters are on their way (most such appends only store them into the window).  One row goes straight to LDS,
     // 4 bytes per lane.
     int pre_p = -1;
+    NewRows<ROWS> pre;
     if (k0 == 0 && (uint32_t)wave * G + blockIdx.x < n_items) {
       const uint32_t it = (uint32_t)wave * G + blockIdx.x;
       const uint32_t p = (it >> 4) * 8u + (it & 7u);
       if (((it >> 3) & 1u) == 0u && p < n_pairs) {
         pre_p = (int)p;
-        __builtin_amdgcn_global_load_lds(k_new + (long long)p * kHeadDim + 2 * lane, &L.row[wave][0], 4, 0, 0);
-        __builtin_amdgcn_global_load_lds(v_new + (long long)p * kHeadDim + 2 * lane, &L.row[wave][64], 4, 0, 0);
+        if constexpr (ROWS == 1) {
+          __builtin_amdgcn_global_load_lds(k_new + (long long)p * kHeadDim + 2 * lane, &L.row[wave][0], 4, 0, 0);
+          __builtin_amdgcn_global_load_lds(v_new + (long long)p * kHeadDim + 2 * lane, &L.row[wave][64], 4, 0, 0);
+        } else {
+          request_rows_of_pair(pre, (int)p, k_new, v_new, T, lane);
+        }
       }
     }
     // every thread looks at one item: what needs a wave or the workgroup is listed, the rest is counted in at once
@@ -1241,7 +1325,7 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
       const uint32_t p = (it / (8u * kParts)) * 8u + (it & 7u);
       if (p < n_pairs) {
         const int b = (int)(p / (uint32_t)c.H_kv);
-        const Counters s = read_counters(c, b, n_new, 1, 0);
+        const Counters s = read_counters(c, b, n_new, T, 0);
         if (s.plan.err || s.n == 0) {
           if (s.plan.err && own == 0) atomicOr(c.status, s.plan.err);
           bool clean;
@@ -1264,7 +1348,7 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
           const int at = atomicAdd(&L.n_heavy, 1);
           L.heavy[at] = (int)(p * kParts) + own;
           L.heavy_nq[at] = s.nq;
-          L.heavy_nr[at] = s.nr;
+          L.heavy_nr[at] = s.nr + 256 * s.n;
         }
       }
     }
@@ -1276,16 +1360,20 @@ __global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, 
       s.nr = L.ahead_nr[wave];
       s.n = L.ahead_n[wave];
       s.plan = plan_append(s.nq, s.nr, s.n, c.R, 0, c.max_groups);
-      light_item<SLIDING>(c, pre_p, k_new, v_new, n_new, lane, &s, __builtin_bit_cast(uint32_t, L.row[wave][lane]),
-                          __builtin_bit_cast(uint32_t, L.row[wave][64 + lane]));
+      if constexpr (ROWS == 1) {
+        pre.k[0] = __builtin_bit_cast(uint32_t, L.row[wave][lane]);
+        pre.v[0] = __builtin_bit_cast(uint32_t, L.row[wave][64 + lane]);
+      }
+      light_item<SLIDING, ROWS>(c, pre_p, k_new, v_new, n_new, T, lane, &s, pre);
     }
-    for (int i = wave; i < n_light; i += kThreads / 64) light_item<SLIDING>(c, L.light[i], k_new, v_new, n_new, lane);
+    for (int i = wave; i < n_light; i += kThreads / 64) light_item<SLIDING, ROWS>(c, L.light[i], k_new, v_new, n_new, T, lane, nullptr, pre);
     for (int i = 0; i < n_heavy; ++i) {
       // (the thread index is made opaque here so that none of the flush's address arithmetic is hoisted to the top of
       // the kernel, where every launch -- most of them flush nothing -- would pay for it)
       int tid_here = tid;
       asm volatile("" : "+v"(tid_here));
-      flush_item<BITS>(c, L, L.heavy[i], L.heavy_nq[i], L.heavy_nr[i], k_new, v_new, tid_here);
+      flush_item<SLIDING && (ROWS > 1), BITS, ROWS>(c, L, L.heavy[i], L.heavy_nq[i], L.heavy_nr[i] & 255, ROWS == 1 ? 1 : L.heavy_nr[i] >> 8,
+                                                    k_new, v_new, T, tid_here);
       __syncthreads();
     }
     __syncthreads();
@@ -1309,17 +1397,20 @@ int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_
   const half_t* kk = reinterpret_cast<const half_t*>(k_new);
   const half_t* vv = reinterpret_cast<const half_t*>(v_new);
   const long long pairs = (long long)c.B * c.H_kv;
-  if (T == 1 && keep == 0) {
+  if (keep == 0 && (T == 1 || (T <= kFewRows && T * (long long)c.H_kv <= kFewRowsOfAllHeads))) {
     const long long n_items = (long long)kParts * 8 * ((pairs + 7) / 8);
     // one workgroup per compute unit at most (the LDS of a flush fills most of one); items beyond that are taken
     // in further rounds by the same workgroups
     const int grid = (int)(n_items < 256 ? n_items : 256);
-    void (*kernel)(kvlinc_cache, const half_t*, const half_t*, const int32_t*) =
-        c.bits == 4 ? (sliding ? append_token_kernel<true, 4> : append_token_kernel<false, 4>)
-                    : (sliding ? append_token_kernel<true, 2> : append_token_kernel<false, 2>);
+    typedef void (*kernel_t)(kvlinc_cache, const half_t*, const half_t*, const int32_t*, int);
+    const kernel_t one = c.bits == 4 ? (sliding ? append_token_kernel<true, 4, 1> : append_token_kernel<false, 4, 1>)
+                                     : (sliding ? append_token_kernel<true, 2, 1> : append_token_kernel<false, 2, 1>);
+    const kernel_t few = c.bits == 4 ? (sliding ? append_token_kernel<true, 4, kFewRows> : append_token_kernel<false, 4, kFewRows>)
+                                     : (sliding ? append_token_kernel<true, 2, kFewRows> : append_token_kernel<false, 2, kFewRows>);
+    const kernel_t kernel = T == 1 ? one : few;
     const size_t lds = c.bits == 4 ? sizeof(TokenLds<4>) : sizeof(TokenLds<2>);
     if (launch_with_lds(kernel, lds) != KVLINC_OK) return KVLINC_EHIP;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, c, kk, vv, n_new);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, c, kk, vv, n_new, T);
     return hipGetLastError() == hipSuccess ? KVLINC_OK : KVLINC_EHIP;
   }
   const long long groups_most = ((long long)T + c.R + kGroup - 1) / kGroup;
