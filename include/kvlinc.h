@@ -18,7 +18,9 @@
  *     arguments on the host, enqueues kernels on `stream` (a hipStream_t passed as void*; NULL = the default stream)
  *     and returns.
  *   - kvlinc_half is the bit pattern of an IEEE binary16 number.
- *   - Return value: 0 = enqueued; negative = rejected before any launch, nothing was touched.
+ *   - Return value: 0 = enqueued; negative = rejected before any launch, nothing was touched.  (KVLINC_EHIP alone can come
+ *     later: the runtime has refused a call or a launch.  An append of more than one launch may by then have written dead
+ *     storage, see below, and split_done has to be zeroed before the cache is used again.)
  *   - Faults only the device can see (capacity exhausted, non-finite input, append to a cache whose
  *     last group is partial) set bits in *status and leave that sequence unchanged: its counters, its live group
  *     records and window rows, and its states S, P, S16 (in all KV heads) are bit for bit what they were.  Storage
@@ -186,16 +188,19 @@ int kvlinc_cache_validate(const kvlinc_cache* cache);
  *
  * Per flushed group: key scale / zero-point / codes per channel, value scale / zero-point / codes per token
  * of the rotated value, S += phi_k(K - K_q)^T V_q and P += sum phi_k(K - K_q) when the adapters are given.
- * New tokens that stay in the window are stored as raw key and rotated fp16 value.  One kernel launch (a bulk
- * append, T > 1, to a cache with more than one KV head or with KVLINC_FLAG_SLIDING_VALUES, or of a long prompt as
- * below, is preceded by a short launch that looks for non-finite input): the workgroup of a sequence that finishes
- * last updates n_quant / n_res, after all of them have read the old values, and only if none of them found a fault.
+ * New tokens that stay in the window are stored as raw key and rotated fp16 value.  An append of one row, or of a few
+ * (T <= 8, T * H_kv <= 192, keep_residual = 0), is one kernel launch.  Any other is two: the first looks at every new row
+ * for non-finite input and writes dead storage only -- the group records, and the rows that stay in the window where no
+ * live slot can be touched --, the second updates the states, stores the other window rows and commits.  (The first is
+ * cut into several where it would pass 2^32 threads, from 8 million (sequence, KV head) pairs on.)  Either way the
+ * workgroup of a sequence that finishes last updates n_quant / n_res, after all of them have read the old values, and only
+ * if none of them found a fault.
  *
  * Reproducibility: records, window rows and counters are the same bits in every run.  So are S, P and S16, except
  * after a bulk append of a long prompt to few sequences (T + R >= 64 groups, B * H_kv < 64, and a cache that keeps the
  * fp32 S): its groups are shared out in chunks over the chip, and the chunks' shares of S and P meet in memory by
  * atomic fp32 additions, whose order -- and with it the last bits of S, P -- differs from run to run (the same sums,
- * inside the same tolerance; one 131072-token prompt: 24 ms -> 1.8 ms).
+ * inside the same tolerance; one 131072-token prompt: 0.48 ms, 24 ms without the chunks).
  */
 int kvlinc_append_quantize(const kvlinc_cache* cache, const kvlinc_half* k_new, const kvlinc_half* v_new,
                            const int32_t* n_new, int32_t T, int32_t keep_residual, void* stream);

@@ -409,9 +409,10 @@ __device__ __forceinline__ bool rows_stored_early(bool sliding, int nr, const Ap
 // records lie beyond the counters: dead storage, whatever becomes of the append.  A key or rotated value that is not finite
 // raises the sequence's flag (bit 30 of its first split_done entry), so that all workgroups of that sequence in the launch
 // that follows refuse the append, whichever head or group the fault is in.
-// Bound: HBM (512 bytes in and 72 out per token and kv head at 2 bits) and the vector unit about equally; workgroups of four
-// waves and 50 KB of LDS, three per compute unit, keep enough loads in flight.  Measured: 16 prompts of 8192 tokens (8 kv
-// heads; 611 MB) 140 us, 4.4 TB/s; a pass that only looked for non-finite rows had taken 164 us before.
+// Bound: the vector unit (78 % of the busy time at 2 bits); 512 bytes in and 72 out per token and kv head come second.
+// Workgroups of four waves and, at 2 (4) bits, 50 (60) KB of LDS, three (two) per compute unit.  Measured, 16 prompts of 8192
+// tokens (8 kv heads; 611 MB): 140 us, 4.4 TB/s; 290 us at 4 bits; a pass that only looked for non-finite rows had taken 164
+// us before.
 constexpr int kQuantWaves = 4;
 template <bool SLIDING, int BITS>
 __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
@@ -493,9 +494,9 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
 //   wave w, row rho of its tile: token 16 (4 (w % 2) + rho % 4) + 4 (w / 2) + rho / 4;
 //   phi in LDS: [feature][token % 16][token / 16];
 //   S update: wave w owns the features 32 (w / 2) .. + 31 and the channels 64 (w % 2) .. + 63.
-// Bound: the vector and the matrix instructions of a group one after the other (two waves per SIMD, all in the same phase:
-// about 7000 and 4100 cycles of 11300 a group and half) and LDS (about 5500).  Measured, 16 prompts of 8192 tokens
-// (8 kv heads): 290 to 360 us for the states as the clock goes (500 us before the terms were formed with mixed-precision
+// Bound: the vector and the matrix instructions of a group one after the other (two waves per SIMD, all in the same phase):
+// of the busy time 62 % vector, 34 % matrix, 8 % both at once; LDS 39 %.  Measured, 16 prompts of 8192 tokens
+// (8 kv heads): 300 to 370 us for the states as the clock goes (500 us before the terms were formed with mixed-precision
 // fused multiply-adds, the four contractions chained and the loads freed of execution masks; 1742 us, quantization included,
 // when the same workgroups also quantized the group in LDS, each half for itself).  Two teams of four waves, one at the
 // logits and the softmax while the other is at the update, took 10 % longer: one wave of a kind per SIMD does not hide its own latencies.

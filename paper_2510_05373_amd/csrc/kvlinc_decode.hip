@@ -396,7 +396,8 @@ constexpr float kFusedBound = 0x1p20f;
 
 // base[nb] = what exponent() takes with a score of the head.  Above kFusedBound (no ordinary keys and queries get there) the
 // scores themselves are replaced by their distance from the reference, rounded as the reference is, and the base is 0.  (The look
-// takes 0 to 0.4 % of a step: 16 sequences of 8k tokens 26.29 -> 26.32 us, one of 131072 tokens 24.95 -> 25.04 us.)
+// takes 0 to 0.9 % of a step: 16 sequences of 8k tokens 26.29 -> 26.36 us, one of 131072 tokens 24.95 -> 25.10 us; one branch for
+// both looks takes the same.)
 template <int NB>
 __device__ __forceinline__ void update_reference(float (&sc)[NB][8], const float (&off)[NB], float (&base)[NB], WaveState<NB>& st, float slack) {
 #pragma unroll
@@ -505,8 +506,8 @@ __device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (
 // group still have their fp16 rotated values in the window slots j.  Their share of E V is formed here from those values
 // by the one wave that has the newest group, on v_mfma_f32_4x4x4_16B_f16 as in window_half: rows = the 4 heads of a head
 // block, columns = 64 channels (lane = channel), k = 4 window slots, the probabilities (binary16, through LDS) broadcast
-// from one lane quad per block of 4 slots.  The result goes to the spare row of the accumulators through `out`, this
-// wave's [NB * 4][128] slice of the combine buffer.
+// from one lane quad per block of 4 slots.  The result is added to the accumulators by way of `out`, this wave's
+// [NB * 4][128] slice of the combine buffer.
 template <int NB>
 __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win, const float (&sc)[NB][8], const float (&base)[NB], int from,
                                                const Roles& lr, WaveState<NB>& st, int lane, float (*out)[kHeadDim]) {

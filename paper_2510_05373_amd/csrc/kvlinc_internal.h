@@ -26,10 +26,11 @@ struct Rec {
 constexpr int kMaxGq = 8;       // query heads per KV head supported by the decode kernels
 
 // Partial result of one block of tokens for one query head (Alg. 1: m^j, l^j, Y_s^j), log2 domain:
-// {m, l, unused, unused, acc[128]}; m = -inf marks an empty block whose other fields are undefined.
+// {m, l, unused, unused, acc[128]}; m = -inf marks an empty block, whose l and acc are zero (the merge gives it the weight 0 but
+// does not leave it out).
 constexpr int kPartStride = 132;
 
-// What one append does to one sequence (same arithmetic in the flush kernel and in the counter commit).
+// What one append does to one sequence (same arithmetic in every append kernel and in the counter commit).
 struct AppendPlan {
   int n_flush;   // tokens leaving the window / new-token stream into quantized groups
   int n_groups;  // groups written (the last one partial iff n_flush % 128 != 0)
