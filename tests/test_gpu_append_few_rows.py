@@ -137,3 +137,39 @@ def test_no_room_for_the_group(kv):
     cache.append(x[:, :, :3].contiguous(), x[:, :, :3].contiguous())
     assert int(cache.status.item()) == kv.KVLINC_ST_CAPACITY
     assert all(torch.equal(a, b) for a, b in zip(_live(cache, False), before))
+
+
+@pytest.mark.parametrize("sliding", [False, True])
+@pytest.mark.parametrize("T", [3, 150])
+def test_appends_of_several_rows_replayed_from_a_graph(kv, T, sliding):
+    """One launch (3 rows) and two (150 rows), through the current stream; every replay against an eager twin, a refused call
+    among them."""
+    import torch
+    B, H_kv, replays = 3, 2, 50 if T == 3 else 8
+    pair = [_cache(kv, B, H_kv, 2, sliding, True, 95, capacity=1536)[0] for _ in range(2)]
+    first = torch.randn(B, H_kv, 120, 128, device="cuda").half()
+    for c in pair:
+        c.append(first, first, n_new=tl.to_dev(np.array([120, 60, 1], dtype=np.int32)))
+    graphed, eager = pair
+    k_in, v_in = (torch.zeros(B, H_kv, T, 128, dtype=torch.float16, device="cuda") for _ in range(2))
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        graphed.append(k_in, v_in)
+    for i in range(replays):
+        k, v = (torch.randn(B, H_kv, T, 128, device="cuda").half() for _ in range(2))
+        if i == replays // 2:
+            k[1, 1, T - 1, 5] = float("inf")
+        k_in.copy_(k)
+        v_in.copy_(v)
+        torch.cuda.synchronize()
+        g.replay()
+        eager.append(k, v)
+        torch.cuda.synchronize()
+        names = ["n_quant", "n_res", "S", "P", "S16", "status", "split_done"]
+        assert all(torch.equal(getattr(graphed, n), getattr(eager, n)) for n in names), i
+        for b in range(B):
+            nq, nr = int(eager.n_quant[b]), int(eager.n_res[b])
+            assert torch.equal(graphed.groups[b, :, :nq // 128], eager.groups[b, :, :nq // 128])
+            assert torch.equal(graphed.k_res[b, :, :nr], eager.k_res[b, :, :nr])
+    assert int(graphed.status.item()) == kv.KVLINC_ST_NONFINITE and int(graphed.n_quant.max().item()) > 0
