@@ -664,135 +664,212 @@ __device__ __forceinline__ void window_half(const kvlinc_cache& c, const half_t*
 // ---- correction terms (Sec. 3.3: C_n = phi_q(q) S, C_d = phi_q(q) P; Eq. 6 for phi) -----------------------------------
 // The work of a kv head is cut into kCorrParts parts over the rows of S: part r covers the kPartFeat features
 // kPartFeat (r % kPartsPerHalf) .. of half hs = r / kPartsPerHalf of phi.  A correction workgroup serves one part
-// for up to kCorrSeqs sequences, on the matrix cores:
-//   phase 1, wave w = query head w of the block of four: logits[s][f] = sum_c q[s][c] W[c][f] for the sequences s as
-//            the 4 rows of the 4x4x4 blocks, block = 4 features (with 32-feature parts blocks 8..15 repeat blocks 0..7), k = 4 channels
-//            (32 steps); the W rows are read in their natural order (a lane reads 4 features of one channel) and
-//            transposed inside the lane quads;
-//   phase 2, wave s = sequence s: e_f = exp(logit_f - m_r) with the part's own maximum m_r,
-//            Z_r = sum_f e_f, Cd_r = sum_f e_f P[f], and Cn_r = e S with the 4 heads as rows, block = 4 channels,
-//            k = 4 features (kPartSteps steps per channel half), S taken from its binary16 tile copy.
+// for 4 or 8 sequences, on the matrix cores:
+//   phase 1, wave w = query head w of a block of four: logits[s][f] = sum_c q[s][c] W[c][f] on v_mfma_f32_16x16x32_f16 with
+//            the sequences s as rows and features as columns.  The W rows are read in their natural order: a lane takes 4
+//            neighbouring features of the 8 channels whose products it feeds, so that the B operands of 4 column tiles
+//            (feature 4 (lane % 16) + i in tile i) are byte permutations of its own registers.
+//   phase 2, wave w = sequences w, w + 4, ...: e_f = exp(logit_f - m_r) with the part's own maximum m_r,
+//            Z_r = sum_f e_f, Cd_r = sum_f e_f P[f], and Cn_r = e S on the 4x4x4 blocks with the 4 heads as rows, block = 4
+//            channels, k = 4 features (kPartSteps steps per channel half), S taken from its binary16 tile copy.
 // Output per (query head, part): {Cd_r, m_r, Z_r, -, Cn_r[128]}; the softmax normalisation of each half of phi over
 // its parts is left to the merge.
+// Bound: latency, a chain of loads, two products and a hand-over.  Phase 1 on the 4x4x4 blocks took a transpose inside lane quads
+// (8 vector instructions a load, 256 a wave) and a chain of 32 dependent products where it now takes 64 byte permutations and 4
+// chains of 4; the reductions of phase 2 went through LDS; W, needed first, came behind the S tiles; and with fewer than 4 heads
+// the other waves waited.  Step (append and decode), before and after: 1 sequence of 300 tokens 14.3 -> 12.7 us, 16 of 8k
+// 26.3 -> 25.9, 144 of 1280 81.6 -> 75.0; 32 sequences of 32 single heads 50.7 -> 46.5.  Requesting all S tiles ahead of the
+// first product, or ahead of W, gained nothing and spilled with two head blocks.
 
 // Workgroup barrier for data exchanged through LDS by ordinary LDS writes.
 __device__ __forceinline__ void barrier_lds_only() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-constexpr int kCorrParts = 4;                // 4 or 8
+constexpr int kCorrParts = 4;
 constexpr int kPartFeat = 256 / kCorrParts;  // features per part
-constexpr int kPartSteps = kPartFeat / 4;    // feature steps (and distinct feature blocks) per part
+constexpr int kPartSteps = kPartFeat / 4;    // feature steps per part
 constexpr int kPartsPerHalf = kCorrParts / 2;
-constexpr int kCorrSeqs = 4;  // sequences served by one correction workgroup (the rows of its matrix products)
+static_assert(kPartFeat == 64, "a row of 16 lanes takes the features of a part, four each");
+constexpr int kMaxCorrSeqs = 8;  // sequences a correction workgroup may serve, at most the 16 rows of its matrix products
 // binary16 tile copy of S: tile (part r, channel half hh, feature step fs) holds, for lane = 4 blk + j, the 4 halves
 // S[64 r + 4 fs + k][64 hh + lane], k = 0..3: what lane (blk, j) feeds as B operand of that step.
 constexpr int kStateTileHalfs = 256;  // halves per tile (64 lanes x 4)
 // r64 = 64-feature block of S (0..3), hh = channel half, fs = feature step inside the block (0..15)
 __device__ __forceinline__ long long state_tile(int r64, int hh, int fs) { return ((r64 * 2 + hh) * 16 + fs) * kStateTileHalfs; }
 
-__device__ __forceinline__ float quadgroup_allmax(float v) {  // over the 16 lanes that share lane & 3
-  v = fmaxf(v, __shfl_xor(v, 4, 64));
-  v = fmaxf(v, __shfl_xor(v, 8, 64));
-  v = fmaxf(v, __shfl_xor(v, 16, 64));
-  v = fmaxf(v, __shfl_xor(v, 32, 64));
-  return v;
+// over the 16 lanes that share lane & 3
+__device__ __forceinline__ float quadgroup_allmax(float v) {
+  v = fmaxf(v, dpp_f<kRowRor4>(v));
+  v = fmaxf(v, dpp_f<kRowRor8>(v));
+  const auto a = __builtin_amdgcn_permlane16_swap(as_bits(v), as_bits(v), false, false);
+  v = fmaxf(as_f32(a[0]), as_f32(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(as_bits(v), as_bits(v), false, false);
+  return fmaxf(as_f32(b[0]), as_f32(b[1]));
 }
 __device__ __forceinline__ float quadgroup_allsum(float v) {
-  v += __shfl_xor(v, 4, 64);
-  v += __shfl_xor(v, 8, 64);
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
+  v += dpp_f<kRowRor4>(v);
+  v += dpp_f<kRowRor8>(v);
+  return xrow_allsum(v);
 }
 
-// sLogit: [kCorrSeqs][4][kPartFeat] floats of LDS.
-// FEW_HEADS: fewer than 4 query heads per kv head (one head block).  The waves whose head does not exist then skip
-// phase 1 and leave their logits as they are: phase 2 forms that head's row from them, isolated from the others, and
-// stores nothing of it.  (A variant of its own, down to the kernel: with the test in the common code the compiler no
-// longer staggers the loads of the two phases, and a second copy of this function in one kernel costs that kernel
-// registers; either way the launches with 4 or more heads lose 3 to 4 % of their time.)
-template <bool FEW_HEADS>
+// Phase 1 for one head: channels 32 kk .. + 31 for the KS steps kk from k0 on.  logits: [sequence][..][kPartFeat], `stride` floats
+// from one sequence to the next, this head's first.
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+template <int KS>
+struct CorrWeights {
+  uint2 w[KS][8];
+  half8_t q[KS];
+};
+template <int KS>
+__device__ __forceinline__ void request_weights(CorrWeights<KS>& x, const half_t* __restrict__ W0, const half_t* __restrict__ q0, int k0, int lane) {
+  const int l16 = lane & 15, kq = lane >> 4;
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) {
+    x.q[kk] = *reinterpret_cast<const half8_t*>(q0 + 32 * (k0 + kk) + 8 * kq);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      x.w[kk][i] = *reinterpret_cast<const uint2*>(W0 + (32 * (k0 + kk) + 8 * kq + i) * (kRank / 2) + 4 * l16);
+  }
+}
+template <int KS>
+__device__ __forceinline__ void part_logits(const CorrWeights<KS>& x, int n_seq, int stride, float* logits, int lane) {
+  const int l16 = lane & 15, kq = lane >> 4;
+  float4_t d[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) d[i] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t b[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const uint2 lo = x.w[kk][2 * p], hi = x.w[kk][2 * p + 1];
+        b[p] = __builtin_amdgcn_perm(i < 2 ? hi.x : hi.y, i < 2 ? lo.x : lo.y, (i & 1) == 0 ? 0x05040100u : 0x07060302u);
+      }
+      d[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x.q[kk], __builtin_bit_cast(half8_t, make_uint4(b[0], b[1], b[2], b[3])), d[i], 0, 0, 0);
+    }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    if (4 * kq + r < n_seq) *reinterpret_cast<float4*>(logits + (4 * kq + r) * stride + 4 * l16) = make_float4(d[0][r], d[1][r], d[2][r], d[3][r]);
+}
+
+// sLogit: [n_seq][4 n_head_blocks][kPartFeat] floats of LDS.
+// FEW_HEADS: fewer than 4 query heads per kv head (one head block); the waves whose head does not exist then take a share of
+// the channels of the others, and the sums over the shares are left to phase 2.  (A variant of its own, down to the kernel: a
+// second copy of this function in one kernel costs that kernel registers.)
+template <bool FEW_HEADS, int NB>
 __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, const half_t* __restrict__ q,
                                                      float* __restrict__ corr, int gq, int g, int r, int b_first,
-                                                     int n_seq, int n_head_blocks, int lane, int wave, float* sLogit) {
+                                                     int n_seq, int lane, int wave, float* sLogit) {
   const int hs = r / kPartsPerHalf, fpart = kPartFeat * (r % kPartsPerHalf);  // features 128 hs + fpart ..
-  const int blk = lane >> 2, j = lane & 3, fblk = blk & (kPartSteps - 1);
-  const int r64 = (128 * hs + fpart) >> 6, fs0 = (fpart & 63) >> 2;  // position of the part among the state tiles
-  const uint32_t perm_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
+  const int blk = lane >> 2, j = lane & 3;
   const half_t* Wq = reinterpret_cast<const half_t*>(c.Wq);
   const half_t* S16 = reinterpret_cast<const half_t*>(c.S16);
-  // everything this wave reads from memory is requested at once: the state tiles and P of its sequence (phase 2),
-  // then the W rows and q of its head (phase 1)
-  const bool has_seq = wave < n_seq;
-  const int b_mine = b_first + (has_seq ? wave : 0), bh_mine = b_mine * c.H_kv + g;
-  const half_t* tiles = S16 + (long long)bh_mine * kRank * kHeadDim;
+  constexpr int kRows = 4 * NB;  // logit rows of a sequence
+  auto w_of = [&](int h) { return Wq + ((((long long)g * gq + h) * 2 + hs) * kHeadDim) * (kRank / 2) + fpart; };
+  auto q_of = [&](int h) { return q + ((long long)(b_first + min(lane & 15, n_seq - 1)) * c.H_q + g * gq + h) * kHeadDim; };
+  // S tiles and P of the wave's sequence
   uint2 sreg[2][kPartSteps];
+  float4 p4;
+  auto request_state = [&](int s, int hh) {
+    const long long bh = (long long)(b_first + min(s, n_seq - 1)) * c.H_kv + g;
+    const half_t* tiles = S16 + bh * kRank * kHeadDim + state_tile(r, hh, 0) + 4 * lane;
 #pragma unroll
-  for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-    for (int fs = 0; fs < kPartSteps; ++fs)
-      sreg[hh][fs] = *reinterpret_cast<const uint2*>(tiles + state_tile(r64, hh, fs0 + fs) + 4 * lane);
-  const float4 p4 = *reinterpret_cast<const float4*>(c.P + (long long)bh_mine * kRank + 128 * hs + fpart + 4 * fblk);
-  for (int hb = 0; hb < n_head_blocks; ++hb) {
-    // ---- phase 1: this wave's head, all sequences ----
-    if (!FEW_HEADS || wave < gq) {
-      const int h = hb * 4 + wave;
-      const int hc = h < gq ? h : gq - 1;
-      const int b_row = b_first + (j < n_seq ? j : n_seq - 1);  // row j of A = sequence j
-      const half_t* qrow = q + ((long long)b_row * c.H_q + g * gq + hc) * kHeadDim + 4 * blk;
-      const half_t* W0 = Wq + (((long long)g * gq + hc) * 2 + hs) * kHeadDim * (kRank / 2) + (long long)j * (kRank / 2) +
-                         fpart + 4 * fblk;
-      uint2 w[32];
-#pragma unroll
-      for (int i = 0; i < 32; ++i) w[i] = *reinterpret_cast<const uint2*>(W0 + (long long)(4 * i) * (kRank / 2));
-      const half4_t a0 = __builtin_bit_cast(half4_t, *reinterpret_cast<const uint2*>(qrow));       // channels 4 blk ..
-      const half4_t a1 = __builtin_bit_cast(half4_t, *reinterpret_cast<const uint2*>(qrow + 64));  // 64 + 4 blk ..
-      float4_t d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < 32; ++i) {
-        const half4_t bop = quad_transpose(w[i].x, w[i].y, perm_sel, lane);
-        d = mfma_bcast(i < 16 ? a0 : a1, bop, d, i & 15);
-      }
-      if (blk < kPartSteps) {
-#pragma unroll
-        for (int s = 0; s < kCorrSeqs; ++s) sLogit[(s * 4 + wave) * kPartFeat + lane] = d[s];
-      }
+    for (int fs = 0; fs < kPartSteps; ++fs) sreg[hh][fs] = *reinterpret_cast<const uint2*>(tiles + fs * kStateTileHalfs);
+    if (hh == 0) p4 = *reinterpret_cast<const float4*>(c.P + bh * kRank + kPartFeat * r + 4 * blk);
+  };
+  int n_shares = 1;  // shares of the channels that the logits are in
+  if constexpr (FEW_HEADS) {
+    if (gq == 1) {
+      n_shares = 4;
+      CorrWeights<1> x;
+      request_weights<1>(x, w_of(0), q_of(0), wave, lane);
+      request_state(wave, 0);
+      part_logits<1>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
+    } else if (gq == 2) {
+      n_shares = 2;
+      CorrWeights<2> x;
+      request_weights<2>(x, w_of(wave >> 1), q_of(wave >> 1), 2 * (wave & 1), lane);
+      request_state(wave, 0);
+      part_logits<2>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
+    } else {
+      CorrWeights<4> x;
+      if (wave < gq) request_weights<4>(x, w_of(wave), q_of(wave), 0, lane);
+      request_state(wave, 0);
+      if (wave < gq) part_logits<4>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
     }
-    barrier_lds_only();
-    // ---- phase 2: this wave's sequence, the four heads of the block; lane = (feature step fs = blk, head j) ----
-    if (has_seq) {
-      const int b = b_mine;
-      // lanes of blocks beyond the part's feature blocks hold no features of their own: their terms are made zero
-      const float4 l4 = *reinterpret_cast<const float4*>(sLogit + (wave * 4 + j) * kPartFeat + 4 * fblk);
-      const float mx = quadgroup_allmax(fmaxf(fmaxf(l4.x, l4.y), fmaxf(l4.z, l4.w)));
-      const float live = blk < kPartSteps ? 1.0f : 0.0f;
-      const float e0 = live * __expf(l4.x - mx), e1 = live * __expf(l4.y - mx), e2 = live * __expf(l4.z - mx),
-                  e3 = live * __expf(l4.w - mx);
-      const float z = quadgroup_allsum((e0 + e1) + (e2 + e3));
-      const float cd = quadgroup_allsum(fmaf(e0, p4.x, fmaf(e1, p4.y, fmaf(e2, p4.z, e3 * p4.w))));
-      const half4_t aop = {(half_t)e0, (half_t)e1, (half_t)e2, (half_t)e3};
-      float4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  } else {
 #pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
+    for (int hb = 0; hb < NB; ++hb) {
+      const int h = min(hb * 4 + wave, gq - 1);
+      CorrWeights<4> x;
+      request_weights<4>(x, w_of(h), q_of(h), 0, lane);
+      if (hb == NB - 1) request_state(wave, 0);
+      part_logits<4>(x, n_seq, kRows * kPartFeat, sLogit + (hb * 4 + wave) * kPartFeat, lane);
+    }
+  }
+  request_state(wave, 1);
+  barrier_lds_only();
+  // ---- phase 2: the wave's sequences in turn, the four heads of a block; lane = (feature step fs = blk, head j) ----
+  for (int s = wave; s < n_seq; s += kWaves) {
+    half4_t aop[NB];
+    float cd[NB], mx[NB], z[NB];
 #pragma unroll
-        for (int fs = 0; fs < kPartSteps; ++fs)
-          acc[hh] = mfma_bcast(aop, __builtin_bit_cast(half4_t, sreg[hh][fs]), acc[hh], fs);
+    for (int hb = 0; hb < NB; ++hb) {
+      const float* row = sLogit + (long long)s * kRows * kPartFeat + 4 * blk;
+      float4 l4;
+      if (FEW_HEADS && n_shares > 1) {
+        const int first = n_shares * min(j, gq - 1);  // (rows of heads that do not exist: a copy, nothing of which is stored)
+        l4 = *reinterpret_cast<const float4*>(row + first * kPartFeat);
+        for (int i = 1; i < n_shares; ++i) {
+          const float4 t = *reinterpret_cast<const float4*>(row + (first + i) * kPartFeat);
+          l4.x += t.x; l4.y += t.y; l4.z += t.z; l4.w += t.w;
+        }
+      } else {
+        l4 = *reinterpret_cast<const float4*>(row + (hb * 4 + (FEW_HEADS ? min(j, gq - 1) : j)) * kPartFeat);
+      }
+      mx[hb] = quadgroup_allmax(fmaxf(fmaxf(l4.x, l4.y), fmaxf(l4.z, l4.w)));
+      const float e0 = __expf(l4.x - mx[hb]), e1 = __expf(l4.y - mx[hb]), e2 = __expf(l4.z - mx[hb]), e3 = __expf(l4.w - mx[hb]);
+      z[hb] = quadgroup_allsum((e0 + e1) + (e2 + e3));
+      cd[hb] = quadgroup_allsum(fmaf(e0, p4.x, fmaf(e1, p4.y, fmaf(e2, p4.z, e3 * p4.w))));
+      aop[hb] = half4_t{(half_t)e0, (half_t)e1, (half_t)e2, (half_t)e3};
+    }
+    const bool more = s + kWaves < n_seq;
+    float4_t acc[NB][2];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      // (two chains per channel half)
+#pragma unroll
+      for (int hb = 0; hb < NB; ++hb) {
+        float4_t a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int fs = 0; fs < kPartSteps; fs += 2) {
+          a0 = mfma_bcast(aop[hb], __builtin_bit_cast(half4_t, sreg[hh][fs]), a0, fs);
+          a1 = mfma_bcast(aop[hb], __builtin_bit_cast(half4_t, sreg[hh][fs + 1]), a1, fs + 1);
+        }
+        acc[hb][hh] = a0 + a1;
+      }
+      if (more) request_state(s + kWaves, hh);
+    }
+    const int b = b_first + s;
+#pragma unroll
+    for (int hb = 0; hb < NB; ++hb) {
       float* out0 = corr + ((long long)b * c.H_q + g * gq + hb * 4) * kCorrParts * kPartStride;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         if (hb * 4 + i < gq) {
           float* dst = out0 + ((long long)i * kCorrParts + r) * kPartStride;
-          st_coherent(dst + 4 + lane, acc[0][i]);
-          st_coherent(dst + 4 + 64 + lane, acc[1][i]);
+          st_coherent(dst + 4 + lane, acc[hb][0][i]);
+          st_coherent(dst + 4 + 64 + lane, acc[hb][1][i]);
         }
       }
       if (blk == 0 && hb * 4 + j < gq) {
         float* dst = out0 + ((long long)j * kCorrParts + r) * kPartStride;
-        st_coherent(dst, cd);
-        st_coherent(dst + 1, mx);
-        st_coherent(dst + 2, z);
+        st_coherent(dst, cd[hb]);
+        st_coherent(dst + 1, mx[hb]);
+        st_coherent(dst + 2, z[hb]);
       }
     }
-    if (hb + 1 < n_head_blocks) barrier_lds_only();  // the logits buffer is reused
   }
 }
 
@@ -981,15 +1058,17 @@ template <int NB, bool SLIDING = false, int BITS = 2, bool FEW_HEADS = false>
 __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(kvlinc_cache c, const half_t* __restrict__ q,
                                                                    float* __restrict__ part, float* __restrict__ corr,
                                                                    half_t* __restrict__ out, int max_splits,
-                                                                   int avg_splits, int gq, int corr_first) {
-  __shared__ __align__(16) float lds[2 * kWaves * NB * 4 + kWaves * NB * 4 * kHeadDim];
-  __shared__ __align__(16) uint32_t ex[kWaves][2 * kExWords];  // per wave: operand hand-over of q K^T and of E V
+                                                                   int avg_splits, int gq, int corr_first, int corr_seqs) {
+  constexpr int kCombine = 2 * kWaves * NB * 4 + kWaves * NB * 4 * kHeadDim;
+  __shared__ __align__(16) float lds[kCombine + kWaves * 2 * kExWords];
+  static_assert(kCombine + kWaves * 2 * kExWords >= kMaxCorrSeqs * NB * 4 * kPartFeat, "the logits of a correction workgroup");
+  uint32_t (*ex)[2 * kExWords] = reinterpret_cast<uint32_t (*)[2 * kExWords]>(lds + kCombine);  // per wave: operand hand-over of q K^T and of E V
   __shared__ int sFlag;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the schedule in scalar registers
-  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + kCorrSeqs - 1) / kCorrSeqs) : 0;
+  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + corr_seqs - 1) / corr_seqs) : 0;
   const int n_parts = corr != nullptr ? kCorrParts : 0;
 
   const int n_stream = gridDim.x - n_corr;
@@ -1019,19 +1098,19 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   }
 
   if (is_corr) {
-    // ---- one part of the correction (Sec. 3.3: C_n, C_d) for up to kCorrSeqs sequences of one kv head ----
+    // ---- one part of the correction (Sec. 3.3: C_n, C_d) for up to corr_seqs sequences of one kv head ----
     const int id = corr_id;
     // The workgroups that read the same slice of W (same kv head and part, different sequences) are H_kv * kCorrParts
     // apart in the grid: workgroups are dealt to the 8 XCDs in turn, so with an even H_kv they share one L2.
     const int r = id % kCorrParts, g = (id / kCorrParts) % c.H_kv, sb = id / (kCorrParts * c.H_kv);
-    const int b_first = sb * kCorrSeqs;
-    const int n_seq = min(kCorrSeqs, c.B - b_first);
+    const int b_first = sb * corr_seqs;
+    const int n_seq = min(corr_seqs, c.B - b_first);
     // A sequence without quantized tokens has S = P = 0 (the states only change at a flush), so its parts come out
     // as zero without looking at n_quant.
     // (the counters are requested first and looked at last: by then they have long arrived)
     const int nq_head = lane < c.B ? c.n_quant[lane] : 0;
     const int nq_mine = c.n_quant[b_first + min(lane, n_seq - 1)];
-    correction_workgroup<FEW_HEADS>(c, q, corr, gq, g, r, b_first, n_seq, NB, lane, wave, lds);
+    correction_workgroup<FEW_HEADS, NB>(c, q, corr, gq, g, r, b_first, n_seq, lane, wave, lds);
     const int total = batch_groups(c, nq_head, lane);
     // count this workgroup in at each of its sequences; merge those it completes
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1296,7 +1375,13 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   const long long bh = (long long)c.B * c.H_kv;
   const int gq = c.H_q / c.H_kv;
   long long n_corr = 0;
-  if (c.S16 != nullptr && gq <= 4) n_corr = (long long)c.H_kv * kCorrParts * ((c.B + kCorrSeqs - 1) / kCorrSeqs);
+  // Sequences per correction workgroup: 4, one for each wave, and 8 where one query head per kv head makes the weights a small part
+  // of what a workgroup reads and workgroups of 4 sequences would not fit the chip at once (three per compute unit).  Decode
+  // launches, 8 against 4: 32 kv heads of one query head, 8 sequences 1.06 to 1.59, 32 sequences 0.94 to 0.99, 64 and 144
+  // 0.99; 2 to 8 query heads, 8 to 144 sequences of 300 to 4000 tokens 0.94 to 2.46 (mostly above 1.05).
+  auto corr_workgroups = [&](int seqs) { return (long long)c.H_kv * kCorrParts * ((c.B + seqs - 1) / seqs); };
+  const int corr_seqs = gq == 1 && corr_workgroups(4) >= 1024 ? 8 : 4;
+  if (c.S16 != nullptr && gq <= 4) n_corr = corr_workgroups(corr_seqs);
   long long s = (kTargetWorkgroups - n_corr + bh / 2) / bh;  // rounded to nearest
   if (s > kMaxSplits) s = kMaxSplits;
   const long long most = (groups + kWaves - 1) / kWaves;
@@ -1311,7 +1396,7 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // fill most of the chip while the streaming workgroups have long contexts ahead of them (many sequences, 16 or
   // more groups per wave): then the streaming workgroups go first, the longest of them decide when the launch ends,
   // and the correction fills the places the short sequences leave.
-  const long long all_corr = c.S16 != nullptr ? (long long)c.H_kv * kCorrParts * ((c.B + kCorrSeqs - 1) / kCorrSeqs) : 0;
+  const long long all_corr = c.S16 != nullptr ? corr_workgroups(corr_seqs) : 0;
   // (More than 4 heads per kv head: the correction takes the third place of a compute unit, and going last it does not
   // hold up the streaming workgroups.  Launches of 5 to 8 heads, 1 to 8 kv heads, 8 to 64 sequences of 8k to 64k tokens, last
   // against first: at 2 bits 0.92 to 1.00 of the time, at 4 bits 0.98 to 1.02.)
@@ -1330,7 +1415,7 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
       corr_first = 2;
     }
   }
-  return DecodeSplits{(int)s, (int)m, corr_first};
+  return DecodeSplits{(int)s, (int)m, corr_first, corr_seqs};
 }
 
 size_t decode_workspace_floats(const kvlinc_cache& c, int n_splits) {
@@ -1346,11 +1431,11 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   half_t* oo = reinterpret_cast<half_t*>(out);
   float* part = workspace;
   float* corr = c.S16 != nullptr ? workspace + (size_t)c.B * c.H_q * n_splits * kPartStride : nullptr;
-  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + kCorrSeqs - 1) / kCorrSeqs) : 0;
+  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + sp.corr_seqs - 1) / sp.corr_seqs) : 0;
   const dim3 grid(BH * n_splits + n_corr), block(kThreads);
   const int corr_first = sp.corr_first;
   const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
-  void (*kernel)(kvlinc_cache, const half_t*, float*, float*, half_t*, int, int, int, int) =
+  void (*kernel)(kvlinc_cache, const half_t*, float*, float*, half_t*, int, int, int, int, int) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)
                               : (sliding ? decode_main_kernel<1, true, 4> : decode_main_kernel<1, false, 4>))
@@ -1358,9 +1443,9 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 2, true> : decode_main_kernel<1, false, 2, true>)
                               : (sliding ? decode_main_kernel<1, true> : decode_main_kernel<1, false>));
   if (start != nullptr)  // timestamps of the dispatch itself, no extra packets on the stream
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first);
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first, sp.corr_seqs);
   else
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first, sp.corr_seqs);
   return hipGetLastError() == hipSuccess ? KVLINC_OK : KVLINC_EHIP;
 }
 

@@ -1,0 +1,58 @@
+"""GPU parity of the linear correction over the ways in which its workgroups are filled: 1 to 8 query heads per kv head (fewer
+than 4 share their channels out among the waves, more than 4 are two head blocks), numbers of sequences around the 4 and 8 that
+a workgroup serves.  Short contexts and small queries, so that the correction is a large part of the result."""
+import numpy as np
+import pytest
+
+import kvlinc_synth as synth
+from tests import kvlinc_testlib as tl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def kv():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2510_05373_amd as kvmod
+    return kvmod
+
+
+def _check(kv, B, H_kv, gq, bits, pairs, n=150):
+    from oracle import attention as o_attn
+    from oracle import kvcache as o_cache
+    H_q = H_kv * gq
+    K, V = tl.gen_kv(95, B, H_kv, [n] * B)
+    q = (np.random.default_rng(95).standard_normal((B, H_q, 128)) * 0.05).astype(np.float16)
+    Wq, Wk = synth.adapters_q(95, H_q), synth.adapters_k(95, H_kv)
+    Wq = (Wq.astype(np.float32) * 64.0).astype(np.float16)  # peaked feature maps, of small queries too
+    Wk = (Wk.astype(np.float32) * (8.0 if bits == 2 else 40.0)).astype(np.float16)  # (the key error is a fifth at 4 bits)
+    cache = kv.KVLincCache(B, H_q, H_kv, n + 128, Wq=tl.to_dev(Wq), Wk=tl.to_dev(Wk), bits=bits)
+    cache.append(tl.to_dev(K), tl.to_dev(V))
+    got = [cache.decode(tl.to_dev(q)).cpu().numpy() for _ in range(2)]
+    assert np.array_equal(tl.u16(got[0]), tl.u16(got[1]))
+    assert int(cache.split_done.abs().sum().item()) == 0
+    nq = int(cache.n_quant[0].item())
+    assert nq == 128
+    want = {}
+    for b, g in pairs:
+        ref = o_cache.build_cache(K[b, g], V[b, g], nq, Wk=Wk[g], bits=bits)
+        for h in range(g * gq, (g + 1) * gq):
+            want[b, h] = o_attn.decode(q[b, h], ref, Wq[h])
+    tl.check_outputs(got[0], want)
+    # the correction is five times what the tolerance lets pass, or more
+    without = {k: o_attn.decode(q[k[0], k[1]], o_cache.build_cache(K[k[0], k[1] // gq], V[k[0], k[1] // gq], nq, Wk=None, bits=bits), None) for k in list(want)[:1]}
+    for k, y in without.items():
+        assert np.linalg.norm(y - want[k]) > 5 * tl.OUT_REL_L2 * np.linalg.norm(want[k])
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("gq", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("B,H_kv", [(1, 1), (3, 2), (4, 1), (5, 3), (9, 1)])
+def test_heads_and_sequences(kv, B, H_kv, gq, bits):
+    _check(kv, B, H_kv, gq, bits, [(b, g) for b in range(B) for g in range(H_kv)])
+
+
+@pytest.mark.parametrize("B,H_kv", [(12, 64), (13, 64), (16, 64), (17, 64)])  # 8 sequences a workgroup from 13 on
+def test_many_single_heads(kv, B, H_kv):
+    _check(kv, B, H_kv, 1, 2, sorted({(b, g) for b in (0, 3, 4, 7, 8, 11, B - 1) for g in (0, 31, 63)}))
