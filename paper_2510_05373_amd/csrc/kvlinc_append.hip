@@ -32,59 +32,23 @@ __device__ inline bool nonfinite_bits(half_t x) {
 
 // One wave rotates one 128-vector: lane l holds elements 2l and 2l+1.  Stage order h = 1, 2, ..., 64 with
 // (x[i], x[i+h]) <- (x[i] + x[i+h], x[i] - x[i+h]) for (i & h) == 0, then the binary32 scale and one rounding to fp16.
-__device__ inline void fwht128_wave(float& x0, float& x1, int lane) {
-  const float a = x0 + x1;
-  const float b = x0 - x1;
-  x0 = a;
-  x1 = b;
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {  // element stride h = 2m  <->  lane stride m
-    const float o0 = __shfl_xor(x0, m, 64);
-    const float o1 = __shfl_xor(x1, m, 64);
-    const bool upper = (lane & m) != 0;
-    x0 = upper ? (o0 - x0) : (x0 + o0);
-    x1 = upper ? (o1 - x1) : (x1 + o1);
-  }
-  const float c = 0x1.6a09e6p-4f;  // fl32(1/sqrt(128))
-  x0 = x0 * c;
-  x1 = x1 * c;
-  // The contract rounds the product to binary32 first and to fp16 afterwards.  Keep the two roundings apart: a
-  // fused multiply-and-convert instruction would round the exact product once and differ in rare near-tie cases.
-  asm volatile("" : "+v"(x0), "+v"(x1));
-}
-
-// The same rotation for NV independent vectors at once (their cross-lane exchanges overlap); per vector the
-// operations and their order are those of fwht128_wave.
+// NV independent vectors at once.
 template <int NV>
-__device__ inline void fwht128_wave_multi(float (&x0)[NV], float (&x1)[NV], int lane) {
+__device__ inline void fwht128_wave(float (&x)[2 * NV], int lane) {  // x[2 u], x[2 u + 1]: vector u
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
-    const float a = x0[u] + x1[u];
-    const float b = x0[u] - x1[u];
-    x0[u] = a;
-    x1[u] = b;
+    const float a = x[2 * u] + x[2 * u + 1], b = x[2 * u] - x[2 * u + 1];
+    x[2 * u] = a;
+    x[2 * u + 1] = b;
   }
-#pragma unroll
-  for (int m = 1; m < 64; m <<= 1) {
-    const bool upper = (lane & m) != 0;
-    float o0[NV], o1[NV];
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      o0[u] = __shfl_xor(x0[u], m, 64);
-      o1[u] = __shfl_xor(x1[u], m, 64);
-    }
-#pragma unroll
-    for (int u = 0; u < NV; ++u) {
-      x0[u] = upper ? (o0[u] - x0[u]) : (x0[u] + o0[u]);
-      x1[u] = upper ? (o1[u] - x1[u]) : (x1[u] + o1[u]);
-    }
-  }
+  lane_butterflies<2 * NV>(x, lane);  // element stride h = 2, 4, ..., 64 is lane stride h / 2
   const float c = 0x1.6a09e6p-4f;  // fl32(1/sqrt(128))
 #pragma unroll
-  for (int u = 0; u < NV; ++u) {
-    x0[u] = x0[u] * c;
-    x1[u] = x1[u] * c;
-    asm volatile("" : "+v"(x0[u]), "+v"(x1[u]));  // keep the binary32 rounding apart from the conversion to fp16
+  for (int u = 0; u < 2 * NV; ++u) {
+    x[u] = x[u] * c;
+    // The contract rounds the product to binary32 first and to fp16 afterwards.  Keep the two roundings apart: a
+    // fused multiply-and-convert instruction would round the exact product once and differ in rare near-tie cases.
+    asm volatile("" : "+v"(x[u]));
   }
 }
 
@@ -127,9 +91,9 @@ __device__ inline bool scan_flag(const kvlinc_cache& c, int b) {
 __device__ inline bool store_window_row(half_t* __restrict__ k_win, half_t* __restrict__ v_win, int slot, uint32_t kk,
                                         uint32_t vv, int lane) {
   const half2_t v2 = as_h2(vv);
-  float x0 = (float)v2[0], x1 = (float)v2[1];
-  fwht128_wave(x0, x1, lane);
-  const half_t r0 = (half_t)x0, r1 = (half_t)x1;
+  float x[2] = {(float)v2[0], (float)v2[1]};
+  fwht128_wave<1>(x, lane);
+  const half_t r0 = (half_t)x[0], r1 = (half_t)x[1];
   const bool mine = nonfinite_pair(kk) || nonfinite_bits(r0) || nonfinite_bits(r1);
   if (__builtin_amdgcn_ballot_w64(mine) != 0) return true;
   *reinterpret_cast<uint32_t*>(k_win + (long long)slot * kHeadDim + 2 * lane) = kk;
@@ -206,16 +170,16 @@ __device__ inline bool new_rows_bad(const NewRows<N>& r, int lane) {
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) small &= mag[u0 + u] < 741000.0f;
     if (small) continue;
-    float x0[kBatch], x1[kBatch];
+    float x[2 * kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const half2_t h = as_h2(r.v[u0 + u]);
-      x0[u] = (float)h[0];
-      x1[u] = (float)h[1];
+      x[2 * u] = (float)h[0];
+      x[2 * u + 1] = (float)h[1];
     }
-    fwht128_wave_multi<kBatch>(x0, x1, lane);
+    fwht128_wave<kBatch>(x, lane);
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) refuse |= nonfinite_bits((half_t)x0[u]) || nonfinite_bits((half_t)x1[u]);
+    for (int u = 0; u < 2 * kBatch; ++u) refuse |= nonfinite_bits((half_t)x[u]);
   }
   return refuse;
 }

@@ -57,6 +57,9 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void st_coherent(float* p, float v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+__device__ __forceinline__ void st_coherent2(float* p, float x, float y) {  // two neighbours, 8-byte aligned
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), __builtin_bit_cast(unsigned long long, float2_t{x, y}), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 __device__ __forceinline__ float2 ld_coherent2(const float* p) {  // two neighbours, 8-byte aligned
   const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return __builtin_bit_cast(float2, v);
@@ -700,15 +703,18 @@ __device__ __forceinline__ long long state_tile(int r64, int hh, int fs) { retur
 __device__ __forceinline__ float quadgroup_allmax(float v) {
   v = fmaxf(v, dpp_f<kRowRor4>(v));
   v = fmaxf(v, dpp_f<kRowRor8>(v));
-  const auto a = __builtin_amdgcn_permlane16_swap(as_bits(v), as_bits(v), false, false);
-  v = fmaxf(as_f32(a[0]), as_f32(a[1]));
-  const auto b = __builtin_amdgcn_permlane32_swap(as_bits(v), as_bits(v), false, false);
-  return fmaxf(as_f32(b[0]), as_f32(b[1]));
+  float x, y;
+  pair_across<16>(v, x, y);
+  pair_across<32>(fmaxf(x, y), x, y);
+  return fmaxf(x, y);
 }
 __device__ __forceinline__ float quadgroup_allsum(float v) {
   v += dpp_f<kRowRor4>(v);
   v += dpp_f<kRowRor8>(v);
-  return xrow_allsum(v);
+  float x, y;
+  pair_across<16>(v, x, y);
+  pair_across<32>(x + y, x, y);
+  return x + y;
 }
 
 // Phase 1 for one head: channels 32 kk .. + 31 for the KS steps kk from k0 on.  logits: [sequence][..][kPartFeat], `stride` floats
@@ -975,15 +981,9 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ p0, const fl
   }
   // y = y_rot H^T: butterflies over the 128 channels, two per lane (bit 1 of the channel is bit 5 of the lane)
   {
-    const float a = y0 + y1, bb = y0 - y1;
-    y0 = a; y1 = bb;
-#pragma unroll
-    for (int mk = 1; mk < 64; mk <<= 1) {
-      const float o0 = __shfl_xor(y0, mk, 64), o1 = __shfl_xor(y1, mk, 64);
-      const bool upper = (lane & mk) != 0;
-      y0 = upper ? (o0 - y0) : (y0 + o0);
-      y1 = upper ? (o1 - y1) : (y1 + o1);
-    }
+    float y[2] = {y0 + y1, y0 - y1};
+    lane_butterflies<2>(y, lane);
+    y0 = y[0]; y1 = y[1];
   }
   const half2_t r = {(half_t)(y0 * 0.08838834764831845f), (half_t)(y1 * 0.08838834764831845f)};
   *reinterpret_cast<uint32_t*>(out + (long long)row * kHeadDim + ch0) = as_u32(r);
@@ -1313,33 +1313,35 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   }
   __syncthreads();
   const bool direct = sDirect != 0;
+  // (a wave takes whole heads, a lane two channels: the weights of the four waves are formed once a head)
   float* own = reinterpret_cast<float*>(&ex[0][0]);  // [gq][kPartStride]: the exchange regions are free by now
-  for (int i = tid; i < gq * kHeadDim; i += kThreads) {
-    const int h = i >> 7, ch = i & 127;
+  for (int h = wave; h < gq; h += kWaves) {
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sM[w][h]);
-    float a = 0.f, l = 0.f;
+    float a0 = 0.f, a1 = 0.f, l = 0.f;
     if (M != -INFINITY) {
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
-        const float f = exp2f(sM[w][h] - M);  // 0 for a wave without tokens
-        a = fmaf(f, sAcc[w][h][ch], a);
+        const float f = __builtin_amdgcn_exp2f(sM[w][h] - M);  // 0 for a wave without tokens
+        const float2 x = *reinterpret_cast<const float2*>(&sAcc[w][h][2 * lane]);
+        a0 = fmaf(f, x.x, a0);
+        a1 = fmaf(f, x.y, a1);
         l = fmaf(f, sL[w][h], l);
       }
     }
     if (direct) {
       float* dst = own + h * kPartStride;
-      if (ch == 0) { dst[0] = M; dst[1] = l; }
-      dst[4 + ch] = a;
+      if (lane == 0) { dst[0] = M; dst[1] = l; }
+      *reinterpret_cast<float2*>(dst + 4 + 2 * lane) = make_float2(a0, a1);
     } else {
       float* dst = part + (((long long)b * c.H_q + g * gq + h) * max_splits + sp) * kPartStride;
-      if (ch == 0) { st_coherent(dst, M); st_coherent(dst + 1, l); }
-      st_coherent(dst + 4 + ch, a);
+      if (lane == 0) st_coherent2(dst, M, l);
+      st_coherent2(dst + 4 + 2 * lane, a0, a1);
     }
   }
   if (direct) {
-    __syncthreads();
+    lds_order();  // (a wave merges the heads that it has combined)
     for (int h = wave; h < gq; h += kWaves)
       merge_row<1, true>(own + h * kPartStride, corr, 1, b * c.H_q + g * gq + h, lane,
                          (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);

@@ -22,7 +22,6 @@ typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kRowH = 136;         // halfs per LDS row of a 128-wide fp16 tile (rows stay 16-byte aligned)
 constexpr int kPlaneWords = 1024;  // a 128 x 128 tile of 2-bit codes; 4-bit codes take two such planes per tile
-constexpr int kRowHalfMirror = 0x141;
 
 __device__ __forceinline__ bool nonfinite_pair(uint32_t w) { return ((w & 0x7C00u) == 0x7C00u) || ((w & 0x7C000000u) == 0x7C000000u); }
 
