@@ -545,40 +545,31 @@ __device__ __forceinline__ uint32_t code_bits_mask() {
 }
 __device__ __forceinline__ uint32_t fp4_codes(uint32_t w, uint32_t pick) { return 0x11111111u ^ (pick & (w ^ 0x11111111u)); }
 
-// h - x and x - h in binary32 for the lower (upper) binary16 number h of a register, one instruction each
-__device__ __forceinline__ float lower_minus(uint32_t h, float x) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-  return r;
+// 1.0f in a scalar register, opaque to constant folding: a fused multiply-add with it keeps the form that takes a binary16 operand
+// as it is (v_fma_mix), where a plain subtraction would convert it first.  (As inline assembly the same instructions came with
+// 75 idle ones a group, which the compiler puts between an assembly statement and the use of its result.)
+__device__ __forceinline__ float opaque_one() {
+  float one = 1.0f;
+  asm("" : "+s"(one));
+  return one;
 }
-__device__ __forceinline__ float upper_minus(uint32_t h, float x) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-  return r;
+typedef float float2_t __attribute__((ext_vector_type(2)));
+// x0, x1 as two binary16 terms each, high terms in h, what they leave in l (the differences are exact).  (The conversion is
+// of both numbers at once: one by one they would be fused into the operations that x0 and x1 come from, which rounds
+// another number, and the low terms would belong to other high terms in rare near-tie cases.)
+__device__ __forceinline__ void two_terms(float x0, float x1, float one, uint32_t& h, uint32_t& l) {
+  const half2_t t = __builtin_convertvector((float2_t{x0, x1}), half2_t);
+  h = as_u32(t);
+  l = as_u32(half2_t{(half_t)__builtin_fmaf(-(float)t[0], one, x0), (half_t)__builtin_fmaf(-(float)t[1], one, x1)});
 }
-__device__ __forceinline__ float minus_lower(float x, uint32_t h) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-  return r;
-}
-__device__ __forceinline__ float minus_upper(float x, uint32_t h) {
-  float r;
-  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(h), "v"(x));
-  return r;
-}
-// x0, x1 as two binary16 terms each, high terms in h, what they leave in l (the differences are exact).  The operands are
-// made opaque: the terms belong to the rounded binary32 values, not to the expressions they come from (a fused
-// multiply-and-convert would round the exact product once, and the low term would then belong to another high term in rare
-// near-tie cases).
-__device__ __forceinline__ void two_terms(float x0, float x1, uint32_t& h, uint32_t& l) {
-  asm("" : "+v"(x0), "+v"(x1));
-  h = as_u32(half2_t{(half_t)x0, (half_t)x1});
-  asm("" : "+v"(h));
-  l = as_u32(half2_t{(half_t)minus_lower(x0, h), (half_t)minus_upper(x1, h)});
+// The same of the products a0 b0, a1 b1: the low terms are what the high ones leave of the exact products.
+__device__ __forceinline__ void two_terms_of_products(float a0, float b0, float a1, float b1, uint32_t& h, uint32_t& l) {
+  const half2_t t = __builtin_convertvector((float2_t{a0 * b0, a1 * b1}), half2_t);
+  h = as_u32(t);
+  l = as_u32(half2_t{(half_t)__builtin_fmaf(a0, b0, -(float)t[0]), (half_t)__builtin_fmaf(a1, b1, -(float)t[1])});
 }
 template <int BYTE>
 __device__ __forceinline__ half2_t fp4_to_h2(uint32_t w, float scale) { return __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, scale, BYTE); }
-typedef float float2_t __attribute__((ext_vector_type(2)));
 
 // Key scales s and mid-points z + ctr s of a group in binary32, channel by channel: formed once per group by 64 threads from
 // the record's scales and zero-points, two channels each.
@@ -598,45 +589,76 @@ __device__ __forceinline__ void store_key_affine(KeyAffine& a, uint32_t scales, 
 template <int BITS>
 __device__ __forceinline__ void state_logits(const KeyError<BITS>& e, const KeyAffine& ka, const StateLds& L, uint32_t pick, int lane, float4_t (&d)[8]) {
   const int l16 = lane & 15, kq = lane >> 4;
+  const float one = opaque_one();
   float4_t lo[8];
 #pragma unroll
   for (int ft = 0; ft < 8; ++ft) d[ft] = lo[ft] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint32_t k2[4] = {e.k[kk].x, e.k[kk].y, e.k[kk].z, e.k[kk].w};
-    float2_t cc[4];
-    {
-      const uint32_t w = fp4_codes(e.code[0][kk] << (kq & 1), pick);
-      constexpr float kStep = BITS == 2 ? 1.0f : 4.0f;
-      cc[0] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, kStep, 0);
-      cc[1] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, kStep, 1);
-      cc[2] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, kStep, 2);
-      cc[3] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, kStep, 3);
+  // The key error of a step is formed between the products of the one before, and W_k is read two tiles ahead: laid out by hand, in
+  // pieces that the compiler may not mix, because it puts every pair of products behind the read of its operand otherwise.  (16
+  // prompts of 8192 tokens 540 -> 521 us, 32 ragged ones at 4 bits in three calls 403 -> 388, one of 700 tokens 61.6 -> 59.5, the
+  // rest of the calls included.  Not for the update, whose operands a step ahead took 3 % longer; and the softmax of a group laid
+  // between the products of the next, at 100 more lines, was no faster: beside a matrix instruction the vector unit issues at half
+  // its rate.)
+  uint32_t op[2][8];  // high terms, low terms
+  float4_t s4, m4;
+  auto read_affine = [&](int kk, int half) __attribute__((always_inline)) {
+    s4 = *reinterpret_cast<const float4_t*>(&ka.s[32 * kk + 8 * kq + 4 * half]);
+    m4 = *reinterpret_cast<const float4_t*>(&ka.mid[32 * kk + 8 * kq + 4 * half]);
+  };
+  auto key_error = [&](int kk, int half) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(s4));
+    const uint32_t w2 = fp4_codes(e.code[0][kk] << (kq & 1), pick);
+    constexpr float kStep = BITS == 2 ? 1.0f : 4.0f;
+    float2_t c0, c1;
+    if (half == 0) {
+      c0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w2, kStep, 0);
+      c1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w2, kStep, 1);
+    } else {
+      c0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w2, kStep, 2);
+      c1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w2, kStep, 3);
     }
     if constexpr (BITS == 4) {  // code - 7.5 = 4 (high digit - 1.5) + (low digit - 1.5)
-      const uint32_t w = fp4_codes(e.code[1][kk] << (kq & 1), pick);
-      const float2_t a0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 0), a1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 1);
-      const float2_t a2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 2), a3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(w, 1.0f, 3);
-      cc[0][0] += a0[0]; cc[0][1] += a0[1]; cc[1][0] += a1[0]; cc[1][1] += a1[1];
-      cc[2][0] += a2[0]; cc[2][1] += a2[1]; cc[3][0] += a3[0]; cc[3][1] += a3[1];
+      const uint32_t wl = fp4_codes(e.code[1][kk] << (kq & 1), pick);
+      float2_t a0, a1;
+      if (half == 0) {
+        a0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wl, 1.0f, 0);
+        a1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wl, 1.0f, 1);
+      } else {
+        a0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wl, 1.0f, 2);
+        a1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(wl, 1.0f, 3);
+      }
+      c0[0] += a0[0]; c0[1] += a0[1]; c1[0] += a1[0]; c1[1] += a1[1];
     }
-    uint32_t eh[4], el[4];
+    const half2_t ka2 = as_h2(half == 0 ? e.k[kk].x : e.k[kk].z), kb2 = as_h2(half == 0 ? e.k[kk].y : e.k[kk].w);
+    // K - (z + s code), the difference to the mid-point first
+    two_terms(__builtin_fmaf(-s4.x, c0[0], __builtin_fmaf((float)ka2[0], one, -m4.x)),
+              __builtin_fmaf(-s4.y, c0[1], __builtin_fmaf((float)ka2[1], one, -m4.y)), one, op[kk & 1][2 * half], op[kk & 1][4 + 2 * half]);
+    two_terms(__builtin_fmaf(-s4.z, c1[0], __builtin_fmaf((float)kb2[0], one, -m4.z)),
+              __builtin_fmaf(-s4.w, c1[1], __builtin_fmaf((float)kb2[1], one, -m4.w)), one, op[kk & 1][2 * half + 1], op[kk & 1][4 + 2 * half + 1]);
+  };
+  half8_t w[3];
+  auto weights = [&](int i) { return *reinterpret_cast<const half8_t*>(&L.Wt[16 * (i & 7) + l16][32 * (i >> 3) + 8 * kq]); };
+  w[0] = weights(0);
+  w[1] = weights(1);
+  read_affine(0, 0);
+  key_error(0, 0);
+  read_affine(0, 1);
+  key_error(0, 1);
 #pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-      const float4 s4 = *reinterpret_cast<const float4*>(&ka.s[32 * kk + 8 * kq + 2 * i]);
-      const float4 m4 = *reinterpret_cast<const float4*>(&ka.mid[32 * kk + 8 * kq + 2 * i]);
-      // K - (z + s code), the difference to the mid-point first
-      two_terms(__builtin_fmaf(-s4.x, cc[i][0], lower_minus(k2[i], m4.x)), __builtin_fmaf(-s4.y, cc[i][1], upper_minus(k2[i], m4.y)), eh[i], el[i]);
-      two_terms(__builtin_fmaf(-s4.z, cc[i + 1][0], lower_minus(k2[i + 1], m4.z)), __builtin_fmaf(-s4.w, cc[i + 1][1], upper_minus(k2[i + 1], m4.w)), eh[i + 1], el[i + 1]);
+  for (int i = 0; i < 32; ++i) {
+    const int kk = i >> 3, ft = i & 7;
+    if (i + 2 < 32) w[(i + 2) % 3] = weights(i + 2);
+    asm volatile("" : "+v"(w[i % 3]));
+    const uint32_t* o = op[kk & 1];
+    const half8_t ah = __builtin_bit_cast(half8_t, make_uint4(o[0], o[1], o[2], o[3]));
+    const half8_t al = __builtin_bit_cast(half8_t, make_uint4(o[4], o[5], o[6], o[7]));
+    lo[ft] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, w[i % 3], lo[ft], 0, 0, 0);
+    d[ft] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, w[i % 3], d[ft], 0, 0, 0);
+    if (kk < 3) {
+      if (ft == 1 || ft == 4) read_affine(kk + 1, ft == 4 ? 1 : 0);
+      if (ft == 3 || ft == 6) key_error(kk + 1, ft == 6 ? 1 : 0);
     }
-    const half8_t ah = __builtin_bit_cast(half8_t, make_uint4(eh[0], eh[1], eh[2], eh[3]));
-    const half8_t al = __builtin_bit_cast(half8_t, make_uint4(el[0], el[1], el[2], el[3]));
-#pragma unroll
-    for (int ft = 0; ft < 8; ++ft) {
-      const half8_t w = *reinterpret_cast<const half8_t*>(&L.Wt[16 * ft + l16][32 * kk + 8 * kq]);
-      lo[ft] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al, w, lo[ft], 0, 0, 0);
-      d[ft] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah, w, d[ft], 0, 0, 0);
-    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 #pragma unroll
   for (int ft = 0; ft < 8; ++ft) d[ft] += lo[ft];
@@ -669,9 +691,17 @@ __device__ __forceinline__ float rows_sum(float v) {  // over the lanes l, l ^ 1
 // A power of two F with max_t s_t F in [2^13, 2^14): phi s_t F then fills binary16's range from the top, and the two binary16
 // terms it is carried in leave 2^-38 of the largest entry (rather than 2^-25 of one).
 __device__ __forceinline__ float scale_factor(const ValueScales& sz, float& inv) {
-  const float m = wave_allmax(fmaxf((float)as_h2(sz.all.x)[0], (float)as_h2(sz.all.y)[0]));
-  const int e = (int)(__builtin_bit_cast(uint32_t, m) >> 23);  // biased
-  const int k = m > 0.0f ? 13 - (e - 127) : 0;
+  uint32_t m = max(sz.all.x & 0xffffu, sz.all.y & 0xffffu);  // (scales are not negative: their bit patterns order like they do)
+  m = max(m, dpp_u<kRowRor1>(m));
+  m = max(m, dpp_u<kRowRor2>(m));
+  m = max(m, dpp_u<kRowRor4>(m));
+  m = max(m, dpp_u<kRowRor8>(m));
+  const auto a = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+  m = max(a[0], a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  const float top = (float)__builtin_bit_cast(half_t, (unsigned short)max(b[0], b[1]));
+  const int e = (int)(__builtin_bit_cast(uint32_t, top) >> 23);  // biased
+  const int k = top > 0.0f ? 13 - (e - 127) : 0;
   inv = __builtin_bit_cast(float, (uint32_t)(127 - k) << 23);
   return __builtin_bit_cast(float, (uint32_t)(127 + k) << 23);
 }
@@ -717,8 +747,8 @@ __device__ __forceinline__ void state_softmax(float4_t (&d)[8], const ValueScale
       st.P[fo] = __builtin_fmaf(e[r], inv[r], st.P[fo]);
       st.Z[fo] = __builtin_fmaf(e[r], wz[r], st.Z[fo]);
     }
-    two_terms(e[0] * ws[0], e[1] * ws[1], h4.x, l4.x);
-    two_terms(e[2] * ws[2], e[3] * ws[3], h4.y, l4.y);
+    two_terms_of_products(e[0], ws[0], e[1], ws[1], h4.x, l4.x);
+    two_terms_of_products(e[2], ws[2], e[3], ws[3], h4.y, l4.y);
     *reinterpret_cast<uint2*>(&L.ph[0][16 * fo + l16][8 * jj + 4 * (wave & 1)]) = h4;
     *reinterpret_cast<uint2*>(&L.ph[1][16 * fo + l16][8 * jj + 4 * (wave & 1)]) = l4;
   }
