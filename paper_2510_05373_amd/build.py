@@ -12,6 +12,8 @@ PROBE_PATH = os.path.join(HERE, "libkvlinc_probe.so")
 COMMON = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first 14 words of a kernel's arguments come with the launch, in scalar registers
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 # per-file extras: the append path holds the bit-exact contracts, no contraction of a*b+c there

@@ -1276,10 +1276,16 @@ __device__ void flush_item(const kvlinc_cache& c, TokenLds<BITS>& L, int item, i
 
 // Items as in append_states_kernel, without chunks.
 // ROWS: 1, or kFewRows for an append of 2 .. kFewRows rows (a kernel of its own, so that the generation step carries none of it).
+// What the way to the counters and to the new rows takes stands first among the arguments, ahead of the cache that holds it too:
+// the first 14 words are in scalar registers when a wave starts (kernarg preload, see build.py), the others a trip to memory away.
+// (Here and in the decode kernel: a step of 1 sequence of 300 tokens 12.1 -> 11.75 us, 16 of 8k 25.2 -> 25.05, 144 of 1280 73.5 ->
+// 73.0.)
 template <bool SLIDING, int BITS, int ROWS>
-__global__ __launch_bounds__(kThreads) void append_token_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
-                                                                 const half_t* __restrict__ v_new,
-                                                                 const int32_t* __restrict__ n_new, int rows_T) {
+__global__ __launch_bounds__(kThreads) void append_token_kernel(int32_t* n_quant, int32_t* n_res, const half_t* __restrict__ k_new,
+                                                                 const half_t* __restrict__ v_new, const int32_t* __restrict__ n_new,
+                                                                 int B, int H_kv, int R, int rows_T, kvlinc_cache cache) {
+  kvlinc_cache c = cache;
+  c.n_quant = n_quant; c.n_res = n_res; c.B = B; c.H_kv = H_kv; c.R = R;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   TokenLds<BITS>& L = *reinterpret_cast<TokenLds<BITS>*>(lds_raw);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1397,7 +1403,7 @@ int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_
     // one workgroup per compute unit at most (the LDS of a flush fills most of one); items beyond that are taken
     // in further rounds by the same workgroups
     const int grid = (int)(n_items < 256 ? n_items : 256);
-    typedef void (*kernel_t)(kvlinc_cache, const half_t*, const half_t*, const int32_t*, int);
+    typedef void (*kernel_t)(int32_t*, int32_t*, const half_t*, const half_t*, const int32_t*, int, int, int, int, kvlinc_cache);
     const kernel_t one = c.bits == 4 ? (sliding ? append_token_kernel<true, 4, 1> : append_token_kernel<false, 4, 1>)
                                      : (sliding ? append_token_kernel<true, 2, 1> : append_token_kernel<false, 2, 1>);
     const kernel_t few = c.bits == 4 ? (sliding ? append_token_kernel<true, 4, kFewRows> : append_token_kernel<false, 4, kFewRows>)
@@ -1405,7 +1411,7 @@ int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_
     const kernel_t kernel = T == 1 ? one : few;
     const size_t lds = c.bits == 4 ? sizeof(TokenLds<4>) : sizeof(TokenLds<2>);
     if (launch_with_lds(kernel, lds) != KVLINC_OK) return KVLINC_EHIP;
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, c, kk, vv, n_new, T);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, stream, c.n_quant, c.n_res, kk, vv, n_new, c.B, c.H_kv, c.R, T, c);
     return hipGetLastError() == hipSuccess ? KVLINC_OK : KVLINC_EHIP;
   }
   const long long groups_most = ((long long)T + c.R + kGroup - 1) / kGroup;

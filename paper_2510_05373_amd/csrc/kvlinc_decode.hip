@@ -1054,11 +1054,14 @@ __device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
 // default one carries none of its code.
 // BITS: so is the one for caches with 4-bit codes (it holds twice the tile words in registers).
 // FEW_HEADS: and the one for fewer than 4 query heads per kv head (see correction_workgroup).
+// (The arguments up to H_kv are in scalar registers when a wave starts, see append_token_kernel.)
 template <int NB, bool SLIDING = false, int BITS = 2, bool FEW_HEADS = false>
-__global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(kvlinc_cache c, const half_t* __restrict__ q,
-                                                                   float* __restrict__ part, float* __restrict__ corr,
-                                                                   half_t* __restrict__ out, int max_splits,
-                                                                   int avg_splits, int gq, int corr_first, int corr_seqs) {
+__global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(uint32_t* groups, int32_t* n_quant, int64_t max_groups,
+                                                                   float* __restrict__ corr, int B, int max_splits, int avg_splits,
+                                                                   int corr_first, int corr_seqs, int H_kv, int gq, kvlinc_cache cache,
+                                                                   const half_t* __restrict__ q, float* __restrict__ part, half_t* __restrict__ out) {
+  kvlinc_cache c = cache;
+  c.groups = groups; c.n_quant = n_quant; c.max_groups = max_groups; c.B = B; c.H_kv = H_kv;
   constexpr int kCombine = 2 * kWaves * NB * 4 + kWaves * NB * 4 * kHeadDim;
   __shared__ __align__(16) float lds[kCombine + kWaves * 2 * kExWords];
   static_assert(kCombine + kWaves * 2 * kExWords >= kMaxCorrSeqs * NB * 4 * kPartFeat, "the logits of a correction workgroup");
@@ -1437,7 +1440,7 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   const dim3 grid(BH * n_splits + n_corr), block(kThreads);
   const int corr_first = sp.corr_first;
   const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
-  void (*kernel)(kvlinc_cache, const half_t*, float*, float*, half_t*, int, int, int, int, int) =
+  void (*kernel)(uint32_t*, int32_t*, int64_t, float*, int, int, int, int, int, int, int, kvlinc_cache, const half_t*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)
                               : (sliding ? decode_main_kernel<1, true, 4> : decode_main_kernel<1, false, 4>))
@@ -1445,9 +1448,11 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 2, true> : decode_main_kernel<1, false, 2, true>)
                               : (sliding ? decode_main_kernel<1, true> : decode_main_kernel<1, false>));
   if (start != nullptr)  // timestamps of the dispatch itself, no extra packets on the stream
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first, sp.corr_seqs);
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c.groups, c.n_quant, c.max_groups, corr, c.B, sp.most, sp.avg,
+                          corr_first, sp.corr_seqs, c.H_kv, gq, c, qq, part, oo);
   else
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c, qq, part, corr, oo, sp.most, sp.avg, gq, corr_first, sp.corr_seqs);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c.groups, c.n_quant, c.max_groups, corr, c.B, sp.most, sp.avg, corr_first, sp.corr_seqs,
+                       c.H_kv, gq, c, qq, part, oo);
   return hipGetLastError() == hipSuccess ? KVLINC_OK : KVLINC_EHIP;
 }
 
