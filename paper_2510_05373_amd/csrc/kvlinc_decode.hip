@@ -1006,11 +1006,25 @@ __device__ __forceinline__ void merge_rows(const float* __restrict__ part, const
 // arithmetic only: every wave of the launch that needs the number gets the same one from the same counters.
 __device__ __forceinline__ int groups_of(int nq) { return (nq + kGroup - 1) / kGroup; }
 
-// Groups of the whole batch, in every lane.  `head`: this lane's share of the first 64 sequences, n_quant[lane] requested
-// ahead by the caller (0 beyond the batch).
-__device__ __forceinline__ int batch_groups(const kvlinc_cache& c, int head, int lane) {
-  uint32_t total = groups_of(head);
-  for (int i = lane + 64; i < c.B; i += 64) total += groups_of(c.n_quant[i]);
+// n_quant of the sequences lane, lane + 64, ... of the first 64 kCounterRows, all requested at once and ahead of the first record
+// (a batch beyond 64 sequences was a further trip to memory for every 64, in the workgroups that stream and in those of the
+// correction: a step of 144 sequences of 1280 tokens 73.0 -> 70.5 us, 64 of 1k to 16k 85.3 -> 84.8).
+constexpr int kCounterRows = 4;
+struct BatchCounters {
+  int n[kCounterRows];
+};
+__device__ __forceinline__ BatchCounters request_counters(const kvlinc_cache& c, int lane) {
+  BatchCounters r;
+#pragma unroll
+  for (int u = 0; u < kCounterRows; ++u) r.n[u] = c.n_quant[min(lane + 64 * u, c.B - 1)];
+  return r;
+}
+// Groups of the whole batch, in every lane.
+__device__ __forceinline__ int batch_groups(const kvlinc_cache& c, const BatchCounters& r, int lane) {
+  uint32_t total = 0;
+#pragma unroll
+  for (int u = 0; u < kCounterRows; ++u) total += lane + 64 * u < c.B ? groups_of(r.n[u]) : 0;
+  for (int i = lane + 64 * kCounterRows; i < c.B; i += 64) total += groups_of(c.n_quant[i]);
   total += dpp_u<kRowRor1>(total);
   total += dpp_u<kRowRor2>(total);
   total += dpp_u<kRowRor4>(total);
@@ -1111,10 +1125,10 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     // A sequence without quantized tokens has S = P = 0 (the states only change at a flush), so its parts come out
     // as zero without looking at n_quant.
     // (the counters are requested first and looked at last: by then they have long arrived)
-    const int nq_head = lane < c.B ? c.n_quant[lane] : 0;
+    const BatchCounters counters = request_counters(c, lane);
     const int nq_mine = c.n_quant[b_first + min(lane, n_seq - 1)];
     correction_workgroup<FEW_HEADS, NB>(c, q, corr, gq, g, r, b_first, n_seq, lane, wave, lds);
-    const int total = batch_groups(c, nq_head, lane);
+    const int total = batch_groups(c, counters, lane);
     // count this workgroup in at each of its sequences; merge those it completes
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -1181,6 +1195,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   const Roles lr = make_roles(lane, ex[wave]);
   KeyRegs<BITS> kr;
   ValueRegs<BITS> vr;
+  const BatchCounters counters = request_counters(c, lane);
   if (sp < avg_splits) {
     const long long first = idx < c.max_groups ? idx : c.max_groups - 1;
     load_keys(kr, rec0 + first * kRecordWords, lr);
@@ -1191,7 +1206,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   const int count = groups_of(nq);
   {
     int total = 0;
-    if (c.B > 1) total = batch_groups(c, lane < c.B ? c.n_quant[lane] : 0, lane);
+    if (c.B > 1) total = batch_groups(c, counters, lane);
     const int mine = sequence_splits(c, count, total, avg_splits, max_splits, lane);
     if (sp >= mine) return;  // this sequence uses fewer splits than the grid provides
     if (mine != n_splits) {  // lengths differ within the batch: plan again, request the right first record
