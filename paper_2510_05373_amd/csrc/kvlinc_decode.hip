@@ -1419,13 +1419,18 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   const long long all_corr = c.S16 != nullptr ? corr_workgroups(corr_seqs) : 0;
   // (More than 4 heads per kv head: the correction takes the third place of a compute unit, and going last it does not
   // hold up the streaming workgroups.  Launches of 5 to 8 heads, 1 to 8 kv heads, 8 to 64 sequences of 8k to 64k tokens, last
-  // against first: at 2 bits 0.92 to 1.00 of the time, at 4 bits 0.98 to 1.02.)
-  int corr_first = ((gq > 4 || 2 * all_corr > 768) && groups >= 16 * kWaves * s) ? 0 : 1;
-  // One or a few long sequences: about one streaming workgroup per compute unit.  The streaming workgroups that
-  // would share a compute unit with a correction workgroup finish late (measured 3.6 us at a context of 128k), so
-  // the correction workgroups pair up on compute units of their own (two runs of the grid lead with them) and the
-  // splits are cut back to leave those compute units free.
+  // against first: at 2 bits, from 8 groups per wave on, 0.86 to 1.01 of the time, with 4 and fewer 0.86 to 1.48; at 4 bits, from
+  // 16 on, 0.98 to 1.02.)
+  const int long_wave = gq > 4 && c.bits == 2 ? 8 : 16;
+  int corr_first = ((gq > 4 || 2 * all_corr > 768) && groups >= long_wave * kWaves * s) ? 0 : 1;
+  // One or a few long sequences: about one streaming workgroup per compute unit.  They go first then, and the correction shares
+  // the compute units it finds: against 2 / 30 of the splits less and compute units of its own, as below, 0.72 to 1.00 of the time
+  // over 1 to 32 sequences of 1800 to 131072 tokens, equal and unequal, 1 to 8 heads (one sequence of 131072 tokens, 8 kv heads:
+  // 20.5 -> 19.9 us a launch).  At 4 bits a compute unit holds two workgroups, not three, and the streaming workgroups that would
+  // share one with a correction workgroup finish late (1.00 to 1.12): the correction workgroups pair up on compute units of their
+  // own (two runs of the grid lead with them) and the splits are cut back to leave those compute units free.
   if (all_corr > 0 && bh * s <= 256 && bh * s + all_corr > 256) {
+    if (c.bits == 2) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
     const long long s2 = (256 - (all_corr + 1) / 2) / bh;
     if (s2 >= 1 && 4 * s2 >= 3 * s) {
       s = s2 < s ? s2 : s;
