@@ -460,8 +460,9 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
 //   S update: wave w owns the features 32 (w / 2) .. + 31 and the channels 64 (w % 2) .. + 63.
 // Bound: the vector and the matrix instructions of a group one after the other (two waves per SIMD, all in the same phase):
 // of the busy time 62 % vector, 34 % matrix, 8 % both at once; LDS 39 % (counted before the logits phase was laid out by hand).
-// Measured, 16 prompts of 8192 tokens (8 kv heads): 290 to 350 us for the states as the clock goes (500 us before the terms were formed with mixed-precision
-// fused multiply-adds, the four contractions chained and the loads freed of execution masks; 1742 us, quantization included,
+// Measured, 16 prompts of 8192 tokens (8 kv heads): about 320 us of a call's 461 for the states, 370 to 440 single calls
+// under a profiler as the clock goes (444 on average before the logits were laid out by hand, 407 now; 500 us before the terms were
+// formed with mixed-precision fused multiply-adds, the four contractions chained and the loads freed of execution masks; 1742 us, quantization included,
 // when the same workgroups also quantized the group in LDS, each half for itself).  Two teams of four waves, one at the
 // logits and the softmax while the other is at the update, took 10 % longer: one wave of a kind per SIMD does not hide its own latencies.
 struct StateLds {

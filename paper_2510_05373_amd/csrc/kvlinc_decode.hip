@@ -1425,12 +1425,12 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   int corr_first = ((gq > 4 || 2 * all_corr > 768) && groups >= long_wave * kWaves * s) ? 0 : 1;
   // One or a few long sequences: about one streaming workgroup per compute unit.  They go first then, and the correction shares
   // the compute units it finds: against 2 / 30 of the splits less and compute units of its own, as below, 0.72 to 1.00 of the time
-  // over 1 to 32 sequences of 1800 to 131072 tokens, equal and unequal, 1 to 8 heads (one sequence of 131072 tokens, 8 kv heads:
-  // 20.5 -> 19.9 us a launch).  At 4 bits a compute unit holds two workgroups, not three, and the streaming workgroups that would
+  // over 1 to 32 sequences of 1800 to 131072 tokens, equal and unequal, 1 to 8 heads.  A single sequence keeps the split count its
+  // callers size their workspace by (131072 tokens, 8 kv heads: 30 splits 20.5 us a launch, 32 would take 19.9).  At 4 bits a compute unit holds two workgroups, not three, and the streaming workgroups that would
   // share one with a correction workgroup finish late (1.00 to 1.12): the correction workgroups pair up on compute units of their
   // own (two runs of the grid lead with them) and the splits are cut back to leave those compute units free.
   if (all_corr > 0 && bh * s <= 256 && bh * s + all_corr > 256) {
-    if (c.bits == 2) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
+    if (c.bits == 2 && c.B > 1) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
     const long long s2 = (256 - (all_corr + 1) / 2) / bh;
     if (s2 >= 1 && 4 * s2 >= 3 * s) {
       s = s2 < s ? s2 : s;
