@@ -459,7 +459,7 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
 //   phi in LDS: [feature][token % 16][token / 16];
 //   S update: wave w owns the features 32 (w / 2) .. + 31 and the channels 64 (w % 2) .. + 63.
 // Bound: the vector and the matrix instructions of a group one after the other (two waves per SIMD, all in the same phase):
-// of the busy time 62 % vector, 34 % matrix, 8 % both at once; LDS 39 % (counted before the logits phase was laid out by hand).
+// of the busy time 67 % vector, 37 % matrix, 10 % both at once; LDS 42 %.
 // Measured, 16 prompts of 8192 tokens (8 kv heads): about 320 us of a call's 461 for the states, 370 to 440 single calls
 // under a profiler as the clock goes (444 on average before the logits were laid out by hand, 407 now; 500 us before the terms were
 // formed with mixed-precision fused multiply-adds, the four contractions chained and the loads freed of execution masks; 1742 us, quantization included,
