@@ -1435,6 +1435,7 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
     if (s2 >= 1 && 4 * s2 >= 3 * s) {
       s = s2 < s ? s2 : s;
       if (m > s) m = c.B > 1 ? 2 * s : s;
+      if (m > kMaxSplits) m = kMaxSplits;
       if (m > most) m = most;
       if (m < s) m = s;
       corr_first = 2;
