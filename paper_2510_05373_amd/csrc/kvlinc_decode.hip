@@ -1423,16 +1423,27 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // 16 on, 0.98 to 1.02.)
   const int long_wave = gq > 4 && c.bits == 2 ? 8 : 16;
   int corr_first = ((gq > 4 || 2 * all_corr > 768) && groups >= long_wave * kWaves * s) ? 0 : 1;
-  // One or a few long sequences: about one streaming workgroup per compute unit.  They go first then, and the correction shares
-  // the compute units it finds: against 2 / 30 of the splits less and compute units of its own, as below, 0.72 to 1.00 of the time
-  // over 1 to 32 sequences of 1800 to 131072 tokens, equal and unequal, 1 to 8 heads.  A single sequence keeps the split count its
-  // callers size their workspace by (131072 tokens, 8 kv heads: 30 splits 20.5 us a launch, 32 would take 19.9).  At 4 bits a compute unit holds two workgroups, not three, and the streaming workgroups that would
-  // share one with a correction workgroup finish late (1.00 to 1.12): the correction workgroups pair up on compute units of their
-  // own (two runs of the grid lead with them) and the splits are cut back to leave those compute units free.
+  // Between one and two workgroups per compute unit, the correction included.  Where the splits can be cut back by a quarter at
+  // most, the correction workgroups may pair up on compute units of their own (two runs of the grid lead with them): what 4 bits
+  // take, where a unit holds two workgroups and the streaming ones that share one with a correction workgroup finish late (1.00
+  // to 1.12 with the correction last).  At 2 bits a unit holds three: the streaming workgroups go first then, with all splits, and
+  // the correction shares the units it finds, but only
+  //   - from 2 splits on, 4 for more than 4 heads, and for 3 and 4 heads where the splits could be cut back: 0.60 to 1.48 of the
+  //     time the others take, 0.94 on average (the splits follow the context here, 512 tokens each; with 2 and 3 of them 5 to 8
+  //     heads take 0.93 to 1.74 times as long, 1.34 on average, and 3 and 4 heads, where they cannot be cut back, 0.89 to 1.58, 1.23
+  //     on average);
+  //   - with one split from 24 groups on and 2 or more heads: 0.88 to 1.09, 0.99 on average.  A single split merges what it holds
+  //     when it finds the correction done, and below that the correction is the longer chain: 0.87 to 1.45, 1.10 on average.
+  // (Decode launches of 2 to 64 sequences of 140 to 131072 tokens, equal ones and lengths spread by 0.3, 0.6 and 0.9, 1 to 8 heads,
+  // 1 to 32 kv heads: 1471 shapes, twice.)
+  // A single sequence is left on units of its own and 30 splits, the stated policy for it: 131072 tokens, 8 kv heads, 20.5 us a
+  // launch, where 32 splits with the correction last would take 19.9.
   if (all_corr > 0 && bh * s <= 256 && bh * s + all_corr > 256) {
-    if (c.bits == 2 && c.B > 1) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
     const long long s2 = (256 - (all_corr + 1) / 2) / bh;
-    if (s2 >= 1 && 4 * s2 >= 3 * s) {
+    const bool own_units = s2 >= 1 && 4 * s2 >= 3 * s;
+    const bool long_enough = s == 1 ? gq >= 2 && groups >= 24 : s >= (gq > 4 ? 4 : 2) && (own_units || gq <= 2);
+    if (c.bits == 2 && c.B > 1 && long_enough) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
+    if (own_units) {
       s = s2 < s ? s2 : s;
       if (m > s) m = c.B > 1 ? 2 * s : s;
       if (m > kMaxSplits) m = kMaxSplits;

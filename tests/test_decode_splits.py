@@ -1,4 +1,6 @@
 """Launch policy of the decode on the host: sizes and orders that the kernel's merge and its workgroups rely on.  No launch is made."""
+import ctypes
+
 import pytest
 
 from tests.test_library_abi import fake_struct, kb
@@ -24,3 +26,44 @@ def test_no_sequence_takes_more_splits_than_the_merge_holds(bits, corr):
                 for context in (1, 128, 700, 1281, 4096, 9000, 17000, 20000, 32768, 70000, 131072):
                     splits = most_splits(c, context)
                     assert 1 <= splits <= SPLITS_OF_THE_MERGE, (B, H_kv, gq, context, splits)
+
+
+class Splits(ctypes.Structure):
+    _fields_ = [("avg", ctypes.c_int), ("most", ctypes.c_int), ("corr_first", ctypes.c_int), ("corr_seqs", ctypes.c_int)]
+
+
+def splits_of(B, H_q, H_kv, context, **over):
+    """The launch policy itself: an internal function of the library, by its symbol."""
+    f = kb.lib._ZN6kvlinc13decode_splitsERK12kvlinc_cachei
+    f.restype, f.argtypes = Splits, [ctypes.POINTER(kb.CacheStruct), ctypes.c_int]
+    c = fake_struct(B=B, H_q=H_q, H_kv=H_kv, max_groups=1025, **over)
+    s = f(ctypes.byref(c), context)
+    assert s.most == most_splits(c, context)
+    return s
+
+
+@pytest.mark.parametrize("gq", range(1, 9))
+def test_the_correction_leads_short_contexts(gq):
+    """Its chain is the longest part of a launch over short contexts: it must not start behind the streaming workgroups there,
+    whatever the number of sequences and heads."""
+    for H_kv in (1, 2, 4, 8, 16, 32):
+        for B in range(2, 65):
+            for context in (1, 140, 300, 512):
+                s = splits_of(B, H_kv * gq, H_kv, context)
+                assert s.avg == 1 and s.corr_first >= 1, (B, H_kv, context)
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,context,first", [
+    (24, 32, 8, 500, 1), (32, 32, 8, 1000, 1), (32, 32, 8, 1500, 1), (32, 32, 8, 4000, 0), (16, 16, 16, 1000, 1), (8, 32, 32, 4000, 1),  # one split
+    (5, 16, 16, 1000, 0), (8, 16, 16, 1000, 0), (16, 32, 8, 1000, 1), (12, 64, 8, 1000, 2), (17, 28, 4, 1400, 2),  # two and three
+    (8, 32, 8, 1800, 0), (12, 28, 4, 2500, 0), (4, 64, 8, 4000, 0), (2, 32, 8, 8000, 0)])
+def test_order_between_one_and_two_workgroups_per_unit(B, H_q, H_kv, context, first):
+    """First (1), on compute units of its own (2) or last (0), from one, two, four splits of a sequence on."""
+    assert splits_of(B, H_q, H_kv, context).corr_first == first
+    if first == 0 and context >= 1800:  # a compute unit holds two workgroups at 4 bits: never last beside so few
+        assert splits_of(B, H_q, H_kv, context, bits=4).corr_first >= 1
+
+
+def test_a_single_sequence_leads_with_the_correction():
+    for context in (1, 300, 5000, 131072):
+        assert splits_of(1, 32, 8, context).corr_first >= 1
