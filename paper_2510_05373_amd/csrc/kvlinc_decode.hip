@@ -1395,12 +1395,21 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   const long long bh = (long long)c.B * c.H_kv;
   const int gq = c.H_q / c.H_kv;
   long long n_corr = 0;
-  // Sequences per correction workgroup: 4, one for each wave, and 8 where one query head per kv head makes the weights a small part
-  // of what a workgroup reads and workgroups of 4 sequences would not fit the chip at once (three per compute unit).  Decode
-  // launches, 8 against 4: 32 kv heads of one query head, 8 sequences 1.06 to 1.59, 32 sequences 0.94 to 0.99, 64 and 144
-  // 0.99; 2 to 8 query heads, 8 to 144 sequences of 300 to 4000 tokens 0.94 to 2.46 (mostly above 1.05).
+  // Sequences per correction workgroup: 4, one for each wave.  8 in turn (8 against 4, decode launches)
+  //   - with 1 or 2 query heads per kv head and 2 bits, where workgroups of 4 and the streaming ones do not fit the chip at once
+  //     (three per compute unit), workgroups of 8 do, and contexts are 12 to 63 groups: equal lengths 0.79 to 1.07 of the time,
+  //     0.89 on average, unequal ones 0.80 to 1.15 and 0.98 (1 to 64 kv heads, 830 shapes; with 4, the streaming workgroups that do
+  //     not fit start behind a whole correction workgroup and end a round later).
+  //     Shorter contexts 0.90 to 1.39, 1.14 on average; longer ones, where the correction goes last (below), 0.82 to 1.23; where 4
+  //     fit, or 8 do not, 0.88 to 1.80;
+  //   - with one query head and 1024 workgroups of 4 or more, where the weights are a small part of what a workgroup reads: 0.96
+  //     to 1.10 at 2 bits, mostly 0.98 to 1.02, 0.94 to 1.04 at 4 bits (8 to 64 kv heads, 300 to 4000 tokens).  An empirical cut:
+  //     from 768 to 1023 0.98 to 1.17 at 2 bits, 0.94 to 1.03 at 4.
   auto corr_workgroups = [&](int seqs) { return (long long)c.H_kv * kCorrParts * ((c.B + seqs - 1) / seqs); };
-  const int corr_seqs = gq == 1 && corr_workgroups(4) >= 1024 ? 8 : 4;
+  constexpr long long kPlaces = 768;
+  const bool eight_fit = bh + corr_workgroups(4) > kPlaces && bh + corr_workgroups(8) <= kPlaces;
+  const bool eight = (gq == 1 && corr_workgroups(4) >= 1024) || (gq <= 2 && c.bits == 2 && eight_fit && groups >= 12 && groups < 64);
+  const int corr_seqs = eight ? 8 : 4;
   if (c.S16 != nullptr && gq <= 4) n_corr = corr_workgroups(corr_seqs);
   long long s = (kTargetWorkgroups - n_corr + bh / 2) / bh;  // rounded to nearest
   if (s > kMaxSplits) s = kMaxSplits;

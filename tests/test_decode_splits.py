@@ -67,3 +67,14 @@ def test_order_between_one_and_two_workgroups_per_unit(B, H_q, H_kv, context, fi
 def test_a_single_sequence_leads_with_the_correction():
     for context in (1, 300, 5000, 131072):
         assert splits_of(1, 32, 8, context).corr_first >= 1
+
+
+@pytest.mark.parametrize("B,H_q,H_kv,bits,seqs", [
+    (12, 32, 32, 2, 4), (13, 32, 32, 2, 8), (16, 32, 32, 2, 8), (17, 32, 32, 2, 4), (8, 64, 64, 2, 8), (8, 128, 64, 2, 8), (53, 16, 8, 2, 8),  # 768 places
+    (8, 192, 64, 2, 4), (13, 32, 32, 4, 4), (32, 32, 32, 2, 8), (32, 32, 32, 4, 8), (28, 32, 32, 2, 4), (32, 64, 32, 2, 4)])
+def test_sequences_of_a_correction_workgroup(B, H_q, H_kv, bits, seqs):
+    for context in (1500, 8064):
+        assert splits_of(B, H_q, H_kv, context, bits=bits).corr_seqs == seqs
+    if B * H_kv < 1000:
+        for context in (300, 1408, 8065, 131072):
+            assert splits_of(B, H_q, H_kv, context, bits=bits).corr_seqs == 4
