@@ -8,7 +8,7 @@
 //   parts, each requested again for the wave's next group as soon as its contraction has consumed it.  Two waves per
 //   (sequence, kv head) also own a 64-token half of the fp16 window, processed as one more block of tokens.  The
 //   waves are combined through LDS and the workgroup writes one (m, l, Y_s) per query head (Alg. 1 line 11);
-//   correction workgroups (kv head, part of phi, 4 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
+//   correction workgroups (kv head, part of phi, 4 or 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
 //   the rows of S, on the matrix cores.
 // Every workgroup counts itself in at its (sequence, kv head); the one that arrives last merges, one wave per query
 // head: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
