@@ -373,20 +373,27 @@ __device__ __forceinline__ bool rows_stored_early(bool sliding, int nr, const Ap
 // records lie beyond the counters: dead storage, whatever becomes of the append.  A key or rotated value that is not finite
 // raises the sequence's flag (bit 30 of its first split_done entry), so that all workgroups of that sequence in the launch
 // that follows refuse the append, whichever head or group the fault is in.
-// Bound: the vector unit (78 % of the busy time at 2 bits); 512 bytes in and 72 out per token and kv head come second.
-// Workgroups of four waves and, at 2 (4) bits, 50 (60) KB of LDS, three (two) per compute unit.  Measured, 16 prompts of 8192
-// tokens (8 kv heads; 611 MB): 140 us, 4.4 TB/s; 290 us at 4 bits; a pass that only looked for non-finite rows had taken 164
-// us before.
+// Bound: the vector unit; 512 bytes in and 72 out per token and kv head come second.
+// Workgroups of four waves, four per compute unit: 124 registers, and 38 KB of LDS because the record is put together where
+// the window's rows have been (only a group that takes tokens from the window reads them, all of them before it writes).
+// Measured, 16 prompts of 8192 tokens (8 kv heads; 611 MB): 130 us, 4.7 TB/s; 146 us with 50 KB and three workgroups a unit.  The
+// calls around it: 460 -> 451 us there, 32 ragged prompts at 4 bits in three chunks (60 KB and two a unit before) 360 -> 343, one
+// of 700 tokens 52.8 -> 49.7.
 constexpr int kQuantWaves = 4;
 template <bool SLIDING, int BITS>
-__global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
+__global__ __launch_bounds__(64 * kQuantWaves, 4) void append_quantize_kernel(kvlinc_cache c, const half_t* __restrict__ k_new,
                                                                             const half_t* __restrict__ v_new,
                                                                             const int32_t* __restrict__ n_new, int T, int keep,
                                                                             int per_pair, int first_pair) {
   using R = Rec<BITS>;
-  __shared__ __align__(16) half_t st[kGroup][kRowH];  // rotated rows of the window
-  __shared__ __align__(16) uint32_t img[R::kWords];
-  __shared__ QuantLds<kQuantWaves> L;
+  constexpr int kStWords = kGroup * kRowH / 2;
+  __shared__ __align__(16) uint32_t shared[kStWords > R::kWords ? kStWords : R::kWords];
+  half_t (*st)[kRowH] = reinterpret_cast<half_t (*)[kRowH]>(shared);  // rotated rows of the window
+  uint32_t* img = shared;                                             // the record, once they have been read
+  __shared__ __align__(16) union {
+    QuantLds<kQuantWaves> q;
+    int ok[kGroup];
+  } L;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int p = first_pair + blockIdx.x / per_pair, j = blockIdx.x % per_pair;
@@ -406,12 +413,12 @@ __global__ __launch_bounds__(64 * kQuantWaves, 3) void append_quantize_kernel(kv
       __syncthreads();
     }
     bad = quantize_group<BITS, kQuantWaves>(reinterpret_cast<const half_t*>(c.k_res) + bh * c.R * kHeadDim, k_src + skip * kHeadDim,
-                                            v_src + skip * kHeadDim, st, nrg, valid, L, img, wave, lane);
+                                            v_src + skip * kHeadDim, st, nrg, valid, L.q, img, wave, lane);
     const long long grp = (long long)(s.nq / kGroup) + j;
     uint4* rec = reinterpret_cast<uint4*>(c.groups + (bh * c.max_groups + grp) * R::kWords);
     for (int i = tid; i < R::kWords / 4; i += 64 * kQuantWaves) rec[i] = reinterpret_cast<const uint4*>(img)[i];
   } else if (rows_stored_early(SLIDING, s.nr, s.plan)) {
-    bad = store_window<kQuantWaves, false>(c, bh, k_src, v_src, s.nr, s.n, s.plan, st, reinterpret_cast<int*>(img), wave, lane);
+    bad = store_window<kQuantWaves, false>(c, bh, k_src, v_src, s.nr, s.n, s.plan, st, L.ok, wave, lane);
   } else {
     // only a look at the rows (they are stored by the next launch)
     bad = false;

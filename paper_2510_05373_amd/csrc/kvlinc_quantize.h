@@ -416,8 +416,10 @@ __device__ __forceinline__ void key_codes(KeyTile<NW>& k, int valid, const Quant
     for (int pl = 0; pl < kPlanes; ++pl) {
 #pragma unroll
       for (int d = 0; d < 2; ++d) word[d][pl] |= dpp_u<kQuadSwap1>(word[d][pl]);
+      // (values, not places: a choice between two elements of the array would put the array into memory)
+      const uint32_t first = word[0][pl], second = word[1][pl], mine = (sub & 1) ? second : first;
       const int tk = key_token<NW>((sub & 1) ? i + 1 : i, wave, lane), nb = tk >> 4, jr = tk & 15;
-      img[Rec<BITS>::kKeyTile + kPlaneWords * pl + ((nb >> 1) * 64 + jr) * 4 + 2 * (nb & 1) + wbase] = (sub & 1) ? word[1][pl] : word[0][pl];
+      img[Rec<BITS>::kKeyTile + kPlaneWords * pl + ((nb >> 1) * 64 + jr) * 4 + 2 * (nb & 1) + wbase] = mine;
     }
   }
 }
@@ -463,7 +465,8 @@ __device__ __forceinline__ void stage_window_values(const half_t* __restrict__ v
 
 // The record of one group into the LDS image img (Rec<BITS>::kWords).  Tokens 0 .. nrg - 1 come from the window (raw keys
 // k_win, slot = token; rotated values staged in st), the others up to `valid` are the new rows k_src, v_src + 128 (token - nrg);
-// padding tokens beyond are zero rows.  Returns whether this thread saw a value or key that is not finite.  Ends with a barrier.
+// padding tokens beyond are zero rows.  st may lie in the same LDS as img: where rows come from it they are all read before
+// anything is written.  Returns whether this thread saw a value or key that is not finite.  Ends with a barrier.
 template <int BITS, int NW>
 __device__ __forceinline__ bool quantize_group(const half_t* __restrict__ k_win, const half_t* __restrict__ k_src,
                                                const half_t* __restrict__ v_src, half_t (*st)[kRowH], int nrg, int valid,
@@ -489,22 +492,24 @@ __device__ __forceinline__ bool quantize_group(const half_t* __restrict__ k_win,
     if (t >= nrg && t < valid) load_row(v[i], v_src + (long long)(t - nrg) * kHeadDim, rl.q);
   }
   key_minmax<NW>(k, valid, L, wave, lane);
+  half2_t h[kPasses][16];
 #pragma unroll
   for (int i = 0; i < kPasses; ++i) {
-    const int pass = kPasses * wave + i, t = value_pass_token(pass, rl);
-    half2_t h[16];
-    row_pairs(v[i], h);
-    if (nrg < kGroup) rotate_rows(h, rl.q);
+    row_pairs(v[i], h[i]);
+    if (nrg < kGroup) rotate_rows(h[i], rl.q);
     if (nrg > 0) {
+      const int t = value_pass_token(kPasses * wave + i, rl);
       Row w;
       load_row(w, st[t], rl.q);
       half2_t hw[16];
       row_pairs(w, hw);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) h[e] = t < nrg ? hw[e] : h[e];
+      for (int e = 0; e < 16; ++e) h[i][e] = t < nrg ? hw[e] : h[i][e];
     }
-    bad |= quantize_value_pass<BITS>(h, pass, rl, lane, img);
   }
+  if (nrg > 0) lds_barrier();
+#pragma unroll
+  for (int i = 0; i < kPasses; ++i) bad |= quantize_value_pass<BITS>(h[i], kPasses * wave + i, rl, lane, img);
   lds_barrier();
   if (tid < kGroup) bad |= key_params<BITS, NW>(L, tid, img);
   lds_barrier();
