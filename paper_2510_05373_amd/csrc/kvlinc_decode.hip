@@ -5,8 +5,8 @@
 //   streaming workgroups (sequence, kv head, split): the four waves take groups of 128 tokens from a static schedule
 //   that is the same for every sequence length; a wave keeps its own (m, l, acc).  The number of splits of a
 //   sequence follows its share of the batch's groups, so that sequences of unequal lengths end together.  A group record is fetched in two
-//   parts, each requested again for the wave's next group as soon as its contraction has consumed it.  Two waves per
-//   (sequence, kv head) also own a 64-token half of the fp16 window, processed as one more block of tokens.  The
+//   parts, each requested again for the wave's next group as soon as its contraction has consumed it.  The four
+//   waves of split 0 of a (sequence, kv head) also take a share of the fp16 window each, as one more block of tokens.  The
 //   waves are combined through LDS and the workgroup writes one (m, l, Y_s) per query head (Alg. 1 line 11);
 //   correction workgroups (kv head, part of phi, 4 or 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
 //   the rows of S, on the matrix cores.
@@ -48,6 +48,7 @@ typedef int v8i_t __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef short short2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 
 // ---- small helpers ----------------------------------------------------------------------------------------------
 
@@ -64,8 +65,14 @@ __device__ __forceinline__ float2 ld_coherent2(const float* p) {  // two neighbo
   const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   return __builtin_bit_cast(float2, v);
 }
+// A number that the launch only reads, through the scalar cache: it does not wait behind the vector loads requested before it.
+__device__ __forceinline__ int scalar_load(const int32_t* p) {
+  typedef const __attribute__((address_space(4))) int32_t* constant_ptr;
+  return *reinterpret_cast<constant_ptr>(reinterpret_cast<uintptr_t>(p));
+}
 // Cache policy of a buffer load that is coherent in the same way: sc0 and sc1.
 constexpr int kCoherentLoad = 1 | 16;
+constexpr int kAllLoads = 0x0f70;  // s_waitcnt vmcnt(0)
 
 __device__ __forceinline__ float as_f32(uint32_t v) { return __builtin_bit_cast(float, v); }
 __device__ __forceinline__ uint32_t as_bits(float v) { return __builtin_bit_cast(uint32_t, v); }
@@ -280,6 +287,16 @@ struct WaveState {
   float pz[NB];         // per-lane partial sum of p * (value zero-point + 1.5 value scale)
   float acc[NB][8];     // E V of channel 16 n + jd
 };
+
+template <int NB>
+__device__ __forceinline__ void empty_state(WaveState<NB>& st) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    st.m[nb] = -INFINITY; st.l[nb] = 0.f; st.pz[nb] = 0.f;
+#pragma unroll
+    for (int n = 0; n < 8; ++n) st.acc[nb][n] = 0.f;
+  }
+}
 
 // q K^T of one group for all heads (Alg. 1 line 7): sc[nb][n] = q.k of head 4 nb + hd, token 16 n + jd (the factor
 // log2(e) / sqrt(d) enters with the reference maximum, see exponent()).
@@ -507,7 +524,7 @@ __device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (
 
 // Sliding value window (Sec. 4.1, setup: the newest 128 tokens in full precision): the tokens j >= from of the newest
 // group still have their fp16 rotated values in the window slots j.  Their share of E V is formed here from those values
-// by the one wave that has the newest group, on v_mfma_f32_4x4x4_16B_f16 as in window_half: rows = the 4 heads of a head
+// by the one wave that has the newest group, on v_mfma_f32_4x4x4_16B_f16: rows = the 4 heads of a head
 // block, columns = 64 channels (lane = channel), k = 4 window slots, the probabilities (binary16, through LDS) broadcast
 // from one lane quad per block of 4 slots.  The result is added to the accumulators by way of `out`, this wave's
 // [NB * 4][128] slice of the combine buffer.
@@ -573,95 +590,98 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
   lds_order();
 }
 
-// ---- half of the fp16 window as one more block of 64 tokens of one wave (raw keys, rotated values) ---------------
-// On v_mfma_f32_4x4x4_16B_f16 with the A operand broadcast from one lane quad: rows = the 4 heads of a head block.
-//   q K^T : columns = 64 tokens (lane = token), k = 4 channels;  E V : columns = 64 channels (lane = channel), k = 4 tokens.
-// Runs before the wave's first group, on empty state.
-
-template <int NB>
-struct WindowState {
-  float m[NB][4];       // maximum per head (wave-uniform), log2 domain
-  float l[NB][4];       // per-lane p (lane = token)
-  float4_t accw[NB][2];  // E V in true units: [head block][channel half], rows = heads, lane = channel
+// ---- a wave's share of the fp16 window as one more block of tokens (raw keys, rotated values) -----------------------------
+// On v_mfma_f32_16x16x32_f16, in the row role of the groups: D register nb of lane (hd, jd) is head 4 nb + hd, row 4 hd + nb of
+// the A operand; the other rows are zero.
+//   q K^T : columns = 16 tokens, positions = 32 channels: step kk takes from lane (hd, jd) the channels
+//           64 (kk / 2) + 16 hd + 8 (kk % 2) + 0..7 of token 16 tt + jd, which is what the lanes of a quad hold of q in the operand
+//           role (lane kk of the quad), so that A comes from qh by broadcasts inside the quads;
+//   E V   : columns = 16 channels, positions = 32 tokens: lane (hd, jd) has tokens 8 hd + 0..7, two 4-slot pieces of v_res.
+// Runs before the wave's first group, on empty state.  Bound: latency and, where many short sequences fill the chip, bytes: what
+// lies beyond the window's tokens is not read (lanes without a token take the last one's rows), unless the launch is so small
+// that the whole window is requested ahead of the counters (see launch_decode).
+// Two waves with 64 tokens each, on the 4x4x4 blocks, waited for their first record, then for the keys (each a 16-byte piece of
+// 64 lines, in 16 instructions), then for the values, then for q.  Steps before and after (with the requests laid out as they are in
+// the kernel below): 144 sequences of 1280 tokens 70.7 -> 64.0 us, 32 x 32 single heads of 1280 45.4 -> 42.0, one sequence of
+// 131072 24.4 -> 22.8, of 300 11.8 -> 10.9 (there the host's calls take as long by now), 16 of 8k 25.1 -> 24.5, 32 of 32k with 7 heads
+// 75.6 -> 72.4.
+struct WindowShare {
+  int first, end;  // tokens first .. end - 1, at most 32 and first a multiple of 4; none: end <= first
 };
+__device__ __forceinline__ WindowShare window_share(int nr, int wave) {
+  const int per = 4 * ((nr + 4 * kWaves - 1) / (4 * kWaves));
+  return WindowShare{per * wave, min(per * (wave + 1), nr)};
+}
+struct WindowRegs {
+  uint4 k[2][4];  // [tt][kk]
+  uint4 v[8];     // [channel block]: slots 8 hd + 0..3 (x, y) and + 4..7 (z, w)
+};
+__device__ __forceinline__ void request_window(WindowRegs& w, const kvlinc_cache& c, int bh, const WindowShare& sh, const Roles& lr) {
+  const half_t* keys = reinterpret_cast<const half_t*>(c.k_res) + (long long)bh * c.R * kHeadDim;
+  const uint2* vb = reinterpret_cast<const uint2*>(reinterpret_cast<const half_t*>(c.v_res) + (long long)bh * c.R * kHeadDim) + lr.jd;
+  const int last = max(sh.end - 1, 0);
+#pragma unroll
+  for (int tt = 0; tt < 2; ++tt) {
+    const uint4* krow = reinterpret_cast<const uint4*>(keys + min(sh.first + 16 * tt + lr.jd, last) * kHeadDim);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) w.k[tt][kk] = krow[8 * (kk >> 1) + 2 * lr.hd + (kk & 1)];
+  }
+  const int u = sh.first / 4 + 2 * lr.hd;
+  const uint2 *v0 = vb + min(u, last >> 2) * kHeadDim, *v1 = vb + min(u + 1, last >> 2) * kHeadDim;
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    const uint2 a = v0[16 * n], b = v1[16 * n];
+    w.v[n] = make_uint4(a.x, a.y, b.x, b.y);
+  }
+}
 
+// The share is not empty: the maxima are finite.
 template <int NB>
-__device__ __forceinline__ void window_half(const kvlinc_cache& c, const half_t* __restrict__ q, int bh, int b, int g,
-                                            int gq, int half, int nr, int lane, WindowState<NB>& st) {
-  const int quad = lane >> 2, hrow = lane & 3;
-  const uint32_t perm_sel = (lane & 1) ? 0x03020706u : 0x05040100u;
-  // 16 x 16 B of this lane's key row now; 32 x 8 B of this lane's two value channels once the keys are consumed
-  const int tok = 64 * half + lane;
-  const int row = tok < c.R ? tok : c.R - 1;  // rows beyond the capacity do not exist; their scores are masked below
-  const uint4* krow = reinterpret_cast<const uint4*>(reinterpret_cast<const half_t*>(c.k_res) +
-                                                     ((long long)bh * c.R + row) * kHeadDim);
-  uint4 kx[16];
+__device__ __forceinline__ void window_part(const WindowRegs& w, const uint32_t (&qh)[NB][4], const WindowShare& sh, const Roles& lr, WaveState<NB>& st) {
+  float4_t d[2];
+  d[0] = d[1] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const uint32_t row0 = lr.ua == 0 ? ~0u : 0u, row1 = lr.ua == 1 ? ~0u : 0u;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) kx[i] = krow[i];
-  const uint2* vbase = reinterpret_cast<const uint2*>(reinterpret_cast<const half_t*>(c.v_res) +
-                                                      (long long)bh * c.R * kHeadDim);
-  const int n_blocks = c.R / 4;
-  // A operand of q K^T: raw q of this lane's head, channels 8*quad .. 8*quad+7
-  half4_t A[NB][2];
+  for (int kk = 0; kk < 4; ++kk) {
+    const auto from_quad = [&](uint32_t v) { return kk == 0 ? dpp_u<0x00>(v) : kk == 1 ? dpp_u<0x55>(v) : kk == 2 ? dpp_u<0xAA>(v) : dpp_u<0xFF>(v); };
+    uint32_t a[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      a[i] = from_quad(qh[0][i]) & row0;
+      if (NB == 2) a[i] |= from_quad(qh[NB - 1][i]) & row1;
+    }
+    const half8_t A = __builtin_bit_cast(half8_t, make_uint4(a[0], a[1], a[2], a[3]));
+#pragma unroll
+    for (int tt = 0; tt < 2; ++tt) d[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(half8_t, w.k[tt][kk]), d[tt], 0, 0, 0);
+  }
+  half_t* pb = reinterpret_cast<half_t*>(lr.ex_pv);  // head 4 nb + hd: 32 halves at words 160 hd + 16 nb (clear of the spare term rows)
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int h = nb * 4 + hrow;
-    uint4 raw = make_uint4(0, 0, 0, 0);
-    if (h < gq) raw = *reinterpret_cast<const uint4*>(q + ((long long)b * c.H_q + g * gq + h) * kHeadDim + 8 * quad);
-    A[nb][0] = as_h4(raw.x, raw.y);
-    A[nb][1] = as_h4(raw.z, raw.w);
-  }
-  float4_t acc[NB][2][2];
+    float sc[2];
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb)
+    for (int tt = 0; tt < 2; ++tt) sc[tt] = sh.first + 16 * tt + lr.jd < sh.end ? d[tt][nb] * kAlpha : -INFINITY;
+    const float m = row_allmax(fmaxf(sc[0], sc[1]));
+    float p[2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) acc[nb][a][0] = acc[nb][a][1] = float4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const half4_t b0 = as_h4(kx[i].x, kx[i].y), b1 = as_h4(kx[i].z, kx[i].w);
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      acc[nb][0][i & 1] = mfma_bcast(A[nb][0], b0, acc[nb][0][i & 1], i);
-      acc[nb][1][i & 1] = mfma_bcast(A[nb][1], b1, acc[nb][1][i & 1], i);
+    for (int tt = 0; tt < 2; ++tt) {
+      p[tt] = __builtin_amdgcn_exp2f(sc[tt] - m);
+      pb[2 * (kExHead * lr.hd + 16 * nb) + 16 * tt + lr.jd] = (half_t)p[tt];
     }
+    st.m[nb] = m;
+    st.l[nb] = p[0] + p[1];
+    st.pz[nb] = 0.0f;
   }
-  float4_t sc[NB];
+  lds_order();
+  const uint4 t = *reinterpret_cast<const uint4*>(pb + 2 * (kExHead * lr.ha + 16 * min(lr.ua, NB - 1)) + 8 * lr.hd);
+  const half8_t A = __builtin_bit_cast(half8_t, lr.ua < NB ? t : make_uint4(0, 0, 0, 0));
+  lds_order();
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    sc[nb] = (acc[nb][0][0] + acc[nb][0][1] + acc[nb][1][0] + acc[nb][1][1]) * kAlpha;
-    if (tok >= nr) sc[nb] = float4_t{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  for (int n = 0; n < 8; ++n) {
+    const float4_t zero = {0.f, 0.f, 0.f, 0.f};
+    const float4_t e = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(half8_t, w.v[n]), zero, 0, 0, 0);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) st.acc[nb][n] = e[nb];
   }
-  uint2 vx[2][16];
-#pragma unroll
-  for (int ch = 0; ch < 2; ++ch)
-#pragma unroll
-    for (int bq = 0; bq < 16; ++bq) {
-      const int blk = 16 * half + bq;
-      vx[ch][bq] = blk < n_blocks ? vbase[(long long)blk * kHeadDim + 64 * ch + lane] : make_uint2(0, 0);
-    }
-  half4_t A2[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    float p[4];
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      st.m[nb][h] = wave_allmax(sc[nb][h]);  // finite: the caller passes a half that holds a token
-      p[h] = __builtin_amdgcn_exp2f(sc[nb][h] - st.m[nb][h]);
-      st.l[nb][h] = p[h];
-    }
-    const half2_t x01 = {(half_t)p[0], (half_t)p[1]}, x23 = {(half_t)p[2], (half_t)p[3]};
-    // 4x4 transpose inside each lane quad: (lane = token, slots = heads) -> (lane = head, slots = tokens)
-    A2[nb] = quad_transpose(as_u32(x01), as_u32(x23), perm_sel, lane);
-    st.accw[nb][0] = st.accw[nb][1] = float4_t{0.f, 0.f, 0.f, 0.f};
-  }
-#pragma unroll
-  for (int bq = 0; bq < 16; ++bq)
-#pragma unroll
-    for (int ch = 0; ch < 2; ++ch) {
-      const half4_t bop = as_h4(vx[ch][bq].x, vx[ch][bq].y);
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) st.accw[nb][ch] = mfma_bcast(A2[nb], bop, st.accw[nb][ch], bq);
-    }
 }
 
 // ---- correction terms (Sec. 3.3: C_n = phi_q(q) S, C_d = phi_q(q) P; Eq. 6 for phi) -----------------------------------
@@ -719,7 +739,6 @@ __device__ __forceinline__ float quadgroup_allsum(float v) {
 
 // Phase 1 for one head: channels 32 kk .. + 31 for the KS steps kk from k0 on.  logits: [sequence][..][kPartFeat], `stride` floats
 // from one sequence to the next, this head's first.
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 template <int KS>
 struct CorrWeights {
   uint2 w[KS][8];
@@ -1019,12 +1038,16 @@ __device__ __forceinline__ BatchCounters request_counters(const kvlinc_cache& c,
   for (int u = 0; u < kCounterRows; ++u) r.n[u] = c.n_quant[min(lane + 64 * u, c.B - 1)];
   return r;
 }
-// Groups of the whole batch, in every lane.
+// Groups of the whole batch, in a scalar register.
 __device__ __forceinline__ int batch_groups(const kvlinc_cache& c, const BatchCounters& r, int lane) {
   uint32_t total = 0;
 #pragma unroll
   for (int u = 0; u < kCounterRows; ++u) total += lane + 64 * u < c.B ? groups_of(r.n[u]) : 0;
-  for (int i = lane + 64 * kCounterRows; i < c.B; i += 64) total += groups_of(c.n_quant[i]);
+  for (int first = 64 * kCounterRows; first < c.B; first += 64) {  // (no lane goes its own way: see the callers)
+    int n = c.n_quant[min(first + lane, c.B - 1)];
+    asm volatile("" : "+v"(n));
+    total += first + lane < c.B ? groups_of(n) : 0;
+  }
   total += dpp_u<kRowRor1>(total);
   total += dpp_u<kRowRor2>(total);
   total += dpp_u<kRowRor4>(total);
@@ -1032,7 +1055,7 @@ __device__ __forceinline__ int batch_groups(const kvlinc_cache& c, const BatchCo
   const auto a = __builtin_amdgcn_permlane16_swap(total, total, false, false);
   total = a[0] + a[1];
   const auto b = __builtin_amdgcn_permlane32_swap(total, total, false, false);
-  return (int)(b[0] + b[1]);
+  return __builtin_amdgcn_readfirstlane((int)(b[0] + b[1]));
 }
 
 // count = the sequence's groups (the same in every lane), total = the batch's.  ceil(avg count B / total - 1/4) is the
@@ -1068,14 +1091,29 @@ __device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
 // default one carries none of its code.
 // BITS: so is the one for caches with 4-bit codes (it holds twice the tile words in registers).
 // FEW_HEADS: and the one for fewer than 4 query heads per kv head (see correction_workgroup).
-// (The arguments up to H_kv are in scalar registers when a wave starts, see append_token_kernel.)
+// What the way to the first requests takes comes in 14 words, which are in scalar registers when a wave starts (see
+// append_token_kernel): five pointers, and counts that stay below 2^24 with small numbers above them.
+struct LaunchWords {
+  uint32_t batch;   // B - 1, splits of a sequence on average << 24, window requested early << 30, correction on << 31
+  uint32_t heads;   // H_kv - 1, most splits of a sequence << 24, runs of the grid that the correction leads << 30
+  uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, eight sequences a correction workgroup << 27
+  uint32_t magic;   // ceil(2^32 / H_kv), or 0 where that does not give quotients by H_kv
+};
+constexpr uint32_t kLow24 = (1u << 24) - 1u;
+
 template <int NB, bool SLIDING = false, int BITS = 2, bool FEW_HEADS = false>
-__global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(uint32_t* groups, int32_t* n_quant, int64_t max_groups,
-                                                                   float* __restrict__ corr, int B, int max_splits, int avg_splits,
-                                                                   int corr_first, int corr_seqs, int H_kv, int gq, kvlinc_cache cache,
-                                                                   const half_t* __restrict__ q, float* __restrict__ part, half_t* __restrict__ out) {
+__global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3) void decode_main_kernel(uint32_t* groups, int32_t* n_quant, const half_t* __restrict__ q,
+                                                                   const kvlinc_half* Wq, kvlinc_half* S16, uint32_t batch_word, uint32_t heads_word,
+                                                                   uint32_t groups_word, uint32_t magic, kvlinc_cache cache,
+                                                                   float* __restrict__ corr, float* __restrict__ part, half_t* __restrict__ out) {
+  const LaunchWords words = {batch_word, heads_word, groups_word, magic};
+  const int max_splits = (words.heads >> 24) & 63, avg_splits = (words.batch >> 24) & 63, L = words.heads >> 30, gq = ((words.groups >> 24) & 7) + 1;
+  const int log_seqs = 2 + ((words.groups >> 27) & 1), corr_seqs = 1 << log_seqs;
+  const bool early_window = (words.batch >> 30) & 1, has_corr = words.batch >> 31;
   kvlinc_cache c = cache;
-  c.groups = groups; c.n_quant = n_quant; c.max_groups = max_groups; c.B = B; c.H_kv = H_kv;
+  c.groups = groups; c.n_quant = n_quant; c.Wq = Wq; c.S16 = S16;
+  c.max_groups = (int)(words.groups & kLow24) + 1; c.B = (int)(words.batch & kLow24) + 1; c.H_kv = (int)(words.heads & kLow24) + 1; c.H_q = gq * c.H_kv;
+  auto by_heads = [&](int n) { return words.magic != 0 ? (int)__umulhi((uint32_t)n, words.magic) : n / c.H_kv; };
   constexpr int kCombine = 2 * kWaves * NB * 4 + kWaves * NB * 4 * kHeadDim;
   __shared__ __align__(16) float lds[kCombine + kWaves * 2 * kExWords];
   static_assert(kCombine + kWaves * 2 * kExWords >= kMaxCorrSeqs * NB * 4 * kPartFeat, "the logits of a correction workgroup");
@@ -1085,28 +1123,25 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keeps the schedule in scalar registers
-  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + corr_seqs - 1) / corr_seqs) : 0;
-  const int n_parts = corr != nullptr ? kCorrParts : 0;
+  const int n_corr = has_corr ? c.H_kv * kCorrParts * ((c.B + corr_seqs - 1) >> log_seqs) : 0;
+  const int n_parts = has_corr ? kCorrParts : 0;
 
-  const int n_stream = gridDim.x - n_corr;
-  // corr_first = 0: the correction workgroups come last; L >= 1: they lead each of the first L runs of 256
+  // L = 0: the correction workgroups come last; L >= 1: they lead each of the first L runs of 256
   // workgroups in equal shares.  The dispatcher deals workgroup i to compute unit i mod 256 while places are free, so
   // with L = 2 the correction workgroups pair up on compute units of their own and no streaming workgroup has one
   // as a neighbour.
   bool is_corr;
   int corr_id, stream_id;
-  int L = corr_first;  // every run that leads with correction workgroups must lie inside the grid and hold its share
-  while (L > 1 && ((int)gridDim.x < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
-  if (L == 0 || n_corr == 0) {
-    is_corr = (int)blockIdx.x >= n_stream;
-    corr_id = blockIdx.x - n_stream;
+  if (L == 0) {
+    corr_id = blockIdx.x - c.B * c.H_kv * max_splits;
+    is_corr = corr_id >= 0;
     stream_id = blockIdx.x;
   } else if (L == 1) {
     is_corr = (int)blockIdx.x < n_corr;
     corr_id = blockIdx.x;
     stream_id = blockIdx.x - n_corr;
   } else {
-    const int per = (n_corr + L - 1) / L;
+    const int per = L == 2 ? (n_corr + 1) >> 1 : (n_corr + 2) / 3;
     const int layer = min((int)blockIdx.x / 256, L), pos = layer < L ? (int)blockIdx.x % 256 : 0;
     const int before = min(n_corr, layer * per + min(pos, per));  // correction workgroups ahead of this one
     is_corr = layer < L && pos < per && before < n_corr;
@@ -1119,7 +1154,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     const int id = corr_id;
     // The workgroups that read the same slice of W (same kv head and part, different sequences) are H_kv * kCorrParts
     // apart in the grid: workgroups are dealt to the 8 XCDs in turn, so with an even H_kv they share one L2.
-    const int r = id % kCorrParts, g = (id / kCorrParts) % c.H_kv, sb = id / (kCorrParts * c.H_kv);
+    const int r = id % kCorrParts, sb = by_heads(id / kCorrParts), g = id / kCorrParts - sb * c.H_kv;
     const int b_first = sb * corr_seqs;
     const int n_seq = min(corr_seqs, c.B - b_first);
     // A sequence without quantized tokens has S = P = 0 (the states only change at a flush), so its parts come out
@@ -1153,123 +1188,135 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   const int wg = stream_id;
   // split-major: the splits that only long sequences use come last in the grid, and the workgroups of any one split
   // index are dealt evenly to the XCDs
-  const int bh = wg % (c.B * c.H_kv);
-  const int sp = wg / (c.B * c.H_kv);
-  const int b = bh / c.H_kv;
-  const int g = bh % c.H_kv;
+  int bh = wg, sp = 0;  // (at most 32 splits: a division by shifts)
+#pragma unroll
+  for (int i = 4; i >= 0; --i) {
+    const int run = (c.B * c.H_kv) << i;
+    const bool past = bh >= run;
+    bh -= past ? run : 0;
+    sp += past ? 1 << i : 0;
+  }
+  const int b = by_heads(bh), g = bh - b * c.H_kv;
 
   // Static schedule, the same for every sequence length, so that a wave knows its first group before it knows the
-  // length.  Time is cut into rounds of 4 n_splits slots, slot(round, wave, split) = 4 n_splits round + n_splits wave
-  // + split; the groups 0, 1, 2, ... go to the slots in order, except that the two waves that own a half of the
-  // window sit out their first kSkip slots (the window is their work for that time).  Consecutive groups thus go to
-  // different workgroups, and every split gets the same share whatever the length.
-  constexpr int kSkip = 2;
+  // length.  Time is cut into rounds of 4 n_splits slots, slot(round, wave, split) = 4 n_splits round + n_splits wave +
+  // n_splits - 1 - split; the groups 0, 1, 2, ... go to the slots in order, except that the four waves of split 0 sit out the
+  // first kSkip rounds: a share of the window each is their work for that time.  Consecutive groups thus go to different
+  // workgroups, and every split gets the same share whatever the length.
+  // (kSkip: 16 sequences of 8k tokens at 2 bits 24.5 us a step, 24.7 with 1; at 4 bits, where a record is twice as long, 39.1 with 2, 37.4
+  // with 1.)
+  constexpr int kSkip = BITS == 2 ? 2 : 1;
   int n_splits = avg_splits;  // first guess: right for a batch of equal lengths
-  int slots, my_half, off, lead1, rd, idx;
-  auto group_of_round = [&](int round) {
-    return round * slots + off - min(round, kSkip) - min(round + lead1, kSkip);
-  };
+  int slots, off, rd, idx;
+  auto group_of_round = [&](int round) { return round * slots + off - (round < kSkip ? kWaves * round + wave : kWaves * kSkip); };
   auto plan = [&]() {
     slots = kWaves * n_splits;
-    my_half = -1;
-    if (n_splits >= 2) {
-      if (wave == kWaves - 1 && sp >= n_splits - 2) my_half = n_splits - 1 - sp;
-    } else if (wave >= kWaves - 2) {
-      my_half = kWaves - 1 - wave;
-    }
-    // group(round) = slot - (slots skipped before it).  The owners of half 0 and half 1 have the round's last and
-    // last but one slot, so the owner of half 0 has skipped min(round, kSkip) slots before a wave's slot and the
-    // owner of half 1 one more if it comes earlier in the round.
-    const int base1 = n_splits >= 2 ? slots - 2 : kWaves - 2;
-    off = wave * n_splits + sp;
-    lead1 = off > base1 ? 1 : 0;
-    rd = my_half >= 0 ? kSkip : 0;
+    off = wave * n_splits + n_splits - 1 - sp;
+    rd = sp == 0 ? kSkip : 0;
     idx = group_of_round(rd);
   };
-  plan();
 
-  // The first record is requested before the sequence length is known (any group index below the capacity is
-  // readable memory); what it holds is used only if the group exists.
+  // What the wave works on first -- its part of the window, a record -- is requested before the sequence length is known (any group
+  // index below the capacity is readable memory, and so are the window's slots); what it holds is used only if it exists.
   constexpr int kRecordWords = Rec<BITS>::kWords;
   const uint32_t* rec0 = c.groups + (long long)bh * c.max_groups * kRecordWords;
   const Roles lr = make_roles(lane, ex[wave]);
   KeyRegs<BITS> kr;
   ValueRegs<BITS> vr;
-  const BatchCounters counters = request_counters(c, lane);
-  if (sp < avg_splits) {
+  uint32_t qh[NB][4];  // q of the head this lane builds operands for (head 4 nb + ha, or the last one), channels c0 .. c0 + 7
+  auto request_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const uint4 raw = *reinterpret_cast<const uint4*>(q + ((long long)b * c.H_q + g * gq + min(nb * 4 + lr.ha, gq - 1)) * kHeadDim + lr.c0);
+      qh[nb][0] = raw.x; qh[nb][1] = raw.y; qh[nb][2] = raw.z; qh[nb][3] = raw.w;
+    }
+  };
+  auto request_record = [&](bool with_q) __attribute__((always_inline)) {
     const long long first = idx < c.max_groups ? idx : c.max_groups - 1;
+    // (in the order of the loop below, whatever the way here: the wait for a part is then for that part alone)
     load_keys(kr, rec0 + first * kRecordWords, lr);
+    asm volatile("" ::: "memory");
+    if (with_q) request_q();
+    asm volatile("" ::: "memory");
     load_values(vr, rec0 + first * kRecordWords, lr);
-  }
-  const int nq = c.n_quant[b];
-  const int nr = c.n_res[b];
-  const int count = groups_of(nq);
-  {
-    int total = 0;
-    if (c.B > 1) total = batch_groups(c, counters, lane);
-    const int mine = sequence_splits(c, count, total, avg_splits, max_splits, lane);
-    if (sp >= mine) return;  // this sequence uses fewer splits than the grid provides
-    if (mine != n_splits) {  // lengths differ within the batch: plan again, request the right first record
+    asm volatile("" ::: "memory");
+  };
+  int nq, nr, count;
+  auto splits_of_sequence = [&](BatchCounters& counters) __attribute__((always_inline)) {
+    nq = scalar_load(c.n_quant + b);
+    nr = scalar_load(c.n_res + b);
+    count = groups_of(nq);
+    // the spare term row of every head reads as zero from here on (this wave's own regions: no barrier needed)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ex[wave][(k >> 1) * kExWords + (2 * (k & 1) + (lane >> 5)) * kExHead + 96 + (lane & 31)] = 0u;
+    lds_order();
+    // (waited for in any case: see the end of the branch below)
+#pragma unroll
+    for (int u = 0; u < kCounterRows; ++u) asm volatile("" : "+v"(counters.n[u]));
+    return sequence_splits(c, count, c.B > 1 ? batch_groups(c, counters, lane) : 0, avg_splits, max_splits, lane);
+  };
+  WaveState<NB> st;
+  // (The counters are requested in every branch by itself: a load from ahead of the branches counts as under way on a path that takes
+  // none of them, which the compiler keeps, and its wait in the loop over the groups would be for the next record, too.  The
+  // statements that open the branches differ so that their loads are not joined ahead of them.)
+  if (sp == 0) {
+    asm volatile("; with the window" ::: "memory");
+    BatchCounters counters = request_counters(c, lane);
+    plan();
+    request_record(true);
+    asm volatile("" ::: "memory");
+    WindowShare sh = window_share(early_window ? c.R : scalar_load(c.n_res + b), wave);
+    WindowRegs w;
+    request_window(w, c, bh, sh, lr);
+    asm volatile("" ::: "memory");
+    const int mine = splits_of_sequence(counters);
+    if (mine != n_splits) {
       n_splits = mine;
       plan();
-      const long long first = idx < c.max_groups ? idx : c.max_groups - 1;
-      load_keys(kr, rec0 + first * kRecordWords, lr);
-      load_values(vr, rec0 + first * kRecordWords, lr);
+      request_record(false);
+    }
+    sh.end = min(sh.end, nr);
+    if (sh.first < sh.end) window_part<NB>(w, qh, sh, lr, st);
+    else empty_state<NB>(st);
+    // (nothing is under way any more: registers that a load may still write make the compiler wait in every round of the loop over
+    // the groups, and that for the next record, too)
+    __builtin_amdgcn_s_waitcnt(kAllLoads);
+  } else if (sp < avg_splits) {
+    asm volatile("; groups" ::: "memory");
+    BatchCounters counters = request_counters(c, lane);
+    plan();
+    request_record(true);
+    empty_state<NB>(st);
+    const int mine = splits_of_sequence(counters);
+    if (mine != n_splits) {  // lengths differ within the batch: plan again, request the right first record
+      n_splits = mine;
+      if (sp < n_splits) {
+        plan();
+        request_record(true);
+      }
+    }
+  } else {  // a split that only the longest sequences of a batch use
+    asm volatile("; groups, perhaps" ::: "memory");
+    BatchCounters counters = request_counters(c, lane);
+    empty_state<NB>(st);
+    n_splits = splits_of_sequence(counters);
+    if (sp < n_splits) {
+      plan();
+      request_record(true);
     }
   }
+  if (sp >= n_splits) return;  // this sequence uses fewer splits than the grid provides
+  // q has arrived from here on: left to its first use, the compiler would wait in every round of the loop for all that may be under
+  // way behind it, the next record among it.
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+v"(qh[nb][0]), "+v"(qh[nb][1]), "+v"(qh[nb][2]), "+v"(qh[nb][3]));
   const int expected = n_splits + n_parts;
-
-  // the spare term row of every head reads as zero from here on (this wave's own regions: no barrier needed)
-  for (int i = lane; i < 2 * 4 * 32; i += 64) ex[wave][(i >> 7) * kExWords + ((i >> 5) & 3) * kExHead + 96 + (i & 31)] = 0u;
-  lds_order();
 
   float (*sM)[NB * 4] = reinterpret_cast<float (*)[NB * 4]>(lds);                    // [kWaves][NB*4]
   float (*sL)[NB * 4] = reinterpret_cast<float (*)[NB * 4]>(lds + kWaves * NB * 4);  // [kWaves][NB*4]
   float (*sAcc)[NB * 4][kHeadDim] = reinterpret_cast<float (*)[NB * 4][kHeadDim]>(lds + 2 * kWaves * NB * 4);
 
-  WaveState<NB> st;
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    st.m[nb] = -INFINITY; st.l[nb] = 0.f; st.pz[nb] = 0.f;
-#pragma unroll
-    for (int n = 0; n < 8; ++n) st.acc[nb][n] = 0.f;
-  }
-
-  if (my_half >= 0 && nr > 64 * my_half) {
-    // this wave's half of the window first, then its results move to the row role: (lane = channel, registers = heads)
-    // -> (row = head, lane = channel % 16, register = channel block n), through this wave's part of the combine buffer
-    WindowState<NB> ws;
-    window_half<NB>(c, q, bh, b, g, gq, my_half, nr, lane, ws);
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      float lsum[4];
-#pragma unroll
-      for (int h = 0; h < 4; ++h) {
-        lsum[h] = wave_allsum(ws.l[nb][h]);
-        sAcc[wave][nb * 4 + h][lane] = ws.accw[nb][0][h];
-        sAcc[wave][nb * 4 + h][64 + lane] = ws.accw[nb][1][h];
-      }
-      lds_order();
-#pragma unroll
-      for (int n = 0; n < 8; ++n) st.acc[nb][n] = sAcc[wave][nb * 4 + lr.hd][16 * n + lr.jd];
-      lds_order();
-      const float m_mine = lr.hd == 0 ? ws.m[nb][0] : lr.hd == 1 ? ws.m[nb][1] : lr.hd == 2 ? ws.m[nb][2] : ws.m[nb][3];
-      const float l_mine = lr.hd == 0 ? lsum[0] : lr.hd == 1 ? lsum[1] : lr.hd == 2 ? lsum[2] : lsum[3];
-      st.m[nb] = m_mine;
-      st.l[nb] = lr.jd == 0 ? l_mine : 0.f;
-    }
-  }
-
   if (idx < count) {
-    // q of the head this lane builds operands for (head 4 nb + ha), channels c0 .. c0 + 7; heads beyond gq read as 0
-    uint32_t qh[NB][4];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int h = nb * 4 + lr.ha;
-      uint4 raw = make_uint4(0, 0, 0, 0);
-      if (h < gq) raw = *reinterpret_cast<const uint4*>(q + ((long long)b * c.H_q + g * gq + h) * kHeadDim + lr.c0);
-      qh[nb][0] = raw.x; qh[nb][1] = raw.y; qh[nb][2] = raw.z; qh[nb][3] = raw.w;
-    }
     // While a group is consumed the wave's next record is already requested: its key part right after the scores,
     // its value part right after E V.  The wave's last group is a copy of the loop body without requests (a request
     // past the end would be a second trip to memory for a record that the non-temporal loads did not leave in the
@@ -1386,6 +1433,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
 // 3 splits 84.0 us, 4 76.5, 5 76.9 a step).  At most 32 splits (the merge holds a row of each
 // in registers; 40 to 64 for one sequence of 131072 tokens, two workgroups per compute unit: 28.2 to 30.8 us a step against 25.0 with 30),
 // at least one group per wave.
+constexpr long long kPlaces = 768;  // workgroups that the chip holds at three per compute unit
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   constexpr int kTargetWorkgroups = 512;
   const long long cap = (long long)c.max_groups * kGroup + c.R;
@@ -1406,7 +1454,6 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   //     to 1.10 at 2 bits, mostly 0.98 to 1.02, 0.94 to 1.04 at 4 bits (8 to 64 kv heads, 300 to 4000 tokens).  An empirical cut:
   //     from 768 to 1023 0.98 to 1.17 at 2 bits, 0.94 to 1.03 at 4.
   auto corr_workgroups = [&](int seqs) { return (long long)c.H_kv * kCorrParts * ((c.B + seqs - 1) / seqs); };
-  constexpr long long kPlaces = 768;
   const bool eight_fit = bh + corr_workgroups(4) > kPlaces && bh + corr_workgroups(8) <= kPlaces;
   const bool eight = (gq == 1 && corr_workgroups(4) >= 1024) || (gq <= 2 && c.bits == 2 && eight_fit && groups >= 12 && groups < 64);
   const int corr_seqs = eight ? 8 : 4;
@@ -1479,9 +1526,20 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   float* corr = c.S16 != nullptr ? workspace + (size_t)c.B * c.H_q * n_splits * kPartStride : nullptr;
   const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + sp.corr_seqs - 1) / sp.corr_seqs) : 0;
   const dim3 grid(BH * n_splits + n_corr), block(kThreads);
-  const int corr_first = sp.corr_first;
+  // every run that leads with correction workgroups must lie inside the grid and hold its share
+  int L = n_corr != 0 ? sp.corr_first : 0;
+  while (L > 1 && ((int)grid.x < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
+  // The whole window ahead of the counters where no compute unit has a second workgroup: one sequence of 300 tokens 10.9 us a step,
+  // 11.5 behind them; beyond that the bytes that are not needed cost as much or more (one sequence of 131072 tokens, 272 workgroups,
+  // the same, 16 of 8k 25.1 against 24.7 us).
+  const bool early_window = (long long)BH * sp.avg + n_corr <= 256;
+  // n / H_kv = umulhi(n, magic) for n below 2^32 / H_kv; n is at most 2^24 + 3 H_kv here
+  const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
+  const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)early_window << 30 | (uint32_t)(corr != nullptr) << 31,
+                             (uint32_t)(c.H_kv - 1) | (uint32_t)sp.most << 24 | (uint32_t)L << 30,
+                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)(sp.corr_seqs == 8) << 27, magic};
   const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
-  void (*kernel)(uint32_t*, int32_t*, int64_t, float*, int, int, int, int, int, int, int, kvlinc_cache, const half_t*, float*, half_t*) =
+  void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)
                               : (sliding ? decode_main_kernel<1, true, 4> : decode_main_kernel<1, false, 4>))
@@ -1489,11 +1547,9 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 2, true> : decode_main_kernel<1, false, 2, true>)
                               : (sliding ? decode_main_kernel<1, true> : decode_main_kernel<1, false>));
   if (start != nullptr)  // timestamps of the dispatch itself, no extra packets on the stream
-    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c.groups, c.n_quant, c.max_groups, corr, c.B, sp.most, sp.avg,
-                          corr_first, sp.corr_seqs, c.H_kv, gq, c, qq, part, oo);
+    hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, start, stop, 0, c.groups, c.n_quant, qq, c.Wq, c.S16, words.batch, words.heads, words.groups, words.magic, c, corr, part, oo);
   else
-    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c.groups, c.n_quant, c.max_groups, corr, c.B, sp.most, sp.avg, corr_first, sp.corr_seqs,
-                       c.H_kv, gq, c, qq, part, oo);
+    hipLaunchKernelGGL(kernel, grid, block, 0, stream, c.groups, c.n_quant, qq, c.Wq, c.S16, words.batch, words.heads, words.groups, words.magic, c, corr, part, oo);
   return hipGetLastError() == hipSuccess ? KVLINC_OK : KVLINC_EHIP;
 }
 
