@@ -793,12 +793,15 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
   constexpr int kRows = 4 * NB;  // logit rows of a sequence
   auto w_of = [&](int h) { return Wq + ((((long long)g * gq + h) * 2 + hs) * kHeadDim) * (kRank / 2) + fpart; };
   auto q_of = [&](int h) { return q + ((long long)(b_first + min(lane & 15, n_seq - 1)) * c.H_q + g * gq + h) * kHeadDim; };
+  // One or two sequences: two waves share each, a channel half a wave; otherwise a wave takes whole sequences.
+  const bool halves = n_seq <= 2;
+  const int s_first = halves ? wave >> 1 : wave, s_step = halves ? 2 : kWaves, hh_first = halves ? wave & 1 : 0;
   // S tiles and P of the wave's sequence
   uint2 sreg[2][kPartSteps];
   float4 p4;
-  auto request_state = [&](int s, int hh) {
+  auto request_state = [&](int s, int hh) {  // (hh: first or second of the wave's channel halves)
     const long long bh = (long long)(b_first + min(s, n_seq - 1)) * c.H_kv + g;
-    const half_t* tiles = S16 + bh * kRank * kHeadDim + state_tile(r, hh, 0) + 4 * lane;
+    const half_t* tiles = S16 + bh * kRank * kHeadDim + state_tile(r, halves ? hh_first : hh, 0) + 4 * lane;
 #pragma unroll
     for (int fs = 0; fs < kPartSteps; ++fs) sreg[hh][fs] = *reinterpret_cast<const uint2*>(tiles + fs * kStateTileHalfs);
     if (hh == 0) p4 = *reinterpret_cast<const float4*>(c.P + bh * kRank + kPartFeat * r + 4 * blk);
@@ -809,18 +812,18 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
       n_shares = 4;
       CorrWeights<1> x;
       request_weights<1>(x, w_of(0), q_of(0), wave, lane);
-      request_state(wave, 0);
+      request_state(s_first, 0);
       part_logits<1>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
     } else if (gq == 2) {
       n_shares = 2;
       CorrWeights<2> x;
       request_weights<2>(x, w_of(wave >> 1), q_of(wave >> 1), 2 * (wave & 1), lane);
-      request_state(wave, 0);
+      request_state(s_first, 0);
       part_logits<2>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
     } else {
       CorrWeights<4> x;
       if (wave < gq) request_weights<4>(x, w_of(wave), q_of(wave), 0, lane);
-      request_state(wave, 0);
+      request_state(s_first, 0);
       if (wave < gq) part_logits<4>(x, n_seq, 4 * kPartFeat, sLogit + wave * kPartFeat, lane);
     }
   } else {
@@ -829,14 +832,14 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
       const int h = min(hb * 4 + wave, gq - 1);
       CorrWeights<4> x;
       request_weights<4>(x, w_of(h), q_of(h), 0, lane);
-      if (hb == NB - 1) request_state(wave, 0);
+      if (hb == NB - 1) request_state(s_first, 0);
       part_logits<4>(x, n_seq, kRows * kPartFeat, sLogit + (hb * 4 + wave) * kPartFeat, lane);
     }
   }
-  request_state(wave, 1);
+  if (!halves) request_state(s_first, 1);
   barrier_lds_only();
   // ---- phase 2: the wave's sequences in turn, the four heads of a block; lane = (feature step fs = blk, head j) ----
-  for (int s = wave; s < n_seq; s += kWaves) {
+  for (int s = s_first; s < n_seq; s += s_step) {
     half4_t aop[NB];
     float cd[NB], mx[NB], z[NB];
 #pragma unroll
@@ -859,10 +862,11 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
       cd[hb] = quadgroup_allsum(fmaf(e0, p4.x, fmaf(e1, p4.y, fmaf(e2, p4.z, e3 * p4.w))));
       aop[hb] = half4_t{(half_t)e0, (half_t)e1, (half_t)e2, (half_t)e3};
     }
-    const bool more = s + kWaves < n_seq;
+    const bool more = s + s_step < n_seq;  // (never with halves)
     float4_t acc[NB][2];
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh) {
+      if (hh == 1 && halves) break;
       // (two chains per channel half)
 #pragma unroll
       for (int hb = 0; hb < NB; ++hb) {
@@ -874,7 +878,7 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
         }
         acc[hb][hh] = a0 + a1;
       }
-      if (more) request_state(s + kWaves, hh);
+      if (more) request_state(s + s_step, hh);
     }
     const int b = b_first + s;
 #pragma unroll
@@ -884,11 +888,11 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
       for (int i = 0; i < 4; ++i) {
         if (hb * 4 + i < gq) {
           float* dst = out0 + ((long long)i * kCorrParts + r) * kPartStride;
-          st_coherent(dst + 4 + lane, acc[hb][0][i]);
-          st_coherent(dst + 4 + 64 + lane, acc[hb][1][i]);
+          st_coherent(dst + 4 + 64 * hh_first + lane, acc[hb][0][i]);
+          if (!halves) st_coherent(dst + 4 + 64 + lane, acc[hb][1][i]);
         }
       }
-      if (blk == 0 && hb * 4 + j < gq) {
+      if (hh_first == 0 && blk == 0 && hb * 4 + j < gq) {
         float* dst = out0 + ((long long)j * kCorrParts + r) * kPartStride;
         st_coherent(dst, cd[hb]);
         st_coherent(dst + 1, mx[hb]);
@@ -901,123 +905,174 @@ __device__ __forceinline__ void correction_workgroup(const kvlinc_cache& c, cons
 // ---- merge the splits of one (sequence, query head), add the correction, rotate back (Alg. 1 lines 13-15; Eq. 5;
 // Sec. 3.1).  Run by one wave of the split that arrives last. ----------------------------------------------------------
 
+// The parts of each half of phi share one softmax: phi_f = e_f exp(m_r - M_hs) / Z_hs.  N channels a lane: cn += their C_n, cd += C_d.
+// p[r] = {Cd_r, m_r, Z_r, -}, x[r] = the lane's channels of Cn_r.
+template <int N>
+__device__ __forceinline__ void add_correction(const u32x4_t (&p)[kCorrParts], const float (&x)[kCorrParts][N], float (&cn)[N], float& cd) {
+#pragma unroll
+  for (int hs = 0; hs < 2; ++hs) {
+    float zsum = 0.f, Mh = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < kPartsPerHalf; ++i) {
+      zsum += as_f32(p[kPartsPerHalf * hs + i][2]);
+      Mh = fmaxf(Mh, as_f32(p[kPartsPerHalf * hs + i][1]));
+    }
+    float zz = 0.f, xx[N], dd = 0.f;
+#pragma unroll
+    for (int c = 0; c < N; ++c) xx[c] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kPartsPerHalf; ++i) {
+      const int rr = kPartsPerHalf * hs + i;
+      const float wgt = __expf(as_f32(p[rr][1]) - Mh);
+      zz = fmaf(wgt, as_f32(p[rr][2]), zz);
+      dd = fmaf(wgt, as_f32(p[rr][0]), dd);
+#pragma unroll
+      for (int c = 0; c < N; ++c) xx[c] = fmaf(wgt, x[rr][c], xx[c]);
+    }
+    const float inv = 1.0f / zz;
+    const bool any = zsum > 0.f;  // (selected, not multiplied away: what is left out may not be a number)
+    cd = any ? fmaf(dd, inv, cd) : cd;
+#pragma unroll
+    for (int c = 0; c < N; ++c) cn[c] = any ? fmaf(xx[c], inv, cn[c]) : cn[c];
+  }
+}
+// (num + 2^-M C_n) / (den + 2^-M C_d) with both factors kept <= 1 (M is the log2-domain maximum); the literal
+// form of Alg. 1's last lines leaves the factor 2^-M out.  M = -inf: no tokens, 0.
+template <int N>
+__device__ __forceinline__ void normalise(float (&n)[N], float den, const float (&cn)[N], float cd, float M, bool literal) {
+  const float Ms = fmaxf(M, 0.f);
+  const float fa = literal ? 1.0f : exp2f(M - Ms), fb = literal ? 1.0f : exp2f(-Ms);
+  const float inv = M != -INFINITY ? 1.0f / (fa * den + fb * cd) : 0.f;
+#pragma unroll
+  for (int c = 0; c < N; ++c) n[c] = M != -INFINITY ? (fa * n[c] + fb * cn[c]) * inv : 0.f;
+}
+constexpr float kRotation = 0.08838834764831845f;  // 1 / sqrt(128)
+constexpr int kPartBytes = kPartStride * 4;
+
+// More than kPairSplits splits: a row a wave.
 // Lane j holds (m, l) of split j, so that the weights of all splits come from one load and one reduction; the rows are
 // requested all at once, two splits per load, 16 bytes a lane.  (A walk over the splits in batches of 8 that each waited for
 // their own m took 4.5 us for the 30 splits of a sequence of 131072 tokens; a step 27.6 -> 25.0 us.)
-// NP: loads, at least n_splits / 2; LOCAL: the partial results are this workgroup's own and lie in LDS (plain loads, one split).
-// Lane l ends up with the channels 4 (l % 32) + 2 (l / 32), + 1.
-template <int NP, bool LOCAL = false>
-__device__ __forceinline__ void merge_row(const float* __restrict__ p0, const float* __restrict__ corr, int n_splits,
-                                          int row, int lane, bool literal, half_t* __restrict__ out) {
-  // p0: the row's partial results, n_splits of kPartStride floats
+// NP: loads, at least n_splits / 2.  Lane l ends up with the channels 4 (l % 32) + 2 (l / 32), + 1.
+// p0: the row's partial results, n_splits of kPartStride floats; corr: of all rows.
+template <int NP>
+__device__ __forceinline__ void merge_row(const float* __restrict__ p0, const float* __restrict__ corr, int n_splits, int row, int lane,
+                                          bool literal, half_t* __restrict__ out) {
   const int half = lane >> 5, ch0 = 4 * (lane & 31) + 2 * half;
-  // correction parts first (their values are needed last): {Cd_r, m_r, Z_r, -, Cn_r[128]}
-  float c_cd[kCorrParts], c_m[kCorrParts], c_z[kCorrParts], c_x[kCorrParts], c_y[kCorrParts];
-  if (corr != nullptr) {
+  u32x4_t cp[kCorrParts];
+  float cx[kCorrParts][2];
+  if (corr != nullptr) {  // (first: their values are needed last)
     const float* cr = corr + (long long)row * kCorrParts * kPartStride;
+    const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cr), 0, kCorrParts * kPartBytes, 0x00027000);
 #pragma unroll
     for (int r = 0; r < kCorrParts; ++r) {
-      const float* pr = cr + r * kPartStride;
-      const float2 cm = ld_coherent2(pr), z = ld_coherent2(pr + 2), xy = ld_coherent2(pr + 4 + ch0);
-      c_cd[r] = cm.x; c_m[r] = cm.y; c_z[r] = z.x;
-      c_x[r] = xy.x; c_y[r] = xy.y;
+      cp[r] = __builtin_amdgcn_raw_buffer_load_b128(parts, r * kPartBytes, 0, kCoherentLoad);
+      const float2 xy = ld_coherent2(cr + r * kPartStride + 4 + ch0);
+      cx[r][0] = xy.x; cx[r][1] = xy.y;
     }
   }
-  float2 ml;
+  const float2 ml = ld_coherent2(p0 + (long long)min(lane, n_splits - 1) * kPartStride);
   u32x4_t a[NP];
-  if (LOCAL) {
-    ml = make_float2(p0[0], p0[1]);
-  } else {
-    ml = ld_coherent2(p0 + (long long)min(lane, n_splits - 1) * kPartStride);
-    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p0), 0, n_splits * kPartStride * 4, 0x00027000);
+  const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p0), 0, n_splits * kPartBytes, 0x00027000);
 #pragma unroll
-    for (int k = 0; k < NP; ++k)
-      a[k] = __builtin_amdgcn_raw_buffer_load_b128(rows, min(2 * k + half, n_splits - 1) * (kPartStride * 4) + 16 + 16 * (lane & 31), 0, kCoherentLoad);
+  for (int k = 0; k < NP; ++k)
+    a[k] = __builtin_amdgcn_raw_buffer_load_b128(rows, min(2 * k + half, n_splits - 1) * kPartBytes + 16 + 16 * (lane & 31), 0, kCoherentLoad);
+  // (the lanes beyond n_splits hold a copy of the last split: its m does not change the maximum, its weight is cleared)
+  const float M = wave_allmax(ml.x);
+  const float w = lane < n_splits && ml.x != -INFINITY ? exp2f(ml.x - M) : 0.f;
+  const float den = wave_allsum(w * ml.y);
+  float n[4] = {0.f, 0.f, 0.f, 0.f}, y[2];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const float w0 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k)), w1 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k + 1));
+    const float wk = half != 0 ? w1 : w0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n[i] = fmaf(wk, as_f32(a[k][i]), n[i]);
   }
-  float M, den, n0 = 0.f, n1 = 0.f;
-  if (LOCAL) {
-    M = ml.x;
-    den = ml.y;
-    n0 = p0[4 + ch0]; n1 = p0[5 + ch0];
-  } else {
-    // (the lanes beyond n_splits hold a copy of the last split: its m does not change the maximum, its weight is cleared)
-    M = wave_allmax(ml.x);
-    const float w = lane < n_splits && ml.x != -INFINITY ? exp2f(ml.x - M) : 0.f;
-    den = wave_allsum(w * ml.y);
-    float n[4] = {0.f, 0.f, 0.f, 0.f};
+  // the even splits of the lower 32 lanes and the odd ones of the upper: the lower lanes finish the first two channels
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      const float w0 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k)), w1 = as_f32(__builtin_amdgcn_readlane(as_bits(w), 2 * k + 1));
-      const float wk = half != 0 ? w1 : w0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) n[i] = fmaf(wk, as_f32(a[k][i]), n[i]);
-    }
-    // the even splits of the lower 32 lanes and the odd ones of the upper: the lower lanes finish the first two channels
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const auto t = __builtin_amdgcn_permlane32_swap(as_bits(n[i]), as_bits(n[i + 2]), false, false);
-      (i == 0 ? n0 : n1) = as_f32(t[0]) + as_f32(t[1]);
-    }
+  for (int i = 0; i < 2; ++i) {
+    const auto t = __builtin_amdgcn_permlane32_swap(as_bits(n[i]), as_bits(n[i + 2]), false, false);
+    y[i] = as_f32(t[0]) + as_f32(t[1]);
   }
-  float y0 = 0.f, y1 = 0.f;
-  if (M != -INFINITY) {
-    float cn0 = 0.f, cn1 = 0.f, cd = 0.f;
-    if (corr != nullptr) {
-      // the parts of each half of phi share one softmax: phi_f = e_f exp(m_r - M_hs) / Z_hs
-#pragma unroll
-      for (int hs = 0; hs < 2; ++hs) {
-        float zsum = 0.f, Mh = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < kPartsPerHalf; ++i) {
-          zsum += c_z[kPartsPerHalf * hs + i];
-          Mh = fmaxf(Mh, c_m[kPartsPerHalf * hs + i]);
-        }
-        if (zsum > 0.f) {
-          float zz = 0.f, xx = 0.f, yy = 0.f, dd = 0.f;
-#pragma unroll
-          for (int i = 0; i < kPartsPerHalf; ++i) {
-            const int rr = kPartsPerHalf * hs + i;
-            const float wgt = __expf(c_m[rr] - Mh);
-            zz = fmaf(wgt, c_z[rr], zz);
-            xx = fmaf(wgt, c_x[rr], xx);
-            yy = fmaf(wgt, c_y[rr], yy);
-            dd = fmaf(wgt, c_cd[rr], dd);
-          }
-          const float inv = 1.0f / zz;
-          cn0 = fmaf(xx, inv, cn0);
-          cn1 = fmaf(yy, inv, cn1);
-          cd = fmaf(dd, inv, cd);
-        }
-      }
-    }
-    // (num + 2^-M C_n) / (den + 2^-M C_d) with both factors kept <= 1 (M is the log2-domain maximum); the literal
-    // form of Alg. 1's last lines leaves the factor 2^-M out
-    const float Ms = fmaxf(M, 0.f);
-    const float fa = literal ? 1.0f : exp2f(M - Ms), fb = literal ? 1.0f : exp2f(-Ms);
-    const float d = fa * den + fb * cd;
-    y0 = (fa * n0 + fb * cn0) / d;
-    y1 = (fa * n1 + fb * cn1) / d;
-  }
+  float cn[2] = {0.f, 0.f}, cd = 0.f;
+  if (corr != nullptr) add_correction<2>(cp, cx, cn, cd);
+  normalise<2>(y, den, cn, cd, M, literal);
   // y = y_rot H^T: butterflies over the 128 channels, two per lane (bit 1 of the channel is bit 5 of the lane)
-  {
-    float y[2] = {y0 + y1, y0 - y1};
-    lane_butterflies<2>(y, lane);
-    y0 = y[0]; y1 = y[1];
-  }
-  const half2_t r = {(half_t)(y0 * 0.08838834764831845f), (half_t)(y1 * 0.08838834764831845f)};
+  const float s = y[0] + y[1], d = y[0] - y[1];
+  y[0] = s; y[1] = d;
+  lane_butterflies<2>(y, lane);
+  const half2_t r = {(half_t)(y[0] * kRotation), (half_t)(y[1] * kRotation)};
   *reinterpret_cast<uint32_t*>(out + (long long)row * kHeadDim + ch0) = as_u32(r);
 }
 
-constexpr int kMaxSplits = 32;  // splits a sequence may take at most: a lane of the merge, and a pair of its registers, each
-__device__ __forceinline__ void merge_rows(const float* __restrict__ part, const float* __restrict__ corr,
-                                           int max_splits, int n_splits, int row, int lane, bool literal,
-                                           half_t* __restrict__ out) {
-  const float* p0 = part + (long long)row * max_splits * kPartStride;
-  if (n_splits <= 4) merge_row<2>(p0, corr, n_splits, row, lane, literal, out);
-  else if (n_splits <= 12) merge_row<6>(p0, corr, n_splits, row, lane, literal, out);
-  else merge_row<kMaxSplits / 2>(p0, corr, n_splits, row, lane, literal, out);
+// Up to kPairSplits splits: two rows a wave, one in each half, four channels a lane -- the instructions of one row.  row: the first
+// of two heads of a sequence (has_two: there is a second one).  own: the rows' only partial results are this workgroup's and lie in
+// LDS, row after row; otherwise p0 as in merge_row, max_splits from one row to the next.
+// Bound: latency, of the trip to memory and of code that few workgroups of a launch run, cold; so it is there once, for both kinds
+// of workgroups, and short.  With a copy in each, one row at a time, a correction workgroup that arrived last at its sequences took
+// 3 to 10 us for them, and launches where the streaming workgroups are the faster ones up to 1.5 times as long.
+constexpr int kPairSplits = 4;
+__device__ __forceinline__ void merge_pair(const float* __restrict__ p0, const float* own, const float* __restrict__ corr, int n_splits,
+                                           int max_splits, int row, bool has_two, int lane, bool literal, half_t* __restrict__ out) {
+  const int second = has_two ? lane >> 5 : 0, l32 = lane & 31, ch0 = 4 * l32;
+  u32x4_t cp[kCorrParts];
+  float cx[kCorrParts][4];
+  if (corr != nullptr) {
+    const float* cr = corr + (long long)row * kCorrParts * kPartStride;
+    const __amdgpu_buffer_rsrc_t parts = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(cr), 0, 2 * kCorrParts * kPartBytes, 0x00027000);
+#pragma unroll
+    for (int r = 0; r < kCorrParts; ++r) {
+      cp[r] = __builtin_amdgcn_raw_buffer_load_b128(parts, second * (kCorrParts * kPartBytes) + r * kPartBytes, 0, kCoherentLoad);
+      const u32x4_t x = __builtin_amdgcn_raw_buffer_load_b128(parts, second * (kCorrParts * kPartBytes) + 16 * l32 + 16 + r * kPartBytes, 0, kCoherentLoad);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cx[r][i] = as_f32(x[i]);
+    }
+  }
+  float M, den, n[4];
+  if (own != nullptr) {
+    const float* mine = own + second * kPartStride;
+    M = mine[0];
+    den = mine[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n[i] = mine[4 + ch0 + i];
+  } else {
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p0), 0, (has_two ? 2 : 1) * max_splits * kPartBytes, 0x00027000);
+    float2 ml[kPairSplits];
+    u32x4_t a[kPairSplits];
+#pragma unroll
+    for (int k = 0; k < kPairSplits; ++k) {
+      const int at = min(k, n_splits - 1) * kPartBytes;
+      const auto t = __builtin_amdgcn_raw_buffer_load_b64(rows, second * (max_splits * kPartBytes), at, kCoherentLoad);
+      ml[k] = make_float2(as_f32(t[0]), as_f32(t[1]));
+      a[k] = __builtin_amdgcn_raw_buffer_load_b128(rows, second * (max_splits * kPartBytes) + 16 * l32 + 16, at, kCoherentLoad);
+    }
+    M = fmaxf(fmaxf(ml[0].x, ml[1].x), fmaxf(ml[2].x, ml[3].x));  // (a copy of the last split in place of those that do not exist)
+    den = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n[i] = 0.f;
+#pragma unroll
+    for (int k = 0; k < kPairSplits; ++k) {
+      const float w = k < n_splits && ml[k].x != -INFINITY ? exp2f(ml[k].x - M) : 0.f;
+      den = fmaf(w, ml[k].y, den);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) n[i] = fmaf(w, as_f32(a[k][i]), n[i]);
+    }
+  }
+  float cn[4] = {0.f, 0.f, 0.f, 0.f}, cd = 0.f;
+  if (corr != nullptr) add_correction<4>(cp, cx, cn, cd);
+  normalise<4>(n, den, cn, cd, M, literal);
+  // y = y_rot H^T: the first two stages in the lane, the others between the 32 lanes of the row
+  {
+    const float a0 = n[0] + n[1], a1 = n[0] - n[1], a2 = n[2] + n[3], a3 = n[2] - n[3];
+    n[0] = a0 + a2; n[1] = a1 + a3; n[2] = a0 - a2; n[3] = a1 - a3;
+  }
+  row_butterflies<4>(n, lane);
+  const half2_t r0 = {(half_t)(n[0] * kRotation), (half_t)(n[1] * kRotation)}, r1 = {(half_t)(n[2] * kRotation), (half_t)(n[3] * kRotation)};
+  *reinterpret_cast<uint2*>(out + (long long)(row + second) * kHeadDim + ch0) = make_uint2(as_u32(r0), as_u32(r1));
 }
 
+constexpr int kMaxSplits = 32;  // splits a sequence may take at most: a lane of the merge, and a pair of its registers, each
 // Splits the groups of a sequence are cut into.  The host fixes the average over the batch (avg_splits) and the most
 // one sequence may take (max_splits; grid and workspace are sized for it).  A sequence takes its share of
 // B * avg_splits in proportion to its number of groups, rounded up from a quarter on, so that the long and the short
@@ -1096,7 +1151,7 @@ __device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
 struct LaunchWords {
   uint32_t batch;   // B - 1, splits of a sequence on average << 24, window requested early << 30, correction on << 31
   uint32_t heads;   // H_kv - 1, most splits of a sequence << 24, runs of the grid that the correction leads << 30
-  uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, eight sequences a correction workgroup << 27
+  uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, log2 of the sequences of a correction workgroup << 27
   uint32_t magic;   // ceil(2^32 / H_kv), or 0 where that does not give quotients by H_kv
 };
 constexpr uint32_t kLow24 = (1u << 24) - 1u;
@@ -1108,7 +1163,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
                                                                    float* __restrict__ corr, float* __restrict__ part, half_t* __restrict__ out) {
   const LaunchWords words = {batch_word, heads_word, groups_word, magic};
   const int max_splits = (words.heads >> 24) & 63, avg_splits = (words.batch >> 24) & 63, L = words.heads >> 30, gq = ((words.groups >> 24) & 7) + 1;
-  const int log_seqs = 2 + ((words.groups >> 27) & 1), corr_seqs = 1 << log_seqs;
+  const int log_seqs = (words.groups >> 27) & 3, corr_seqs = 1 << log_seqs;
   const bool early_window = (words.batch >> 30) & 1, has_corr = words.batch >> 31;
   kvlinc_cache c = cache;
   c.groups = groups; c.n_quant = n_quant; c.Wq = Wq; c.S16 = S16;
@@ -1149,6 +1204,13 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     stream_id = blockIdx.x - before;
   }
 
+  // What is left to merge when the workgroup has done its part: the sequences done (bit s: sequence m_first + s) of kv head m_g, of
+  // as many splits as the bytes of `splits` say.
+  int m_first, m_g;
+  uint32_t done = 0;
+  uint64_t splits = 0;
+  bool direct = false;
+
   if (is_corr) {
     // ---- one part of the correction (Sec. 3.3: C_n, C_d) for up to corr_seqs sequences of one kv head ----
     const int id = corr_id;
@@ -1172,18 +1234,14 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
       sFlags[tid] = __hip_atomic_fetch_add(c.split_done + (b_first + tid) * c.H_kv + g, 1, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_SYSTEM);
     __syncthreads();
+    m_first = b_first;
+    m_g = g;
     for (int s = 0; s < n_seq; ++s) {
-      const int b = b_first + s, bh = b * c.H_kv + g;
       const int n_splits = sequence_splits(c, groups_of(__builtin_amdgcn_readlane(nq_mine, s)), total, avg_splits, max_splits, lane);
-      if (sFlags[s] == n_splits + n_parts - 1) {
-        for (int h = wave; h < gq; h += kWaves)
-          merge_rows(part, corr, max_splits, n_splits, b * c.H_q + g * gq + h, lane, (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);
-        if (tid == 0) c.split_done[bh] = 0;
-      }
+      splits |= (uint64_t)n_splits << (8 * s);
+      if (__builtin_amdgcn_readfirstlane(sFlags[s]) == n_splits + n_parts - 1) done |= 1u << s;
     }
-    return;
-  }
-
+  } else {
   // ---- one split of the groups and of the window (Alg. 1, the loop over blocks) ----
   const int wg = stream_id;
   // split-major: the splits that only long sequences use come last in the grid, and the workgroups of any one split
@@ -1377,7 +1435,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
       sAcc[wave][h][16 * n + lr.jd] = st.acc[nb][n] + pz;
   }
   __syncthreads();
-  const bool direct = sDirect != 0;
+  direct = __builtin_amdgcn_readfirstlane(sDirect) != 0;
   // (a wave takes whole heads, a lane two channels: the weights of the four waves are formed once a head)
   float* own = reinterpret_cast<float*>(&ex[0][0]);  // [gq][kPartStride]: the exchange regions are free by now
   for (int h = wave; h < gq; h += kWaves) {
@@ -1405,21 +1463,37 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
       st_coherent2(dst + 4 + 2 * lane, a0, a1);
     }
   }
+  m_first = b;
+  m_g = g;
+  splits = n_splits;
   if (direct) {
-    lds_order();  // (a wave merges the heads that it has combined)
-    for (int h = wave; h < gq; h += kWaves)
-      merge_row<1, true>(own + h * kPartStride, corr, 1, b * c.H_q + g * gq + h, lane,
-                         (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);
-    if (tid == 0 && n_parts != 0) c.split_done[bh] = 0;  // the arrivals of the correction workgroups
-    return;
+    barrier_lds_only();
+    done = 1;
+  } else {
+    // The workgroup that arrives last merges (Alg. 1 lines 13-15): it reads what the others wrote with coherent
+    // loads.  No workgroup waits for another.
+    done = arrive(c.split_done + bh, expected, &sFlag) ? 1 : 0;
+  }
   }
 
-  // The workgroup that arrives last merges (Alg. 1 lines 13-15): it reads what the others wrote with coherent
-  // loads.  No workgroup waits for another.
-  if (arrive(c.split_done + bh, expected, &sFlag)) {
-    for (int h = wave; h < gq; h += kWaves)
-      merge_rows(part, corr, max_splits, n_splits, b * c.H_q + g * gq + h, lane, (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0, out);
-    if (tid == 0) c.split_done[bh] = 0;
+  // ---- merge (Alg. 1 lines 13-15) ----
+  const bool literal = (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0;
+  int turn = 0;
+  for (uint32_t left = done; left != 0; left &= left - 1) {
+    const int s = __builtin_ctz(left), n_splits = (int)(splits >> (8 * s)) & 255, row0 = (m_first + s) * c.H_q + m_g * gq;
+    if (n_splits <= kPairSplits) {
+      for (int h = 0; h < gq; h += 2, ++turn)
+        if (turn % kWaves == wave)
+          merge_pair(part + (long long)(row0 + h) * max_splits * kPartStride, direct ? reinterpret_cast<float*>(&ex[0][0]) + h * kPartStride : nullptr, corr,
+                     n_splits, max_splits, row0 + h, h + 1 < gq, lane, literal, out);
+    } else {
+      for (int h = wave; h < gq; h += kWaves) {
+        const float* p0 = part + (long long)(row0 + h) * max_splits * kPartStride;
+        if (n_splits <= 12) merge_row<6>(p0, corr, n_splits, row0 + h, lane, literal, out);
+        else merge_row<kMaxSplits / 2>(p0, corr, n_splits, row0 + h, lane, literal, out);
+      }
+    }
+    if (tid == 0) c.split_done[(m_first + s) * c.H_kv + m_g] = 0;
   }
 }
 
@@ -1494,11 +1568,24 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // 1 to 32 kv heads: 1471 shapes, twice.)
   // A single sequence is left on units of its own and 30 splits, the stated policy for it: 131072 tokens, 8 kv heads, 20.5 us a
   // launch, where 32 splits with the correction last would take 19.9.
+  // One or two sequences a correction workgroup instead of 4 where that gives no compute unit another workgroup: two or four waves
+  // share a sequence then, and a workgroup that arrives last has fewer rows to merge.  Decode launches with the fewest that fit so,
+  // against 4, on average (0.1 to 0.3 of the time between single shapes, either way): on one workgroup per unit 0.94 to 1.00 (1
+  // head in 32 to 8 in 8, one split), 0.99 to 1.01 (more splits); on two 0.88 to 0.98; on three 0.98.  A unit more: 1.04 to 1.35.
+  // (4 bits, where a unit holds two: 2 sequences rather than 1 on two, 0.98 against 1.01.)
+  auto launch = [&](long long avg, long long most_splits, int first) {
+    int seqs = corr_seqs;
+    const long long per_unit = (bh * avg + corr_workgroups(4) + 255) / 256;
+    if (seqs == 4 && per_unit <= (c.bits == 2 ? 3 : 2))
+      for (int k = 2; k >= (c.bits == 4 && per_unit == 2 ? 2 : 1); --k)
+        if (bh * avg + corr_workgroups(k) <= 256 * per_unit) seqs = k;
+    return DecodeSplits{(int)avg, (int)most_splits, first, seqs};
+  };
   if (all_corr > 0 && bh * s <= 256 && bh * s + all_corr > 256) {
     const long long s2 = (256 - (all_corr + 1) / 2) / bh;
     const bool own_units = s2 >= 1 && 4 * s2 >= 3 * s;
     const bool long_enough = s == 1 ? gq >= 2 && groups >= 24 : s >= (gq > 4 ? 4 : 2) && (own_units || gq <= 2);
-    if (c.bits == 2 && c.B > 1 && long_enough) return DecodeSplits{(int)s, (int)m, 0, corr_seqs};
+    if (c.bits == 2 && c.B > 1 && long_enough) return launch(s, m, 0);
     if (own_units) {
       s = s2 < s ? s2 : s;
       if (m > s) m = c.B > 1 ? 2 * s : s;
@@ -1508,7 +1595,7 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
       corr_first = 2;
     }
   }
-  return DecodeSplits{(int)s, (int)m, corr_first, corr_seqs};
+  return launch(s, m, corr_first);
 }
 
 size_t decode_workspace_floats(const kvlinc_cache& c, int n_splits) {
@@ -1537,7 +1624,7 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
   const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)early_window << 30 | (uint32_t)(corr != nullptr) << 31,
                              (uint32_t)(c.H_kv - 1) | (uint32_t)sp.most << 24 | (uint32_t)L << 30,
-                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)(sp.corr_seqs == 8) << 27, magic};
+                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(sp.corr_seqs) << 27, magic};
   const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
   void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)

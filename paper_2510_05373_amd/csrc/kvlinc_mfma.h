@@ -77,9 +77,9 @@ __device__ __forceinline__ float wave_allsum(float v) {
 // combine of the decode workgroups: a step of 1 sequence of 300 tokens 12.7 -> 12.1 us, 16 of 8k 25.9 -> 25.3, 1 of 131072
 // 25.1 -> 24.5.)  NV vectors at once.
 template <int NV>
-__device__ __forceinline__ void lane_butterflies(float (&v)[NV], int lane) {
+__device__ __forceinline__ void row_butterflies(float (&v)[NV], int lane) {  // strides 1 .. 16: inside the halves of a wave
   auto sign = [&](int bit) { return (lane & bit) != 0 ? -1.0f : 1.0f; };
-  const float s1 = sign(1), s2 = sign(2), s4 = sign(4), s8 = sign(8), s16 = sign(16), s32 = sign(32);
+  const float s1 = sign(1), s2 = sign(2), s4 = sign(4), s8 = sign(8), s16 = sign(16);
 #pragma unroll
   for (int u = 0; u < NV; ++u) v[u] = __builtin_fmaf(v[u], s1, dpp_f<kQuadSwap1>(v[u]));
 #pragma unroll
@@ -94,6 +94,11 @@ __device__ __forceinline__ void lane_butterflies(float (&v)[NV], int lane) {
     pair_across<16>(v[u], x, y);
     v[u] = __builtin_fmaf(y, s16, x);
   }
+}
+template <int NV>
+__device__ __forceinline__ void lane_butterflies(float (&v)[NV], int lane) {
+  row_butterflies<NV>(v, lane);
+  const float s32 = (lane & 32) != 0 ? -1.0f : 1.0f;
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
     float x, y;
