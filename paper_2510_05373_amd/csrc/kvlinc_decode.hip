@@ -8,11 +8,12 @@
 //   parts, each requested again for the wave's next group as soon as its contraction has consumed it.  The four
 //   waves of split 0 of a (sequence, kv head) also take a share of the fp16 window each, as one more block of tokens.  The
 //   waves are combined through LDS and the workgroup writes one (m, l, Y_s) per query head (Alg. 1 line 11);
-//   correction workgroups (kv head, part of phi, 4 or 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
+//   correction workgroups (kv head, part of phi, 1 to 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
 //   the rows of S, on the matrix cores.
-// Every workgroup counts itself in at its (sequence, kv head); the one that arrives last merges, one wave per query
-// head: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
-// H^T and stores fp16 (Alg. 1 lines 13-15 with Eq. 5).  No workgroup waits for another.
+// Every workgroup counts itself in at its (sequence, kv head); the streaming workgroup that arrives last, or the correction
+// workgroup where that is later and not awaited (see kCorrArrival), merges: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
+// H^T and stores fp16 (Alg. 1 lines 13-15 with Eq. 5).  Every wait is bounded: what it waited for is left to
+// whoever comes last then.
 //
 // The two contractions of a group (Alg. 1 lines 5-10) run on v_mfma_scale_f32_16x16x128_f8f6f4, 16 rows x 16 columns x
 // 128 contraction positions per instruction, 8 instructions per contraction and block of 4 query heads:
@@ -598,8 +599,7 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 //           role (lane kk of the quad), so that A comes from qh by broadcasts inside the quads;
 //   E V   : columns = 16 channels, positions = 32 tokens: lane (hd, jd) has tokens 8 hd + 0..7, two 4-slot pieces of v_res.
 // Runs before the wave's first group, on empty state.  Bound: latency and, where many short sequences fill the chip, bytes: what
-// lies beyond the window's tokens is not read (lanes without a token take the last one's rows), unless the launch is so small
-// that the whole window is requested ahead of the counters (see launch_decode).
+// lies beyond the window's tokens is not read (lanes without a token take the last one's rows).
 // Two waves with 64 tokens each, on the 4x4x4 blocks, waited for their first record, then for the keys (each a 16-byte piece of
 // 64 lines, in 16 instructions), then for the values, then for q.  Steps before and after (with the requests laid out as they are in
 // the kernel below): 144 sequences of 1280 tokens 70.7 -> 64.0 us, 32 x 32 single heads of 1280 45.4 -> 42.0, one sequence of
@@ -608,9 +608,16 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 struct WindowShare {
   int first, end;  // tokens first .. end - 1, at most 32 and first a multiple of 4; none: end <= first
 };
-__device__ __forceinline__ WindowShare window_share(int nr, int wave) {
-  const int per = 4 * ((nr + 4 * kWaves - 1) / (4 * kWaves));
-  return WindowShare{per * wave, min(per * (wave + 1), nr)};
+// k of the waves share, the last ones: as many as have no group in the last round of a sequence with one split (count: its groups),
+// as many as are needed, or all.  (Four waves always, and the whole window requested ahead of the counters in small launches: 0.9265
+// instead of 0.9200 of the time of two waves with 64 tokens each, on average over some 4900 decode launches.)
+__device__ __forceinline__ WindowShare window_share(int nr, int count, bool one_split, int wave) {
+  int k = one_split ? -count & (kWaves - 1) : 0;
+  k = max(k == 0 ? kWaves : k, (nr + 31) / 32);
+  const int fours = (nr + 3) / 4;  // at most 32: exact below
+  const int per = 4 * (k == 4 ? (fours + 3) >> 2 : k == 3 ? ((fours + 2) * 171) >> 9 : k == 2 ? (fours + 1) >> 1 : fours);
+  const int at = per * (wave - (kWaves - k));
+  return WindowShare{max(at, 0), min(at + per, nr)};  // (at < 0: empty, for at + per <= 0)
 }
 struct WindowRegs {
   uint4 k[2][4];  // [tt][kk]
@@ -1127,14 +1134,34 @@ __device__ __forceinline__ int sequence_splits(const kvlinc_cache& c, int count,
   return __builtin_amdgcn_readfirstlane(max(s, 1));            // the same in every lane: keep it in a scalar register
 }
 
-// Arrival of a workgroup at its (sequence, kv head): every wave first waits until its write-through stores have been
-// acknowledged, then one thread counts the workgroup in.  Returns true in the workgroup that completes the count.
-__device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
+// What arrives at a (sequence, kv head): its streaming workgroups, 1 each, and those of the correction, kCorrArrival each.
+// Who merges: the streaming workgroup that completes the streaming ones, if the correction is complete; otherwise, where the launch
+// says that the correction is awaited -- its workgroups run already or are done --, the same workgroup, which looks at the
+// counter until it is, up to kLooks times; or else the correction workgroup that completes the count.  A streaming workgroup
+// that gives up leaves kGaveUp in the counter: whoever adds to it last, it or the correction, sees the other and merges.
+// (A correction workgroup has the rows of up to 8 sequences to merge, a streaming workgroup those of one, which the single split of a
+// sequence has in LDS besides: see launch_decode for what awaiting gives.  Looks without s_sleep(16) between them, 2 instead: 1.002
+// of the time on average and 1.30 instead of 1.27 at most; 48: 1.003.)
+constexpr int kCorrArrival = 64, kGaveUp = 1 << 16, kLooks = 64;
+__device__ __forceinline__ int streams_arrived(int count) { return count & (kCorrArrival - 1); }
+__device__ __forceinline__ int parts_arrived(int count) { return (count & (kGaveUp - 1)) / kCorrArrival; }
+
+// Arrival of a streaming workgroup: every wave first waits until its write-through stores have been
+// acknowledged, then one thread counts the workgroup in.  Returns the counter as it was before.
+__device__ __forceinline__ int arrive(int* counter, int* sFlag) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) *sFlag = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   __syncthreads();
-  return *sFlag == expected - 1;
+  return __builtin_amdgcn_readfirstlane(*sFlag);
+}
+// One thread looks at the counter until all parts of the correction have arrived, a bounded number of times.
+__device__ __forceinline__ bool await_parts(int* counter, int n_parts) {
+  for (int i = 0; i < kLooks; ++i) {
+    if (parts_arrived(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts) return true;
+    __builtin_amdgcn_s_sleep(16);  // (about half a microsecond: more looks get in the way of the arrivals they wait for)
+  }
+  return false;
 }
 
 // Grid: B H_kv max_splits streaming workgroups, split-major (workgroup = split * B H_kv + sequence * H_kv + kv head),
@@ -1149,7 +1176,7 @@ __device__ __forceinline__ bool arrive(int* counter, int expected, int* sFlag) {
 // What the way to the first requests takes comes in 14 words, which are in scalar registers when a wave starts (see
 // append_token_kernel): five pointers, and counts that stay below 2^24 with small numbers above them.
 struct LaunchWords {
-  uint32_t batch;   // B - 1, splits of a sequence on average << 24, window requested early << 30, correction on << 31
+  uint32_t batch;   // B - 1, splits of a sequence on average << 24, correction awaited << 30, on << 31
   uint32_t heads;   // H_kv - 1, most splits of a sequence << 24, runs of the grid that the correction leads << 30
   uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, log2 of the sequences of a correction workgroup << 27
   uint32_t magic;   // ceil(2^32 / H_kv), or 0 where that does not give quotients by H_kv
@@ -1164,7 +1191,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   const LaunchWords words = {batch_word, heads_word, groups_word, magic};
   const int max_splits = (words.heads >> 24) & 63, avg_splits = (words.batch >> 24) & 63, L = words.heads >> 30, gq = ((words.groups >> 24) & 7) + 1;
   const int log_seqs = (words.groups >> 27) & 3, corr_seqs = 1 << log_seqs;
-  const bool early_window = (words.batch >> 30) & 1, has_corr = words.batch >> 31;
+  const bool has_corr = words.batch >> 31, awaited = (words.batch >> 30) & 1;
   kvlinc_cache c = cache;
   c.groups = groups; c.n_quant = n_quant; c.Wq = Wq; c.S16 = S16;
   c.max_groups = (int)(words.groups & kLow24) + 1; c.B = (int)(words.batch & kLow24) + 1; c.H_kv = (int)(words.heads & kLow24) + 1; c.H_q = gq * c.H_kv;
@@ -1231,7 +1258,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     __syncthreads();
     int* sFlags = reinterpret_cast<int*>(lds);
     if (tid < n_seq)
-      sFlags[tid] = __hip_atomic_fetch_add(c.split_done + (b_first + tid) * c.H_kv + g, 1, __ATOMIC_RELAXED,
+      sFlags[tid] = __hip_atomic_fetch_add(c.split_done + (b_first + tid) * c.H_kv + g, kCorrArrival, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_SYSTEM);
     __syncthreads();
     m_first = b_first;
@@ -1239,7 +1266,8 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     for (int s = 0; s < n_seq; ++s) {
       const int n_splits = sequence_splits(c, groups_of(__builtin_amdgcn_readlane(nq_mine, s)), total, avg_splits, max_splits, lane);
       splits |= (uint64_t)n_splits << (8 * s);
-      if (__builtin_amdgcn_readfirstlane(sFlags[s]) == n_splits + n_parts - 1) done |= 1u << s;
+      const int before = __builtin_amdgcn_readfirstlane(sFlags[s]);
+      if (parts_arrived(before) == n_parts - 1 && streams_arrived(before) == n_splits && (!awaited || before >= kGaveUp)) done |= 1u << s;
     }
   } else {
   // ---- one split of the groups and of the window (Alg. 1, the loop over blocks) ----
@@ -1323,9 +1351,9 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     plan();
     request_record(true);
     asm volatile("" ::: "memory");
-    WindowShare sh = window_share(early_window ? c.R : scalar_load(c.n_res + b), wave);
+    const WindowShare sh = window_share(scalar_load(c.n_res + b), groups_of(scalar_load(c.n_quant + b)), avg_splits == 1, wave);
     WindowRegs w;
-    request_window(w, c, bh, sh, lr);
+    if (sh.first < sh.end) request_window(w, c, bh, sh, lr);
     asm volatile("" ::: "memory");
     const int mine = splits_of_sequence(counters);
     if (mine != n_splits) {
@@ -1333,7 +1361,6 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
       plan();
       request_record(false);
     }
-    sh.end = min(sh.end, nr);
     if (sh.first < sh.end) window_part<NB>(w, qh, sh, lr, st);
     else empty_state<NB>(st);
     // (nothing is under way any more: registers that a load may still write make the compiler wait in every round of the loop over
@@ -1368,7 +1395,6 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   // way behind it, the next record among it.
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) asm volatile("" : "+v"(qh[nb][0]), "+v"(qh[nb][1]), "+v"(qh[nb][2]), "+v"(qh[nb][3]));
-  const int expected = n_splits + n_parts;
 
   float (*sM)[NB * 4] = reinterpret_cast<float (*)[NB * 4]>(lds);                    // [kWaves][NB*4]
   float (*sL)[NB * 4] = reinterpret_cast<float (*)[NB * 4]>(lds + kWaves * NB * 4);  // [kWaves][NB*4]
@@ -1412,17 +1438,12 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     }
   }
 
-  // A sequence with a single split whose correction parts have all arrived has nobody left to wait for: its one
-  // workgroup then merges what it holds, without the trip of its partial result through memory.  The look at the
-  // counter is taken here so that its latency passes during the combine; a look that comes too early only sends the
-  // workgroup down the ordinary way.
+  // A sequence with a single split merges what its one workgroup holds, without the trip of its partial result through memory, when
+  // the correction parts have all arrived (or the correction is off) or are awaited.  The first look at the counter is taken here
+  // so that its latency passes during the combine.
   __shared__ int sDirect;
-  if (tid == 0) {
-    int direct = 0;
-    if (n_splits == 1)
-      direct = n_parts == 0 ? 1 : (__hip_atomic_load(c.split_done + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) == n_parts);
-    sDirect = direct;
-  }
+  if (tid == 0)
+    sDirect = n_splits == 1 && (n_parts == 0 || parts_arrived(__hip_atomic_load(c.split_done + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts);
   // combine the four waves (Alg. 1 lines 13-14 restricted to this workgroup) and write (m, l, Y_s)
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -1436,6 +1457,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   }
   __syncthreads();
   direct = __builtin_amdgcn_readfirstlane(sDirect) != 0;
+  const bool keep = direct || (awaited && n_splits == 1);  // the result stays here for now
   // (a wave takes whole heads, a lane two channels: the weights of the four waves are formed once a head)
   float* own = reinterpret_cast<float*>(&ex[0][0]);  // [gq][kPartStride]: the exchange regions are free by now
   for (int h = wave; h < gq; h += kWaves) {
@@ -1453,7 +1475,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
         l = fmaf(f, sL[w][h], l);
       }
     }
-    if (direct) {
+    if (keep) {
       float* dst = own + h * kPartStride;
       if (lane == 0) { dst[0] = M; dst[1] = l; }
       *reinterpret_cast<float2*>(dst + 4 + 2 * lane) = make_float2(a0, a1);
@@ -1466,13 +1488,41 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   m_first = b;
   m_g = g;
   splits = n_splits;
-  if (direct) {
+  int* const counter = c.split_done + bh;
+  if (keep) {
     barrier_lds_only();
+    if (!direct) {
+      if (tid == 0) sDirect = await_parts(counter, n_parts);
+      barrier_lds_only();
+      direct = __builtin_amdgcn_readfirstlane(sDirect) != 0;
+    }
+    if (!direct) {  // given up: the result goes to memory after all
+      for (int h = wave; h < gq; h += kWaves) {
+        const float* src = own + h * kPartStride;
+        float* dst = part + ((long long)b * c.H_q + g * gq + h) * max_splits * kPartStride;
+        if (lane == 0) st_coherent2(dst, src[0], src[1]);
+        st_coherent2(dst + 4 + 2 * lane, src[4 + 2 * lane], src[5 + 2 * lane]);
+      }
+    }
+  }
+  if (direct) {
     done = 1;
   } else {
-    // The workgroup that arrives last merges (Alg. 1 lines 13-15): it reads what the others wrote with coherent
-    // loads.  No workgroup waits for another.
-    done = arrive(c.split_done + bh, expected, &sFlag) ? 1 : 0;
+    // The workgroup that completes the count merges (Alg. 1 lines 13-15): it reads what the others wrote with coherent loads.
+    const int before = arrive(counter, &sFlag);
+    if (streams_arrived(before) == n_splits - 1) {
+      bool complete = parts_arrived(before) == n_parts;
+      if (!complete && awaited) {
+        if (tid == 0) {
+          bool there = await_parts(counter, n_parts);
+          if (!there) there = parts_arrived(__hip_atomic_fetch_add(counter, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts;
+          sFlag = there;
+        }
+        barrier_lds_only();
+        complete = __builtin_amdgcn_readfirstlane(sFlag) != 0;
+      }
+      done = complete ? 1 : 0;
+    }
   }
   }
 
@@ -1569,15 +1619,16 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // A single sequence is left on units of its own and 30 splits, the stated policy for it: 131072 tokens, 8 kv heads, 20.5 us a
   // launch, where 32 splits with the correction last would take 19.9.
   // One or two sequences a correction workgroup instead of 4 where that gives no compute unit another workgroup: two or four waves
-  // share a sequence then, and a workgroup that arrives last has fewer rows to merge.  Decode launches with the fewest that fit so,
-  // against 4, on average (0.1 to 0.3 of the time between single shapes, either way): on one workgroup per unit 0.94 to 1.00 (1
-  // head in 32 to 8 in 8, one split), 0.99 to 1.01 (more splits); on two 0.88 to 0.98; on three 0.98.  A unit more: 1.04 to 1.35.
-  // (4 bits, where a unit holds two: 2 sequences rather than 1 on two, 0.98 against 1.01.)
+  // share a sequence then, and a workgroup that arrives last has fewer rows to merge.  More splits than one, decode launches with the
+  // fewest that fit so, against 4, on average (0.1 to 0.3 of the time between single shapes, either way): 0.99 to 1.01 on one workgroup
+  // per unit, 0.88 to 0.98 on two, 0.98 on three.  A unit more: 1.04 to 1.35.  (4 bits, where a unit holds two: 2 sequences rather
+  // than 1 on two, 0.98 against 1.01.)  One split (7700 shapes of up to 1100 tokens): 2 sequences where all workgroups have a unit of
+  // their own, 0.97 and 0.98 of the time of 4, 1 sequence 1.01; beyond that 2 take 1.02.
   auto launch = [&](long long avg, long long most_splits, int first) {
     int seqs = corr_seqs;
     const long long per_unit = (bh * avg + corr_workgroups(4) + 255) / 256;
-    if (seqs == 4 && per_unit <= (c.bits == 2 ? 3 : 2))
-      for (int k = 2; k >= (c.bits == 4 && per_unit == 2 ? 2 : 1); --k)
+    if (seqs == 4 && per_unit <= (avg == 1 ? 1 : c.bits == 2 ? 3 : 2))
+      for (int k = 2; k >= (avg == 1 || (c.bits == 4 && per_unit == 2) ? 2 : 1); --k)
         if (bh * avg + corr_workgroups(k) <= 256 * per_unit) seqs = k;
     return DecodeSplits{(int)avg, (int)most_splits, first, seqs};
   };
@@ -1612,20 +1663,21 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   float* part = workspace;
   float* corr = c.S16 != nullptr ? workspace + (size_t)c.B * c.H_q * n_splits * kPartStride : nullptr;
   const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + sp.corr_seqs - 1) / sp.corr_seqs) : 0;
+  const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
   const dim3 grid(BH * n_splits + n_corr), block(kThreads);
   // every run that leads with correction workgroups must lie inside the grid and hold its share
   int L = n_corr != 0 ? sp.corr_first : 0;
   while (L > 1 && ((int)grid.x < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
-  // The whole window ahead of the counters where no compute unit has a second workgroup: one sequence of 300 tokens 10.9 us a step,
-  // 11.5 behind them; beyond that the bytes that are not needed cost as much or more (one sequence of 131072 tokens, 272 workgroups,
-  // the same, 16 of 8k 25.1 against 24.7 us).
-  const bool early_window = (long long)BH * sp.avg + n_corr <= 256;
+  // The correction is awaited where its workgroups come first, or all of the launch is on the chip at once; not by more than 256
+  // sequences and heads with one split each, whose looks crowd the counters.  Over 4940 random shapes, as a part of the time of a
+  // merge by whoever arrives last (mean, worst): one split and up to 256 of them 0.90, 1.20 awaited and 0.94, 1.39 not, beyond 256
+  // 0.92, 1.27 and 0.92, 1.17; several splits 0.93, 1.17 and 0.93, 1.31.
+  const bool awaited = (sp.avg > 1 || BH <= 256) && (L > 0 || (long long)grid.x <= (c.bits == 2 && !(sliding && gq > 4) ? kPlaces : 512));
   // n / H_kv = umulhi(n, magic) for n below 2^32 / H_kv; n is at most 2^24 + 3 H_kv here
   const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
-  const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)early_window << 30 | (uint32_t)(corr != nullptr) << 31,
+  const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)awaited << 30 | (uint32_t)(corr != nullptr) << 31,
                              (uint32_t)(c.H_kv - 1) | (uint32_t)sp.most << 24 | (uint32_t)L << 30,
                              (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(sp.corr_seqs) << 27, magic};
-  const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
   void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)

@@ -1,5 +1,5 @@
 """GPU parity of the decode's window part: numbers of window tokens around the shares of the four waves and their tiles (a share is a
-multiple of 4 tokens, 32 at most), requested ahead of the counters (few workgroups) and behind them (many), one split and several.
+multiple of 4 tokens, 32 at most; with one split, of the waves without a group in the last round), one split and several.
 Slots behind the window hold large numbers, which must not show."""
 import numpy as np
 import pytest
@@ -14,7 +14,7 @@ TOKENS = [1, 3, 4, 5, 15, 16, 17, 20, 33, 64, 65, 100, 113, 127, 128]
 
 @pytest.mark.parametrize("bits", [2, 4])
 @pytest.mark.parametrize("gq", [1, 4, 7])
-@pytest.mark.parametrize("H_kv,groups", [(1, 0), (1, 1), (16, 1), (1, 17), (4, 17)])  # (more than 256 workgroups with 16 and 4 heads)
+@pytest.mark.parametrize("H_kv,groups", [(1, 0), (1, 1), (16, 1), (1, 17), (4, 17)])
 def test_window_tokens(H_kv, groups, gq, bits):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
