@@ -97,7 +97,7 @@ static int decode_checked(const kvlinc_cache* cache, const kvlinc_half* q, kvlin
   if ((start == nullptr) != (stop == nullptr)) return KVLINC_EINVAL;
   if (bad_ptr(workspace, 16) || workspace_bytes < kvlinc_decode_workspace_bytes(cache, max_context))
     return KVLINC_EWORKSPACE;
-  return kvlinc::launch_decode(*cache, q, out, static_cast<float*>(workspace), kvlinc::decode_splits(*cache, max_context),
+  return kvlinc::launch_decode(*cache, q, out, static_cast<float*>(workspace), max_context,
                                static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(start),
                                static_cast<hipEvent_t>(stop));
 }
@@ -124,7 +124,7 @@ int kvlinc_decode_attention_noalloc(const kvlinc_cache* cache, const kvlinc_half
   void* ws = nullptr;
   const int rs = scratch_of_current_device(&ws);
   if (rs != KVLINC_OK) return rs;
-  return kvlinc::launch_decode(*cache, q, out, static_cast<float*>(ws), kvlinc::decode_splits(*cache, max_context),
+  return kvlinc::launch_decode(*cache, q, out, static_cast<float*>(ws), max_context,
                                static_cast<hipStream_t>(stream), nullptr, nullptr);
 }
 

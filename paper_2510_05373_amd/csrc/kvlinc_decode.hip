@@ -1089,7 +1089,7 @@ constexpr int kMaxSplits = 32;  // splits a sequence may take at most: a lane of
 // full there, and a second workgroup, whose place in the grid is behind the first ones of all sequences, starts when most of them
 // are done.  Decode launches of unequal lengths, more than 100 sequences and kv heads (2900 shapes of up to 32 groups), as a part of the
 // time with one group per wave: 16 groups 0.92 (9 to 16 groups) and 0.99 (17 to 32), 32 groups 0.92 and 0.955, but up to 1.12;
-// 144 sequences of 640 to 1280 tokens, 8 kv heads, 47.8 -> 42.1 us a launch.
+// 144 sequences of 640 to 1280 tokens, 8 kv heads, 47.8 -> 42.1 us a launch, 41.0 without the second workgroups in the grid.
 constexpr int kAloneGroups = 24;
 __device__ __forceinline__ int groups_of(int nq) { return (nq + kGroup - 1) / kGroup; }
 
@@ -1555,6 +1555,13 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
 
 }  // namespace
 
+// Groups of the longest context that a launch can meet.
+static long long longest_groups(const kvlinc_cache& c, int max_context) {
+  const long long cap = (long long)c.max_groups * kGroup + c.R;
+  const long long ctx = (max_context > 0 && max_context < cap) ? max_context : cap;
+  return ctx > kGroup ? (ctx + kGroup - 1) / kGroup : 1;
+}
+
 // Splits per (sequence, kv head).  Measured on MI355X (256 compute units): the launch is fastest when all its
 // workgroups, the correction workgroups included, are resident at once at about two per compute unit -- a second
 // generation of workgroups pays the start-up and the merge tail again, and a compute unit that hosts a correction
@@ -1566,10 +1573,7 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
 constexpr long long kPlaces = 768;  // workgroups that the chip holds at three per compute unit
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   constexpr int kTargetWorkgroups = 512;
-  const long long cap = (long long)c.max_groups * kGroup + c.R;
-  const long long ctx = (max_context > 0 && max_context < cap) ? max_context : cap;
-  long long groups = (ctx + kGroup - 1) / kGroup;
-  if (groups < 1) groups = 1;
+  const long long groups = longest_groups(c, max_context);
   const long long bh = (long long)c.B * c.H_kv;
   const int gq = c.H_q / c.H_kv;
   long long n_corr = 0;
@@ -1597,7 +1601,6 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   long long m = c.B > 1 ? 2 * s : s;
   if (m > kMaxSplits) m = kMaxSplits;
   if (m > most) m = most;
-  if (s == 1 && m > (groups + kAloneGroups - 1) / kAloneGroups) m = (groups + kAloneGroups - 1) / kAloneGroups;
   if (m < s) m = s;
   // The correction workgroups are chains of dependent steps and go first in the grid, except when they alone would
   // fill most of the chip while the streaming workgroups have long contexts ahead of them (many sequences, 16 or
@@ -1660,9 +1663,12 @@ size_t decode_workspace_floats(const kvlinc_cache& c, int n_splits) {
   return (size_t)c.B * c.H_q * (n_splits + kCorrParts) * kPartStride;  // split partials, then the correction parts
 }
 
-int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, DecodeSplits sp,
+int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, int max_context,
                   hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
-  const int n_splits = sp.most;
+  const DecodeSplits sp = decode_splits(c, max_context);
+  // The grid has no second workgroups where no sequence takes them (sequence_splits).  The workspace is sized for them all the same:
+  // its size is the same for a program's buffers, and for the limit of the static scratch, whatever the launch makes of it.
+  const int n_splits = sp.avg == 1 && longest_groups(c, max_context) <= kAloneGroups ? 1 : sp.most;
   const int gq = c.H_q / c.H_kv;
   const int BH = c.B * c.H_kv;
   const half_t* qq = reinterpret_cast<const half_t*>(q);
@@ -1683,7 +1689,7 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   // n / H_kv = umulhi(n, magic) for n below 2^32 / H_kv; n is at most 2^24 + 3 H_kv here
   const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
   const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)awaited << 30 | (uint32_t)(corr != nullptr) << 31,
-                             (uint32_t)(c.H_kv - 1) | (uint32_t)sp.most << 24 | (uint32_t)L << 30,
+                             (uint32_t)(c.H_kv - 1) | (uint32_t)n_splits << 24 | (uint32_t)L << 30,
                              (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(sp.corr_seqs) << 27, magic};
   void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)

@@ -58,8 +58,8 @@ __host__ __device__ inline AppendPlan plan_append(int n_quant, int n_res, int n_
 }
 
 // Splits of the decode launch (blocks of groups per (sequence, KV head)): the average over the batch, which a batch
-// of equal lengths uses for every sequence, and the most one sequence may take; grid and workspace are sized for
-// `most`.  corr_first: 0 = the correction workgroups come after the streaming ones in the grid, L >= 1 = they lead
+// of equal lengths uses for every sequence, and the most one sequence may take, which the workspace is sized for
+// (and the grid, see launch_decode).  corr_first: 0 = the correction workgroups come after the streaming ones in the grid, L >= 1 = they lead
 // each of the first L runs of 256 workgroups.  corr_seqs: sequences that a correction workgroup serves.
 struct DecodeSplits { int avg, most, corr_first, corr_seqs; };
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context);
@@ -68,7 +68,7 @@ int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_
                   int T, int keep, hipStream_t stream);
 size_t decode_workspace_floats(const kvlinc_cache& c, int n_splits);
 // start / stop: optional events attached to the kernel's own dispatch (both or neither)
-int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, DecodeSplits splits,
+int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, int max_context,
                   hipStream_t stream, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
 }  // namespace kvlinc
