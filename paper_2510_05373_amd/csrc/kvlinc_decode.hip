@@ -1174,7 +1174,7 @@ __device__ __forceinline__ bool await_parts(int* counter, int n_parts) {
 // each streaming the groups and the window share of one split of a (sequence, kv head), or leaving at once when its
 // sequence uses fewer splits; and, when the correction is on, the correction workgroups: after them (corr_first = 0)
 // or leading the first corr_first runs of 256 workgroups (1: all of them first -- they are long chains of dependent
-// steps and should start at once).  All of them count themselves in at split_done; the last arrival merges.
+// steps and should start at once).  All of them count themselves in at split_done; who merges: above.
 // SLIDING: the variant with the sliding value window (KVLINC_FLAG_SLIDING_VALUES) is a kernel of its own, so that the
 // default one carries none of its code.
 // BITS: so is the one for caches with 4-bit codes (it holds twice the tile words in registers).
@@ -1522,10 +1522,10 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
         if (tid == 0) {
           bool there = await_parts(counter, n_parts);
           if (!there) there = parts_arrived(__hip_atomic_fetch_add(counter, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts;
-          sFlag = there;
+          sDirect = there;  // (not sFlag: another wave may not have read the arrival's result there yet)
         }
         barrier_lds_only();
-        complete = __builtin_amdgcn_readfirstlane(sFlag) != 0;
+        complete = __builtin_amdgcn_readfirstlane(sDirect) != 0;
       }
       done = complete ? 1 : 0;
     }
