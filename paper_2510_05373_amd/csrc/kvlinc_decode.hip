@@ -523,6 +523,15 @@ __device__ __forceinline__ void pv_phase(const ValueRegs<BITS>& g, const float (
   }
 }
 
+// The values that pv_window_tail will read, one word of every line of 128 bytes, requested while the scores of the group are formed:
+// nobody else reads these slots (the window's share ends at its live tokens), and the trip to memory would come after everything.
+constexpr int kWindowLines = kGroup * kHeadDim * 2 / 128;  // R is kGroup where values slide
+__device__ __forceinline__ void touch_window_tail(uint32_t (&touched)[kWindowLines / 64], const half_t* __restrict__ v_win, int from, int lane) {
+#pragma unroll
+  for (int u = 0; u < kWindowLines / 64; ++u)
+    touched[u] = reinterpret_cast<const uint32_t*>(v_win)[32 * min(8 * (from >> 2) + 64 * u + lane, kWindowLines - 1)];
+}
+
 // Sliding value window (Sec. 4.1, setup: the newest 128 tokens in full precision): the tokens j >= from of the newest
 // group still have their fp16 rotated values in the window slots j.  Their share of E V is formed here from those values
 // by the one wave that has the newest group, on v_mfma_f32_4x4x4_16B_f16: rows = the 4 heads of a head
@@ -1436,11 +1445,16 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
       idx = count;
     }
     if (SLIDING && idx < count) {  // sliding value window: the newest group, whose tokens from n_res on have fp16 values
+      const half_t* const v_win = reinterpret_cast<const half_t*>(c.v_res) + (long long)bh * c.R * kHeadDim;
       float sc[NB][8], off[NB], base[NB];
+      uint32_t touched[kWindowLines / 64];
+      touch_window_tail(touched, v_win, nr, lane);
       qk_phase<NB, BITS>(kr, kGroup, qh, lr, sc, off);
       update_reference<NB>(sc, off, base, st, slack);
+#pragma unroll
+      for (int u = 0; u < kWindowLines / 64; ++u) asm volatile("" ::"v"(touched[u]));
       pv_phase<NB, BITS, true>(vr, sc, base, lr, st, nr);
-      pv_window_tail<NB>(reinterpret_cast<const half_t*>(c.v_res) + (long long)bh * c.R * kHeadDim, sc, base, nr, lr, st, lane, sAcc[wave]);
+      pv_window_tail<NB>(v_win, sc, base, nr, lr, st, lane, sAcc[wave]);
     }
   }
 
