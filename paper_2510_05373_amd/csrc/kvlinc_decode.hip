@@ -557,28 +557,32 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf) A[nb][hf] = *reinterpret_cast<const half4_t*>(pb + (nb * 4 + hrow) * kGroup + 64 * hf + 4 * quad);
   const uint2* vb = reinterpret_cast<const uint2*>(v_win);  // [slot / 4][channel] -> 4 slots
+  // (blocks requested together: with 16 two head blocks at 4 bits spilled 30 registers, with 4 two)
+  constexpr int kBlocks = NB == 2 ? 4 : 16;
   const int first = from >> 2;                              // blocks of 4 slots below it hold no such token
   float4_t acc[NB][2];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) acc[nb][0] = acc[nb][1] = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int hf = 0; hf < 2; ++hf) {
-    uint2 vx[2][16];
+  for (int part = 0; part < kGroup / 4 / kBlocks; ++part) {
+    uint2 vx[2][kBlocks];
 #pragma unroll
-    for (int bq = 0; bq < 16; ++bq)
+    for (int bq = 0; bq < kBlocks; ++bq)
 #pragma unroll
       for (int ch = 0; ch < 2; ++ch) {
-        const int blk = 16 * hf + bq;
+        const int blk = kBlocks * part + bq;
         vx[ch][bq] = blk >= first ? vb[(long long)blk * kHeadDim + 64 * ch + lane] : make_uint2(0, 0);
       }
 #pragma unroll
-    for (int bq = 0; bq < 16; ++bq)
+    for (int bq = 0; bq < kBlocks; ++bq)
 #pragma unroll
       for (int ch = 0; ch < 2; ++ch) {
         const half4_t bop = as_h4(vx[ch][bq].x, vx[ch][bq].y);
+        const int blk = kBlocks * part + bq;
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[nb][ch] = mfma_bcast(A[nb][hf], bop, acc[nb][ch], bq);
+        for (int nb = 0; nb < NB; ++nb) acc[nb][ch] = mfma_bcast(A[nb][blk / 16], bop, acc[nb][ch], blk % 16);
       }
+    asm volatile("" ::: "memory");  // (the next blocks' loads stay behind these products)
   }
   // (lane = channel, registers = heads) -> (row = head, lane = channel % 16, register = channel block n)
 #pragma unroll
