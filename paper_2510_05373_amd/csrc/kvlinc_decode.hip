@@ -958,10 +958,25 @@ __device__ __forceinline__ void add_correction(const u32x4_t (&p)[kCorrParts], c
 }
 // (num + 2^-M C_n) / (den + 2^-M C_d) with both factors kept <= 1 (M is the log2-domain maximum); the literal
 // form of Alg. 1's last lines leaves the factor 2^-M out.  M = -inf: no tokens, 0.
+// Rows with all logits far below zero are scaled by the larger of 2^M and the power of two above C_d instead of by 1, so that the
+// divisor is a normal number whatever M is and however little is added (den counts the maximum itself as 1), and by 2^M alone
+// where nothing is added (C_d = 0): the reciprocal overflows from logits of -88 on otherwise, the divisor is zero from -103 on.  (A
+// branch: the factors of all other rows are there before C_d is; without it decode launches of up to 64 sequences and heads took
+// 1.007 of the time.)
+constexpr float kFarBelow = -64.0f;
 template <int N>
-__device__ __forceinline__ void normalise(float (&n)[N], float den, const float (&cn)[N], float cd, float M, bool literal) {
+__device__ __forceinline__ void normalise(float (&n)[N], float den, float (&cn)[N], float cd, float M, bool literal) {
   const float Ms = fmaxf(M, 0.f);
-  const float fa = literal ? 1.0f : exp2f(M - Ms), fb = literal ? 1.0f : exp2f(-Ms);
+  float fa = literal ? 1.0f : exp2f(M - Ms), fb = literal ? 1.0f : exp2f(-Ms);
+  if (M < kFarBelow && !literal) {
+    const int e = cd != 0.f ? __builtin_amdgcn_frexp_expf(cd) : 0;  // cd / 2^e in [1/2, 1)
+    const float top = cd != 0.f ? fmaxf(M, (float)e) : M;
+    fa = exp2f(M - top);
+    fb = cd != 0.f ? exp2f((float)e - top) : 0.f;
+    cd = ldexpf(cd, -e);
+#pragma unroll
+    for (int c = 0; c < N; ++c) cn[c] = ldexpf(cn[c], -e);
+  }
   const float inv = M != -INFINITY ? 1.0f / (fa * den + fb * cd) : 0.f;
 #pragma unroll
   for (int c = 0; c < N; ++c) n[c] = M != -INFINITY ? (fa * n[c] + fb * cn[c]) * inv : 0.f;
