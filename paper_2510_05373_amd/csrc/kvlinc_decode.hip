@@ -1170,11 +1170,11 @@ __device__ __forceinline__ int sequence_splits(const kvlinc_cache& c, int count,
 
 // What arrives at a (sequence, kv head): its streaming workgroups, 1 each, and those of the correction, kCorrArrival each.
 // Who merges: the streaming workgroup that completes the streaming ones, if the correction is complete; otherwise, where the launch
-// says that the correction is awaited -- its workgroups run already or are done --, the same workgroup, which looks at the
+// says that the correction is awaited -- all of its workgroups run already or are done --, the same workgroup, which looks at the
 // counter until it is, up to kLooks times; or else the correction workgroup that completes the count.  A streaming workgroup
 // that gives up leaves kGaveUp in the counter: whoever adds to it last, it or the correction, sees the other and merges.
 // (A correction workgroup has the rows of up to 8 sequences to merge, a streaming workgroup those of one, which the single split of a
-// sequence has in LDS besides: see launch_decode for what awaiting gives.  Looks without s_sleep(16) between them, 2 instead: 1.002
+// sequence has in LDS besides: see decode_launch for what awaiting gives.  Looks without s_sleep(16) between them, 2 instead: 1.002
 // of the time on average and 1.30 instead of 1.27 at most; 48: 1.003.)
 constexpr int kCorrArrival = 64, kGaveUp = 1 << 16, kLooks = 64;
 __device__ __forceinline__ int streams_arrived(int count) { return count & (kCorrArrival - 1); }
@@ -1696,34 +1696,46 @@ size_t decode_workspace_floats(const kvlinc_cache& c, int n_splits) {
   return (size_t)c.B * c.H_q * (n_splits + kCorrParts) * kPartStride;  // split partials, then the correction parts
 }
 
-int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, int max_context,
-                  hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
+DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context) {
   const DecodeSplits sp = decode_splits(c, max_context);
+  DecodeLaunch l;
   // The grid has no second workgroups where no sequence takes them (sequence_splits).  The workspace is sized for them all the same:
   // its size is the same for a program's buffers, and for the limit of the static scratch, whatever the launch makes of it.
-  const int n_splits = sp.avg == 1 && longest_groups(c, max_context) <= kAloneGroups ? 1 : sp.most;
-  const int gq = c.H_q / c.H_kv;
+  l.avg = sp.avg;
+  l.splits = sp.avg == 1 && longest_groups(c, max_context) <= kAloneGroups ? 1 : sp.most;
+  l.corr_seqs = sp.corr_seqs;
   const int BH = c.B * c.H_kv;
+  const int n_corr = c.S16 != nullptr ? c.H_kv * kCorrParts * ((c.B + sp.corr_seqs - 1) / sp.corr_seqs) : 0;
+  l.workgroups = BH * l.splits + n_corr;
+  // every run that leads with correction workgroups must lie inside the grid and hold its share
+  int L = n_corr != 0 ? sp.corr_first : 0;
+  while (L > 1 && (l.workgroups < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
+  l.corr_first = L;
+  // The correction is awaited only where all of its workgroups are ahead of the streaming ones (one run leads): they run already
+  // then, or are done.  3000 such launches: 0.983 of the time of a merge by whoever arrives last, 0.71 to 1.21.  Streaming workgroups
+  // ahead of it, or of half of it, would hold the very places that it waits for when launches of other streams have the rest of the
+  // chip: three caches decoded on three streams, the correction last, took 0.97 to 1.37 of the time when it was awaited, 1.09 on
+  // average (30 shapes); alone, launches with the correction last or in two runs take 0.99 of the time when it is not (1500 shapes).
+  // Nor is it awaited by more than 256 sequences and heads with one split each, whose looks crowd the counters.
+  l.awaited = L == 1 && (sp.avg > 1 || BH <= 256);
+  return l;
+}
+
+int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out, float* workspace, int max_context,
+                  hipStream_t stream, hipEvent_t start, hipEvent_t stop) {
+  const DecodeLaunch l = decode_launch(c, max_context);
+  const int gq = c.H_q / c.H_kv;
   const half_t* qq = reinterpret_cast<const half_t*>(q);
   half_t* oo = reinterpret_cast<half_t*>(out);
   float* part = workspace;
-  float* corr = c.S16 != nullptr ? workspace + (size_t)c.B * c.H_q * n_splits * kPartStride : nullptr;
-  const int n_corr = corr != nullptr ? c.H_kv * kCorrParts * ((c.B + sp.corr_seqs - 1) / sp.corr_seqs) : 0;
+  float* corr = c.S16 != nullptr ? workspace + (size_t)c.B * c.H_q * l.splits * kPartStride : nullptr;
   const bool sliding = (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0;
-  const dim3 grid(BH * n_splits + n_corr), block(kThreads);
-  // every run that leads with correction workgroups must lie inside the grid and hold its share
-  int L = n_corr != 0 ? sp.corr_first : 0;
-  while (L > 1 && ((int)grid.x < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
-  // The correction is awaited where its workgroups come first, or all of the launch is on the chip at once; not by more than 256
-  // sequences and heads with one split each, whose looks crowd the counters.  Over 4940 random shapes, as a part of the time of a
-  // merge by whoever arrives last (mean, worst): one split and up to 256 of them 0.90, 1.20 awaited and 0.94, 1.39 not, beyond 256
-  // 0.92, 1.27 and 0.92, 1.17; several splits 0.93, 1.17 and 0.93, 1.31.
-  const bool awaited = (sp.avg > 1 || BH <= 256) && (L > 0 || (long long)grid.x <= (c.bits == 2 && !(sliding && gq > 4) ? kPlaces : 512));
+  const dim3 grid(l.workgroups), block(kThreads);
   // n / H_kv = umulhi(n, magic) for n below 2^32 / H_kv; n is at most 2^24 + 3 H_kv here
   const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
-  const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)sp.avg << 24 | (uint32_t)awaited << 30 | (uint32_t)(corr != nullptr) << 31,
-                             (uint32_t)(c.H_kv - 1) | (uint32_t)n_splits << 24 | (uint32_t)L << 30,
-                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(sp.corr_seqs) << 27, magic};
+  const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)l.avg << 24 | (uint32_t)l.awaited << 30 | (uint32_t)(corr != nullptr) << 31,
+                             (uint32_t)(c.H_kv - 1) | (uint32_t)l.splits << 24 | (uint32_t)l.corr_first << 30,
+                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(l.corr_seqs) << 27, magic};
   void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)

@@ -59,10 +59,14 @@ __host__ __device__ inline AppendPlan plan_append(int n_quant, int n_res, int n_
 
 // Splits of the decode launch (blocks of groups per (sequence, KV head)): the average over the batch, which a batch
 // of equal lengths uses for every sequence, and the most one sequence may take, which the workspace is sized for
-// (and the grid, see launch_decode).  corr_first: 0 = the correction workgroups come after the streaming ones in the grid, L >= 1 = they lead
+// (and the grid, see decode_launch).  corr_first: 0 = the correction workgroups come after the streaming ones in the grid, L >= 1 = they lead
 // each of the first L runs of 256 workgroups.  corr_seqs: sequences that a correction workgroup serves.
 struct DecodeSplits { int avg, most, corr_first, corr_seqs; };
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context);
+// What a launch makes of it: streaming workgroups per (sequence, KV head) in the grid, the runs that the correction does lead, whether
+// the streaming workgroups await it (0 or 1), all workgroups.
+struct DecodeLaunch { int avg, splits, corr_seqs, corr_first, awaited, workgroups; };
+DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context);
 
 int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_half* v_new, const int32_t* n_new,
                   int T, int keep, hipStream_t stream);

@@ -78,3 +78,31 @@ def test_sequences_of_a_correction_workgroup(B, H_q, H_kv, bits, seqs):
     if B * H_kv < 1000:
         for context in (300, 1408, 8065, 131072):
             assert splits_of(B, H_q, H_kv, context, bits=bits).corr_seqs == 4
+
+
+class Launch(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("avg", "splits", "corr_seqs", "corr_first", "awaited", "workgroups")]
+
+
+def launch_of(B, H_q, H_kv, context, **over):
+    f = kb.lib._ZN6kvlinc13decode_launchERK12kvlinc_cachei
+    f.restype, f.argtypes = Launch, [ctypes.POINTER(kb.CacheStruct), ctypes.c_int]
+    return f(ctypes.byref(fake_struct(B=B, H_q=H_q, H_kv=H_kv, max_groups=1025, **over)), context)
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("gq", [1, 2, 4, 7])
+def test_the_correction_is_awaited_only_where_all_of_it_goes_first(gq, bits):
+    """Streaming workgroups that wait for correction workgroups behind them in the grid hold the places that these need as soon as
+    another stream's launch shares the chip."""
+    seen = set()
+    for H_kv in (1, 2, 3, 4, 8, 16, 32):
+        for B in list(range(1, 41)) + [64, 144]:
+            for context in (1, 300, 500, 1281, 4096, 9000, 20000, 131072):
+                l = launch_of(B, H_kv * gq, H_kv, context, bits=bits)
+                s = splits_of(B, H_kv * gq, H_kv, context, bits=bits)
+                n_corr = H_kv * 4 * -(-B // s.corr_seqs)
+                assert (l.avg, l.corr_seqs) == (s.avg, s.corr_seqs) and l.workgroups == B * H_kv * l.splits + n_corr and l.splits in (1, s.most)
+                assert not l.awaited or l.corr_first == 1, (B, H_kv, context)
+                seen.add((l.corr_first, l.awaited))
+    assert {(1, 1), (2, 0)} <= seen and (bits == 4 or (0, 0) in seen)
