@@ -36,11 +36,11 @@
 
 #include "kvlinc_internal.h"
 #include "kvlinc_mfma.h"
+#include "kvlinc_schedule.h"
 
 namespace kvlinc {
 namespace {
 
-constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kAlpha = kLog2e * 0.08838834764831845f;  // log2(e) / sqrt(128)
@@ -1212,7 +1212,8 @@ __device__ __forceinline__ bool await_parts(int* counter, int n_parts) {
 struct LaunchWords {
   uint32_t batch;   // B - 1, splits of a sequence on average << 24, correction awaited << 30, on << 31
   uint32_t heads;   // H_kv - 1, most splits of a sequence << 24, runs of the grid that the correction leads << 30
-  uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, log2 of the sequences of a correction workgroup << 27
+  uint32_t groups;  // max_groups - 1, query heads per kv head - 1 << 24, log2 of the sequences of a correction workgroup << 27,
+                    // rounds that split 0 sits out - 1 << 29
   uint32_t magic;   // ceil(2^32 / H_kv), or 0 where that does not give quotients by H_kv
 };
 constexpr uint32_t kLow24 = (1u << 24) - 1u;
@@ -1318,22 +1319,14 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   }
   const int b = by_heads(bh), g = bh - b * c.H_kv;
 
-  // Static schedule, the same for every sequence length, so that a wave knows its first group before it knows the
-  // length.  Time is cut into rounds of 4 n_splits slots, slot(round, wave, split) = 4 n_splits round + n_splits wave +
-  // n_splits - 1 - split; the groups 0, 1, 2, ... go to the slots in order, except that the four waves of split 0 sit out the
-  // first kSkip rounds: a share of the window each is their work for that time.  Consecutive groups thus go to different
-  // workgroups, and every split gets the same share whatever the length.
-  // (kSkip: 16 sequences of 8k tokens at 2 bits 24.5 us a step, 24.7 with 1; at 4 bits, where a record is twice as long, 39.1 with 2, 37.4
-  // with 1.)
-  constexpr int kSkip = BITS == 2 ? 2 : 1;
+  // Static schedule, the same for every sequence length, so that a wave knows its first group before it knows the length (GroupOrder).
   int n_splits = avg_splits;  // first guess: right for a batch of equal lengths
-  int slots, off, rd, idx;
-  auto group_of_round = [&](int round) { return round * slots + off - (round < kSkip ? kWaves * round + wave : kWaves * kSkip); };
+  const int skip = BITS == 2 ? (int)((words.groups >> 29) & 1) + 1 : 1;
+  int rd, idx;
   auto plan = [&]() {
-    slots = kWaves * n_splits;
-    off = wave * n_splits + n_splits - 1 - sp;
-    rd = sp == 0 ? kSkip : 0;
-    idx = group_of_round(rd);
+    const GroupOrder order(n_splits, sp, wave, skip);
+    rd = sp == 0 ? skip : 0;
+    idx = order.group(rd);
   };
 
   // What the wave works on first -- its part of the window, a record -- is requested before the sequence length is known (any group
@@ -1444,8 +1437,9 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     const float slack = (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0 ? 0.0f : kSlack;
     const bool sliding = SLIDING && nq % kGroup == 0 && nr < kGroup;
     const int count_plain = sliding ? count - 1 : count;
+    const GroupOrder order(n_splits, sp, wave, skip);
     while (idx < count_plain) {
-      const int nxt = group_of_round(++rd);
+      const int nxt = order.group(++rd);
       if (nxt >= count) break;
       const uint32_t* src = rec0 + (long long)nxt * kRecordWords;
       float sc[NB][8], off[NB], base[NB];
@@ -1718,6 +1712,8 @@ DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context) {
   // average (30 shapes); alone, launches with the correction last or in two runs take 0.99 of the time when it is not (1500 shapes).
   // Nor is it awaited by more than 256 sequences and heads with one split each, whose looks crowd the counters.
   l.awaited = L == 1 && (sp.avg > 1 || BH <= 256);
+  // (a context of the bound itself has one group less: its last tokens are the window's)
+  l.skip = window_rounds((int)longest_groups(c, max_context) - 1, sp.avg, c.bits);
   return l;
 }
 
@@ -1735,7 +1731,7 @@ int launch_decode(const kvlinc_cache& c, const kvlinc_half* q, kvlinc_half* out,
   const uint32_t magic = c.H_kv > 1 && c.H_kv <= 128 ? (uint32_t)(((1ull << 32) + c.H_kv - 1) / c.H_kv) : 0u;
   const LaunchWords words = {(uint32_t)(c.B - 1) | (uint32_t)l.avg << 24 | (uint32_t)l.awaited << 30 | (uint32_t)(corr != nullptr) << 31,
                              (uint32_t)(c.H_kv - 1) | (uint32_t)l.splits << 24 | (uint32_t)l.corr_first << 30,
-                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(l.corr_seqs) << 27, magic};
+                             (uint32_t)(c.max_groups - 1) | (uint32_t)(gq - 1) << 24 | (uint32_t)__builtin_ctz(l.corr_seqs) << 27 | (uint32_t)(l.skip - 1) << 29, magic};
   void (*kernel)(uint32_t*, int32_t*, const half_t*, const kvlinc_half*, kvlinc_half*, uint32_t, uint32_t, uint32_t, uint32_t, kvlinc_cache, float*, float*, half_t*) =
       c.bits == 4 ? (gq > 4   ? (sliding ? decode_main_kernel<2, true, 4> : decode_main_kernel<2, false, 4>)
                      : gq < 4 ? (sliding ? decode_main_kernel<1, true, 4, true> : decode_main_kernel<1, false, 4, true>)

@@ -64,8 +64,8 @@ __host__ __device__ inline AppendPlan plan_append(int n_quant, int n_res, int n_
 struct DecodeSplits { int avg, most, corr_first, corr_seqs; };
 DecodeSplits decode_splits(const kvlinc_cache& c, int max_context);
 // What a launch makes of it: streaming workgroups per (sequence, KV head) in the grid, the runs that the correction does lead, whether
-// the streaming workgroups await it (0 or 1), all workgroups.
-struct DecodeLaunch { int avg, splits, corr_seqs, corr_first, awaited, workgroups; };
+// the streaming workgroups await it (0 or 1), all workgroups, the rounds that split 0 sits out for the window.
+struct DecodeLaunch { int avg, splits, corr_seqs, corr_first, awaited, workgroups, skip; };
 DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context);
 
 int launch_append(const kvlinc_cache& c, const kvlinc_half* k_new, const kvlinc_half* v_new, const int32_t* n_new,

@@ -81,7 +81,7 @@ def test_sequences_of_a_correction_workgroup(B, H_q, H_kv, bits, seqs):
 
 
 class Launch(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int) for n in ("avg", "splits", "corr_seqs", "corr_first", "awaited", "workgroups")]
+    _fields_ = [(n, ctypes.c_int) for n in ("avg", "splits", "corr_seqs", "corr_first", "awaited", "workgroups", "skip")]
 
 
 def launch_of(B, H_q, H_kv, context, **over):
