@@ -1713,7 +1713,9 @@ DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context) {
   // Nor is it awaited by more than 256 sequences and heads with one split each, whose looks crowd the counters.
   l.awaited = L == 1 && (sp.avg > 1 || BH <= 256);
   // (a context of the bound itself has one group less: its last tokens are the window's)
-  l.skip = window_rounds((int)longest_groups(c, max_context) - 1, sp.avg, c.bits);
+  const int count = (int)longest_groups(c, max_context) - 1;
+  const int most = (count + kWaves - 1) / kWaves;  // splits that it takes at most (sequence_splits)
+  l.skip = window_rounds(count, sp.avg < most ? sp.avg : most, c.bits);
   return l;
 }
 

@@ -28,7 +28,7 @@ struct GroupOrder {
 // wrong, launches of two splits or more took 1.006 of the time of two rounds always, those with the longer schedules included.)
 inline int window_rounds(int count, int n_splits, int bits) {
   if (bits != 2) return 1;
-  return (count + 7) % (kWaves * n_splits) < kWaves && n_splits > 1 ? 1 : 2;
+  return n_splits > 1 && (count + 7) % (kWaves * n_splits) < kWaves ? 1 : 2;
 }
 
 }  // namespace kvlinc

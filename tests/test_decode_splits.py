@@ -106,3 +106,18 @@ def test_the_correction_is_awaited_only_where_all_of_it_goes_first(gq, bits):
                 assert not l.awaited or l.corr_first == 1, (B, H_kv, context)
                 seen.add((l.corr_first, l.awaited))
     assert {(1, 1), (2, 0)} <= seen and (bits == 4 or (0, 0) in seen)
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+def test_rounds_that_split_0_sits_out(bits):
+    """One where two would make a context of the bound itself a round longer, for the splits that such a sequence takes."""
+    seen = set()
+    for B, H_kv, gq in ((1, 8, 4), (2, 1, 1), (16, 8, 4), (15, 8, 1), (32, 4, 7), (40, 8, 4), (144, 8, 4)):
+        for context in range(1, 12000, 127):
+            l = launch_of(B, H_kv * gq, H_kv, context, bits=bits)
+            groups = -(-max(context, 1) // 128) - 1
+            n = min(l.avg, -(-groups // 4))
+            longer = n > 1 and -(-(groups + 8) // (4 * n)) > -(-(groups + 4) // (4 * n))
+            assert l.skip == (1 if bits == 4 or longer else 2), (B, H_kv, gq, context)
+            seen.add(l.skip)
+    assert seen == ({1} if bits == 4 else {1, 2})
