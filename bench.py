@@ -29,7 +29,7 @@ WORKLOAD = 2  # index into kvlinc_synth.CONFIGS
 def timed_steps(K):
     n = max(4, min(16, K // 16))
     return sorted(set(min(K - 1, int((i + 0.5) * K / n)) for i in range(n))) if K > 0 else []
-KERNEL_SOURCES = ("kvlinc_decode.hip", "kvlinc_mfma.h", "kvlinc_internal.h")  # what the decode kernel is compiled from
+KERNEL_SOURCES = ("kvlinc_decode.hip", "kvlinc_mfma.h", "kvlinc_internal.h", "kvlinc_handoff.h", "kvlinc_schedule.h")  # what the decode kernel is compiled from
 
 
 def kernel_source_sha1():

@@ -11,7 +11,7 @@
 //   correction workgroups (kv head, part of phi, 1 to 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
 //   the rows of S, on the matrix cores.
 // Every workgroup counts itself in at its (sequence, kv head); the streaming workgroup that arrives last, or the correction
-// workgroup where that is later and not awaited (see kCorrArrival), merges: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
+// workgroup where that is later and not awaited (see kvlinc_handoff.h), merges: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
 // H^T and stores fp16 (Alg. 1 lines 13-15 with Eq. 5).  Every wait is bounded: what it waited for is left to
 // whoever comes last then.
 //
@@ -34,6 +34,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include "kvlinc_handoff.h"
 #include "kvlinc_internal.h"
 #include "kvlinc_mfma.h"
 #include "kvlinc_schedule.h"
@@ -1168,35 +1169,20 @@ __device__ __forceinline__ int sequence_splits(const kvlinc_cache& c, int count,
   return __builtin_amdgcn_readfirstlane(max(s, 1));            // the same in every lane: keep it in a scalar register
 }
 
-// What arrives at a (sequence, kv head): its streaming workgroups, 1 each, and those of the correction, kCorrArrival each.
-// Who merges: the streaming workgroup that completes the streaming ones, if the correction is complete; otherwise, where the launch
-// says that the correction is awaited -- all of its workgroups run already or are done --, the same workgroup, which looks at the
-// counter until it is, up to kLooks times; or else the correction workgroup that completes the count.  A streaming workgroup
-// that gives up leaves kGaveUp in the counter: whoever adds to it last, it or the correction, sees the other and merges.
-// (A correction workgroup has the rows of up to 8 sequences to merge, a streaming workgroup those of one, which the single split of a
-// sequence has in LDS besides: see decode_launch for what awaiting gives.  Looks without s_sleep(16) between them, 2 instead: 1.002
-// of the time on average and 1.30 instead of 1.27 at most; 48: 1.003.)
-constexpr int kCorrArrival = 64, kGaveUp = 1 << 16, kLooks = 64;
-__device__ __forceinline__ int streams_arrived(int count) { return count & (kCorrArrival - 1); }
-__device__ __forceinline__ int parts_arrived(int count) { return (count & (kGaveUp - 1)) / kCorrArrival; }
-
-// Arrival of a streaming workgroup: every wave first waits until its write-through stores have been
-// acknowledged, then one thread counts the workgroup in.  Returns the counter as it was before.
-__device__ __forceinline__ int arrive(int* counter, int* sFlag) {
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0) *sFlag = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(*sFlag);
-}
-// One thread looks at the counter until all parts of the correction have arrived, a bounded number of times.
-__device__ __forceinline__ bool await_parts(int* counter, int n_parts) {
-  for (int i = 0; i < kLooks; ++i) {
-    if (parts_arrived(__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts) return true;
-    __builtin_amdgcn_s_sleep(16);  // (about half a microsecond: more looks get in the way of the arrivals they wait for)
-  }
-  return false;
-}
+// The counter of a (sequence, kv head), which its workgroups arrive at: see kvlinc_handoff.h for who merges.
+// (Why a streaming workgroup rather than one of the correction, which may be awaited: that has the rows of up to 8 sequences to merge, a
+// streaming workgroup those of one, which the single split of a sequence has in LDS besides; see decode_launch for what awaiting
+// gives.  Looks without s_sleep(16) between them, 2 instead: 1.002 of the time on average and 1.30 instead of 1.27 at most; 48: 1.003.)
+#ifndef KVLINC_LOOKS
+#define KVLINC_LOOKS 64  // (tests build a library with none, in which every wait runs out at once)
+#endif
+constexpr int kLooks = KVLINC_LOOKS;
+struct ArrivalCounter {
+  int* count;
+  __device__ __forceinline__ int add(int n) { return __hip_atomic_fetch_add(count, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+  __device__ __forceinline__ int look() { return __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+  __device__ __forceinline__ void pause() { __builtin_amdgcn_s_sleep(16); }  // (about half a microsecond: more looks get in the way of the arrivals they wait for)
+};
 
 // Grid: B H_kv max_splits streaming workgroups, split-major (workgroup = split * B H_kv + sequence * H_kv + kv head),
 // each streaming the groups and the window share of one split of a (sequence, kv head), or leaving at once when its
@@ -1293,16 +1279,14 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     __syncthreads();
     int* sFlags = reinterpret_cast<int*>(lds);
     if (tid < n_seq)
-      sFlags[tid] = __hip_atomic_fetch_add(c.split_done + (b_first + tid) * c.H_kv + g, kCorrArrival, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_SYSTEM);
+      sFlags[tid] = ArrivalCounter{c.split_done + (b_first + tid) * c.H_kv + g}.add(kCorrArrival);
     __syncthreads();
     m_first = b_first;
     m_g = g;
     for (int s = 0; s < n_seq; ++s) {
       const int n_splits = sequence_splits(c, groups_of(__builtin_amdgcn_readlane(nq_mine, s)), total, avg_splits, max_splits, lane);
       splits |= (uint64_t)n_splits << (8 * s);
-      const int before = __builtin_amdgcn_readfirstlane(sFlags[s]);
-      if (parts_arrived(before) == n_parts - 1 && streams_arrived(before) == n_splits && (!awaited || before >= kGaveUp)) done |= 1u << s;
+      if (correction_merges(__builtin_amdgcn_readfirstlane(sFlags[s]), n_splits, n_parts, awaited)) done |= 1u << s;
     }
   } else {
   // ---- one split of the groups and of the window (Alg. 1, the loop over blocks) ----
@@ -1475,8 +1459,8 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   // the correction parts have all arrived (or the correction is off) or are awaited.  The first look at the counter is taken here
   // so that its latency passes during the combine.
   __shared__ int sDirect;
-  if (tid == 0)
-    sDirect = n_splits == 1 && (n_parts == 0 || parts_arrived(__hip_atomic_load(c.split_done + bh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts);
+  ArrivalCounter counter{c.split_done + bh};
+  if (tid == 0) sDirect = n_splits == 1 && (n_parts == 0 || parts_arrived(counter.look()) == n_parts);
   // combine the four waves (Alg. 1 lines 13-14 restricted to this workgroup) and write (m, l, Y_s)
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
@@ -1521,11 +1505,10 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   m_first = b;
   m_g = g;
   splits = n_splits;
-  int* const counter = c.split_done + bh;
   if (keep) {
     barrier_lds_only();
     if (!direct) {
-      if (tid == 0) sDirect = await_parts(counter, n_parts);
+      if (tid == 0) sDirect = await_parts(counter, n_parts, kLooks);
       barrier_lds_only();
       direct = __builtin_amdgcn_readfirstlane(sDirect) != 0;
     }
@@ -1541,21 +1524,13 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   if (direct) {
     done = 1;
   } else {
-    // The workgroup that completes the count merges (Alg. 1 lines 13-15): it reads what the others wrote with coherent loads.
-    const int before = arrive(counter, &sFlag);
-    if (streams_arrived(before) == n_splits - 1) {
-      bool complete = parts_arrived(before) == n_parts;
-      if (!complete && awaited) {
-        if (tid == 0) {
-          bool there = await_parts(counter, n_parts);
-          if (!there) there = parts_arrived(__hip_atomic_fetch_add(counter, kGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM)) == n_parts;
-          sDirect = there;  // (not sFlag: another wave may not have read the arrival's result there yet)
-        }
-        barrier_lds_only();
-        complete = __builtin_amdgcn_readfirstlane(sDirect) != 0;
-      }
-      done = complete ? 1 : 0;
-    }
+    // Every wave first waits until its write-through stores have been acknowledged, then one thread counts the workgroup in.  If it
+    // merges (Alg. 1 lines 13-15) it reads what the others wrote with coherent loads.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) sFlag = stream_arrives(counter, n_splits, n_parts, awaited, keep, kLooks);  // (keep: it has given up)
+    __syncthreads();
+    done = __builtin_amdgcn_readfirstlane(sFlag) != 0;
   }
   }
 
@@ -1705,8 +1680,8 @@ DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context) {
   int L = n_corr != 0 ? sp.corr_first : 0;
   while (L > 1 && (l.workgroups < 256 * (L - 1) + (n_corr + L - 1) / L || (n_corr + L - 1) / L > 256)) --L;
   l.corr_first = L;
-  // The correction is awaited only where all of its workgroups are ahead of the streaming ones (one run leads): they run already
-  // then, or are done.  3000 such launches: 0.983 of the time of a merge by whoever arrives last, 0.71 to 1.21.  Streaming workgroups
+  // The correction is awaited only where all of its workgroups are ahead of the streaming ones (one run leads): they are given
+  // their places first.  3000 such launches: 0.983 of the time of a merge by whoever arrives last, 0.71 to 1.21.  Streaming workgroups
   // ahead of it, or of half of it, would hold the very places that it waits for when launches of other streams have the rest of the
   // chip: three caches decoded on three streams, the correction last, took 0.97 to 1.37 of the time when it was awaited, 1.09 on
   // average (30 shapes); alone, launches with the correction last or in two runs take 0.99 of the time when it is not (1500 shapes).

@@ -1,26 +1,19 @@
 """The order in which a decode launch walks the groups of a sequence, from a host build of the header that the kernel includes."""
-import ctypes
-import os
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from tests.decode_model import build_model
+
 WAVES = 4
 
 
 @pytest.fixture(scope="module")
 def model(tmp_path_factory):
-    so = str(tmp_path_factory.mktemp("model") / "model.so")
-    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--cuda-host-only", "-O2", "-std=c++17", "-fPIC", "-shared", "-pthread",
-                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2510_05373_amd", "csrc"),
-                    os.path.join(ROOT, "tests", "decode_model.cpp"), "-o", so], check=True)
-    return ctypes.CDLL(so)
+    return build_model(tmp_path_factory)
 
 
 def walk(model, count, n, bits):
     """(groups of every wave in its order, by (split, wave); rounds that split 0 sits out)."""
-    skip = model.window_rounds(count, n, bits)
+    skip = model.rounds_left_out(count, n, bits)
     waves = {}
     for split in range(n):
         for wave in range(WAVES):
