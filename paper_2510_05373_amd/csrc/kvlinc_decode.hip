@@ -1634,13 +1634,15 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
   // share a sequence then, and a workgroup that arrives last has fewer rows to merge.  More splits than one, decode launches with the
   // fewest that fit so, against 4, on average (0.1 to 0.3 of the time between single shapes, either way): 0.99 to 1.01 on one workgroup
   // per unit, 0.88 to 0.98 on two, 0.98 on three.  A unit more: 1.04 to 1.35.  (4 bits, where a unit holds two: 2 sequences rather
-  // than 1 on two, 0.98 against 1.01.)  One split (7700 shapes of up to 1100 tokens): 2 sequences where all workgroups have a unit of
+  // than 1 on two, 0.98 against 1.01; the sliding window's kernel for more than 4 heads holds two as well: with workgroups of 1 and 2 as if
+  // it held three, 59 such launches took up to 1.16 of the time of the kernels before, 1.09 with 4.)  One split (7700 shapes of up to 1100 tokens): 2 sequences where all workgroups have a unit of
   // their own, 0.97 and 0.98 of the time of 4, 1 sequence 1.01; beyond that 2 take 1.02.
+  const int held = c.bits == 4 || (gq > 4 && (c.flags & KVLINC_FLAG_SLIDING_VALUES) != 0) ? 2 : 3;  // workgroups on a unit (launch bounds)
   auto launch = [&](long long avg, long long most_splits, int first) {
     int seqs = corr_seqs;
     const long long per_unit = (bh * avg + corr_workgroups(4) + 255) / 256;
-    if (seqs == 4 && per_unit <= (avg == 1 ? 1 : c.bits == 2 ? 3 : 2))
-      for (int k = 2; k >= (avg == 1 || (c.bits == 4 && per_unit == 2) ? 2 : 1); --k)
+    if (seqs == 4 && per_unit <= (avg == 1 ? 1 : held))
+      for (int k = 2; k >= (avg == 1 || (held == 2 && per_unit == 2) ? 2 : 1); --k)
         if (bh * avg + corr_workgroups(k) <= 256 * per_unit) seqs = k;
     return DecodeSplits{(int)avg, (int)most_splits, first, seqs};
   };

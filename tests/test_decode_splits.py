@@ -121,3 +121,19 @@ def test_rounds_that_split_0_sits_out(bits):
             assert l.skip == (1 if bits == 4 or longer else 2), (B, H_kv, gq, context)
             seen.add(l.skip)
     assert seen == ({1} if bits == 4 else {1, 2})
+
+
+@pytest.mark.parametrize("bits,sliding,held", [(2, False, 3), (4, False, 2), (2, True, 3), (4, True, 2)])
+def test_small_correction_workgroups_only_where_all_workgroups_fit_the_chip(bits, sliding, held):
+    """`held`: workgroups that a compute unit holds; the kernel of the sliding window for more than 4 heads holds two."""
+    seen = set()
+    for gq in (1, 2, 4, 5, 8):
+        places = 256 * (2 if sliding and gq > 4 else held)
+        for H_kv in (1, 2, 3, 4, 8, 16, 32):
+            for B in list(range(1, 41)) + [64, 144]:
+                for context in (1, 300, 900, 1500, 3000, 4500, 9000, 20000):
+                    s = splits_of(B, H_kv * gq, H_kv, context, bits=bits, flags=kb.KVLINC_FLAG_SLIDING_VALUES if sliding else 0)
+                    seen.add(s.corr_seqs)
+                    if s.corr_seqs < 4:
+                        assert B * H_kv * s.avg + H_kv * 4 * -(-B // s.corr_seqs) <= places, (B, H_kv, gq, context)
+    assert {1, 2, 4} <= seen
