@@ -1657,7 +1657,9 @@ DecodeSplits decode_splits(const kvlinc_cache& c, int max_context) {
       if (m > kMaxSplits) m = kMaxSplits;
       if (m > most) m = most;
       if (m < s) m = s;
-      corr_first = 2;
+      // (All of them on units of their own, one run: the correction is the first to start, and awaited.  47 launches, most of them at
+      // 4 bits: 0.77 of the time of two runs, 0.56 to 1.03.)
+      if (bh * s + all_corr > 256) corr_first = 2;
     }
   }
   return launch(s, m, corr_first);

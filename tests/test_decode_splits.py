@@ -137,3 +137,16 @@ def test_small_correction_workgroups_only_where_all_workgroups_fit_the_chip(bits
                     if s.corr_seqs < 4:
                         assert B * H_kv * s.avg + H_kv * 4 * -(-B // s.corr_seqs) <= places, (B, H_kv, gq, context)
     assert {1, 2, 4} <= seen
+
+
+@pytest.mark.parametrize("bits", [2, 4])
+def test_two_runs_lead_only_where_units_are_shared(bits):
+    seen = set()
+    for gq in (1, 2, 4, 7):
+        for H_kv in (1, 2, 3, 4, 8, 16, 32):
+            for B in list(range(1, 41)) + [64, 144]:
+                for context in (300, 900, 1500, 3000, 4500, 9000, 20000, 131072):
+                    s = splits_of(B, H_kv * gq, H_kv, context, bits=bits)
+                    seen.add(s.corr_first)
+                    assert s.corr_first < 2 or B * H_kv * s.avg + H_kv * 4 * -(-B // 4) > 256, (B, H_kv, gq, context)
+    assert {1, 2} <= seen
