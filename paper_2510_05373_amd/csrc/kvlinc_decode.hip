@@ -1689,8 +1689,10 @@ DecodeLaunch decode_launch(const kvlinc_cache& c, int max_context) {
   // ahead of it, or of half of it, would hold the very places that it waits for when launches of other streams have the rest of the
   // chip: three caches decoded on three streams, the correction last, took 0.97 to 1.37 of the time when it was awaited, 1.09 on
   // average (30 shapes); alone, launches with the correction last or in two runs take 0.99 of the time when it is not (1500 shapes).
-  // Nor is it awaited by more than 256 sequences and heads with one split each, whose looks crowd the counters.
-  l.awaited = L == 1 && (sp.avg > 1 || BH <= 256);
+  // Nor is it awaited by more than 256 sequences and heads with one split each, whose looks crowd the counters, nor by several splits of
+  // a sequence whose correction workgroups have no other sequence's rows to merge: without the wait 2441 such launches took 0.996 of
+  // the time, those of a single sequence 0.993 with up to 4 heads and 0.973 with more.
+  l.awaited = L == 1 && (sp.avg > 1 ? sp.corr_seqs > 1 && c.B > 1 : BH <= 256);
   // (a context of the bound itself has one group less: its last tokens are the window's)
   const int count = (int)longest_groups(c, max_context) - 1;
   const int most = (count + kWaves - 1) / kWaves;  // splits that it takes at most (sequence_splits)

@@ -30,11 +30,11 @@ def no_looks(kv):
 
 
 # (sequences, kv heads, heads per kv head, longest context, sequences of a correction workgroup, splits): one split and several -- up
-# to 4 and 12 (merge_pair, merge_row) and more --, one head block and two, workgroups of 1, 2 and 4 sequences, whole and ragged.
+# to 4 and 12 (merge_pair, merge_row) and more --, one head block and two, workgroups of 2 and 4 sequences, whole and ragged.
 @pytest.mark.parametrize("bits,sliding", [(2, False), (4, False), (2, True)])
 @pytest.mark.parametrize("B,H_kv,gq,n,seqs,splits", [
     (1, 1, 4, 150, 2, 1), (3, 2, 7, 300, 2, 1), (5, 3, 1, 150, 2, 1), (7, 16, 4, 300, 4, 1), (7, 16, 8, 300, 4, 1), (27, 4, 2, 300, 4, 1),
-    (1, 1, 4, 900, 1, 2), (3, 3, 1, 900, 1, 2), (13, 2, 7, 1500, 1, 3), (24, 2, 2, 1500, 2, 3), (3, 3, 3, 3000, 1, 6), (1, 2, 8, 9000, 1, 18)])
+    (24, 2, 2, 1500, 2, 3), (13, 2, 7, 3000, 2, 6), (3, 16, 3, 1500, 4, 3), (13, 4, 8, 1500, 4, 3), (12, 1, 4, 9000, 2, 18)])
 def test_every_wait_runs_out(kv, no_looks, B, H_kv, gq, n, seqs, splits, bits, sliding):
     import torch
     H_q = H_kv * gq
