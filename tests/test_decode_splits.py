@@ -80,6 +80,14 @@ def test_sequences_of_a_correction_workgroup(B, H_q, H_kv, bits, seqs):
             assert splits_of(B, H_q, H_kv, context, bits=bits).corr_seqs == 4
 
 
+@pytest.mark.parametrize("B,H_q,H_kv,context,bits,seqs", [
+    (1, 4, 1, 300, 2, 2), (9, 32, 8, 300, 2, 2), (7, 64, 16, 300, 2, 4), (16, 32, 8, 300, 2, 4),  # one split: 2 where all have a unit of their own
+    (1, 32, 8, 131072, 2, 1), (5, 32, 8, 818, 2, 1), (6, 32, 8, 818, 2, 2), (16, 32, 8, 8320, 2, 4), (9, 64, 8, 2875, 2, 1),  # several, up to three a unit
+    (16, 32, 8, 8320, 4, 4), (5, 64, 16, 818, 2, 1), (5, 64, 16, 818, 4, 2)])  # two a unit at 4 bits: never 1 there
+def test_few_sequences_of_a_correction_workgroup(B, H_q, H_kv, context, bits, seqs):
+    assert splits_of(B, H_q, H_kv, context, bits=bits).corr_seqs == seqs
+
+
 class Launch(ctypes.Structure):
     _fields_ = [(n, ctypes.c_int) for n in ("avg", "splits", "corr_seqs", "corr_first", "awaited", "workgroups", "skip")]
 

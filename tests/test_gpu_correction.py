@@ -1,11 +1,13 @@
 """GPU parity of the linear correction over the ways in which its workgroups are filled: 1 to 8 query heads per kv head (fewer
-than 4 share their channels out among the waves, more than 4 are two head blocks), numbers of sequences around the 4 and 8 that
-a workgroup serves.  Short contexts and small queries, so that the correction is a large part of the result."""
+than 4 share their channels out among the waves, more than 4 are two head blocks), numbers of sequences around the 1, 2, 4 and 8
+that a workgroup serves (one and two sequences are shared by the waves, of more every wave takes whole ones).  Short contexts and
+small queries, so that the correction is a large part of the result."""
 import numpy as np
 import pytest
 
 import kvlinc_synth as synth
 from tests import kvlinc_testlib as tl
+from tests.test_decode_splits import launch_of
 
 pytestmark = pytest.mark.gpu
 
@@ -18,10 +20,13 @@ def kv():
     return kvmod
 
 
-def _check(kv, B, H_kv, gq, bits, pairs, n=150, sliding=False, bound=0):
+def _check(kv, B, H_kv, gq, bits, pairs, n=150, sliding=False, bound=0, seqs=None):
     from oracle import attention as o_attn
     from oracle import kvcache as o_cache
     H_q = H_kv * gq
+    if seqs is not None:
+        capacity = 128 * -(-max(n + 128, bound) // 128) + 128
+        assert launch_of(B, H_q, H_kv, bound or capacity, bits=bits, flags=kv.KVLINC_FLAG_SLIDING_VALUES if sliding else 0).corr_seqs == seqs
     K, V = tl.gen_kv(95, B, H_kv, [n] * B)
     q = (np.random.default_rng(95).standard_normal((B, H_q, 128)) * 0.05).astype(np.float16)
     Wq, Wk = synth.adapters_q(95, H_q), synth.adapters_k(95, H_kv)
@@ -34,7 +39,7 @@ def _check(kv, B, H_kv, gq, bits, pairs, n=150, sliding=False, bound=0):
     assert np.array_equal(tl.u16(got[0]), tl.u16(got[1]))
     assert int(cache.split_done.abs().sum().item()) == 0
     nq = int(cache.n_quant[0].item())
-    assert nq == 128
+    assert nq == (n - 1) // 128 * 128
     want = {}
     window = "sliding" if sliding else "block"
     for b, g in pairs:
@@ -52,7 +57,23 @@ def _check(kv, B, H_kv, gq, bits, pairs, n=150, sliding=False, bound=0):
 @pytest.mark.parametrize("gq", [1, 2, 3, 4, 5, 7, 8])
 @pytest.mark.parametrize("B,H_kv", [(1, 1), (3, 2), (4, 1), (5, 3), (9, 1)])
 def test_heads_and_sequences(kv, B, H_kv, gq, bits):
-    _check(kv, B, H_kv, gq, bits, [(b, g) for b in range(B) for g in range(H_kv)])
+    _check(kv, B, H_kv, gq, bits, [(b, g) for b in range(B) for g in range(H_kv)], seqs=2)
+
+
+# 4 sequences a workgroup, and 1, 2 and 3 in the last one
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("gq", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("B", [13, 14, 15, 16])
+def test_four_sequences(kv, B, gq, bits):
+    _check(kv, B, 16, gq, bits, sorted({(b, g) for b in (0, 3, 4, 12, B - 1) for g in (0, 15)}), seqs=4)
+
+
+# two splits: one sequence a workgroup, and two (one in the last, and none left over)
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("gq", [1, 2, 3, 4, 5, 7, 8])
+@pytest.mark.parametrize("B,H_kv,seqs", [(1, 2, 1), (3, 2, 1), (5, 8, 1), (5, 9, 2), (6, 8, 2)])
+def test_one_and_two_sequences_of_two_splits(kv, B, H_kv, seqs, gq, bits):
+    _check(kv, B, H_kv, gq, bits, sorted({(b, g) for b in (0, B // 2, B - 1) for g in (0, H_kv - 1)}), n=690, seqs=seqs)
 
 
 @pytest.mark.parametrize("B,H_kv", [(12, 64), (13, 64), (16, 64), (17, 64)])  # 8 sequences a workgroup from 13 on

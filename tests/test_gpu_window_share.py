@@ -14,7 +14,7 @@ TOKENS = [1, 3, 4, 5, 15, 16, 17, 20, 33, 64, 65, 100, 113, 127, 128]
 
 @pytest.mark.parametrize("bits", [2, 4])
 @pytest.mark.parametrize("gq", [1, 4, 7])
-@pytest.mark.parametrize("H_kv,groups", [(1, 0), (1, 1), (16, 1), (1, 17), (4, 17), (8, 18)])  # (8, 18): one round for the window (up to 4 heads)
+@pytest.mark.parametrize("H_kv,groups", [(1, 0), (1, 1), (1, 2), (1, 3), (16, 1), (1, 17), (4, 17), (8, 18)])  # (8, 18): one round for the window (up to 4 heads)
 def test_window_tokens(H_kv, groups, gq, bits):
     import torch
     assert torch.cuda.is_available(), "GPU tests need a GPU"
