@@ -95,7 +95,7 @@
  *                     keep_residual = 0; set it when the cache is created and keep it.
  *   status            [1] int32, OR-ed KVLINC_ST_* bits.
  *   split_done        [B, H_kv] int32 scratch counters (arrival counts: of the workgroups of a (sequence, KV head)
- *                     in kvlinc_decode_attention, where the last one merges; of the workgroups of a sequence in
+ *                     in kvlinc_decode_attention, by which one of them merges; of the workgroups of a sequence in
  *                     kvlinc_append_quantize, where the last one updates n_quant / n_res).  Zero them once after
  *                     allocation; every call leaves them at zero.  Two calls on the same cache must not overlap in
  *                     time; calls on different caches (each with a workspace of its own) may, on different streams.
@@ -224,8 +224,9 @@ size_t kvlinc_decode_workspace_bytes(const kvlinc_cache* cache, int32_t max_cont
  * A sequence with no tokens yields zeros.
  *
  * One kernel launch: blocks of groups are processed by separate workgroups that leave (max, sum, numerator) partials
- * in the workspace (Alg. 1, the per-block outputs); the workgroup of a (sequence, KV head) that finishes last, counted
- * in cache->split_done, merges them, adds the correction and writes `out`.  The number of blocks of a sequence follows
+ * in the workspace (Alg. 1, the per-block outputs); one workgroup of a (sequence, KV head) merges them, adds the correction
+ * and writes `out`: by the counts in cache->split_done the last one to finish, or the last one of the blocks, which may wait for
+ * the workgroups of the correction for a bounded time (about 0.1 ms; the last of those merges if that runs out).  The number of blocks of a sequence follows
  * max_context and the sequence's share of the batch's tokens, so results are deterministic (bit for bit) for a given
  * max_context and given lengths of the sequences of the batch; across different bounds or batch compositions they
  * agree up to the summation order.

@@ -11,9 +11,9 @@
 //   correction workgroups (kv head, part of phi, 1 to 8 sequences): C_n = phi_q S and C_d = phi_q P, cut into parts over
 //   the rows of S, on the matrix cores.
 // Every workgroup counts itself in at its (sequence, kv head); the streaming workgroup that arrives last, or the correction
-// workgroup where that is later and not awaited (see kvlinc_handoff.h), merges: it weighs the splits by 2^(m_j - M), adds the correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies
-// H^T and stores fp16 (Alg. 1 lines 13-15 with Eq. 5).  Every wait is bounded: what it waited for is left to
-// whoever comes last then.
+// workgroup where that is later and not awaited (see kvlinc_handoff.h), merges: it weighs the splits by 2^(m_j - M), adds the
+// correction as (num + 2^-M C_n) / (den + 2^-M C_d), applies H^T and stores fp16 (Alg. 1 lines 13-15 with Eq. 5).  A wait
+// is bounded: if it runs out, whoever comes last merges.
 //
 // The two contractions of a group (Alg. 1 lines 5-10) run on v_mfma_scale_f32_16x16x128_f8f6f4, 16 rows x 16 columns x
 // 128 contraction positions per instruction, 8 instructions per contraction and block of 4 query heads:
@@ -708,14 +708,15 @@ __device__ __forceinline__ void window_part(const WindowRegs& w, const uint32_t 
 // ---- correction terms (Sec. 3.3: C_n = phi_q(q) S, C_d = phi_q(q) P; Eq. 6 for phi) -----------------------------------
 // The work of a kv head is cut into kCorrParts parts over the rows of S: part r covers the kPartFeat features
 // kPartFeat (r % kPartsPerHalf) .. of half hs = r / kPartsPerHalf of phi.  A correction workgroup serves one part
-// for 4 or 8 sequences, on the matrix cores:
+// for 1, 2, 4 or 8 sequences, on the matrix cores:
 //   phase 1, wave w = query head w of a block of four: logits[s][f] = sum_c q[s][c] W[c][f] on v_mfma_f32_16x16x32_f16 with
 //            the sequences s as rows and features as columns.  The W rows are read in their natural order: a lane takes 4
 //            neighbouring features of the 8 channels whose products it feeds, so that the B operands of 4 column tiles
 //            (feature 4 (lane % 16) + i in tile i) are byte permutations of its own registers.
-//   phase 2, wave w = sequences w, w + 4, ...: e_f = exp(logit_f - m_r) with the part's own maximum m_r,
-//            Z_r = sum_f e_f, Cd_r = sum_f e_f P[f], and Cn_r = e S on the 4x4x4 blocks with the 4 heads as rows, block = 4
-//            channels, k = 4 features (kPartSteps steps per channel half), S taken from its binary16 tile copy.
+//   phase 2, wave w = sequences w, w + 4, ..., or, of one or two sequences, the channel half w % 2 of sequence w / 2:
+//            e_f = exp(logit_f - m_r) with the part's own maximum m_r, Z_r = sum_f e_f, Cd_r = sum_f e_f P[f], and Cn_r = e S
+//            on the 4x4x4 blocks with the 4 heads as rows, block = 4 channels, k = 4 features (kPartSteps steps per channel
+//            half), S taken from its binary16 tile copy.
 // Output per (query head, part): {Cd_r, m_r, Z_r, -, Cn_r[128]}; the softmax normalisation of each half of phi over
 // its parts is left to the merge.
 // Bound: latency, a chain of loads, two products and a hand-over.  Phase 1 on the 4x4x4 blocks took a transpose inside lane quads
@@ -957,27 +958,17 @@ __device__ __forceinline__ void add_correction(const u32x4_t (&p)[kCorrParts], c
     for (int c = 0; c < N; ++c) cn[c] = any ? fmaf(xx[c], inv, cn[c]) : cn[c];
   }
 }
-// (num + 2^-M C_n) / (den + 2^-M C_d) with both factors kept <= 1 (M is the log2-domain maximum); the literal
+// (num + 2^-M C_n) / (den + 2^-M C_d), M the log2-domain maximum, with both sums scaled by 2^M but not below 2^-64 (den counts the
+// maximum itself as 1; C_d and C_n stay in range under a factor of 2^64, and the divisor is a normal number however little is added);
+// where nothing is added (C_d = 0) the factor cancels and is left out.  (Scaled by 2^min(M, 0) the reciprocal overflowed, and
+// in the end the divisor was zero, for rows whose logits are all below -88 and to which next to nothing is added.)  The literal
 // form of Alg. 1's last lines leaves the factor 2^-M out.  M = -inf: no tokens, 0.
-// Rows with all logits far below zero are scaled by the larger of 2^M and the power of two above C_d instead of by 1, so that the
-// divisor is a normal number whatever M is and however little is added (den counts the maximum itself as 1), and by 2^M alone
-// where nothing is added (C_d = 0): the reciprocal overflows from logits of -88 on otherwise, the divisor is zero from -103 on.  (A
-// branch: the factors of all other rows are there before C_d is; without it decode launches of up to 64 sequences and heads took
-// 1.007 of the time.)
-constexpr float kFarBelow = -64.0f;
 template <int N>
-__device__ __forceinline__ void normalise(float (&n)[N], float den, float (&cn)[N], float cd, float M, bool literal) {
-  const float Ms = fmaxf(M, 0.f);
-  float fa = literal ? 1.0f : exp2f(M - Ms), fb = literal ? 1.0f : exp2f(-Ms);
-  if (M < kFarBelow && !literal) {
-    const int e = cd != 0.f ? __builtin_amdgcn_frexp_expf(cd) : 0;  // cd / 2^e in [1/2, 1)
-    const float top = cd != 0.f ? fmaxf(M, (float)e) : M;
-    fa = exp2f(M - top);
-    fb = cd != 0.f ? exp2f((float)e - top) : 0.f;
-    cd = ldexpf(cd, -e);
-#pragma unroll
-    for (int c = 0; c < N; ++c) cn[c] = ldexpf(cn[c], -e);
-  }
+__device__ __forceinline__ void normalise(float (&n)[N], float den, const float (&cn)[N], float cd, float M, bool literal) {
+  const float Ms = fmaxf(M, -64.f);
+  float fa = literal ? 1.0f : exp2f(M - Ms);
+  const float fb = literal ? 1.0f : exp2f(-Ms);
+  fa = cd != 0.f ? fa : 1.0f;
   const float inv = M != -INFINITY ? 1.0f / (fa * den + fb * cd) : 0.f;
 #pragma unroll
   for (int c = 0; c < N; ++c) n[c] = M != -INFINITY ? (fa * n[c] + fb * cn[c]) * inv : 0.f;
@@ -1307,8 +1298,9 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
   int n_splits = avg_splits;  // first guess: right for a batch of equal lengths
   const int skip = BITS == 2 ? (int)((words.groups >> 29) & 1) + 1 : 1;
   int rd, idx;
+  GroupOrder order(n_splits, sp, wave, skip);
   auto plan = [&]() {
-    const GroupOrder order(n_splits, sp, wave, skip);
+    order = GroupOrder(n_splits, sp, wave, skip);
     rd = sp == 0 ? skip : 0;
     idx = order.group(rd);
   };
@@ -1421,7 +1413,6 @@ __global__ __launch_bounds__(kThreads, BITS == 4 || (NB == 2 && SLIDING) ? 2 : 3
     const float slack = (c.flags & KVLINC_FLAG_ALG1_LITERAL) != 0 ? 0.0f : kSlack;
     const bool sliding = SLIDING && nq % kGroup == 0 && nr < kGroup;
     const int count_plain = sliding ? count - 1 : count;
-    const GroupOrder order(n_splits, sp, wave, skip);
     while (idx < count_plain) {
       const int nxt = order.group(++rd);
       if (nxt >= count) break;

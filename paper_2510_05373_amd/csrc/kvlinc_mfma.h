@@ -131,18 +131,5 @@ __device__ __forceinline__ float4_t mfma_bcast(half4_t a, half4_t b, float4_t c,
   }
 }
 
-
-// 4x4 transpose of binary16 elements inside each lane quad: lane t of a quad brings {v[t][0], v[t][1]} in X and
-// {v[t][2], v[t][3]} in Y; lane h leaves with {v[0][h], v[1][h], v[2][h], v[3][h]}.
-// perm_sel = (lane & 1) ? 0x03020706 : 0x05040100.
-__device__ __forceinline__ half4_t quad_transpose(uint32_t X, uint32_t Y, uint32_t perm_sel, int lane) {
-  const uint32_t TX = dpp_u<kQuadSwap1>(X), TY = dpp_u<kQuadSwap1>(Y);
-  const uint32_t X1 = __builtin_amdgcn_perm(TX, X, perm_sel);  // even lane {X.lo, TX.lo}; odd lane {TX.hi, X.hi}
-  const uint32_t Y1 = __builtin_amdgcn_perm(TY, Y, perm_sel);
-  const uint32_t X2 = dpp_u<kQuadSwap2>(X1), Y2 = dpp_u<kQuadSwap2>(Y1);
-  const bool upper = (lane & 2) != 0;
-  return as_h4(upper ? Y2 : X1, upper ? Y1 : X2);
-}
-
 }  // namespace
 }  // namespace kvlinc
