@@ -617,7 +617,7 @@ __device__ __forceinline__ void pv_window_tail(const half_t* __restrict__ v_win,
 // Two waves with 64 tokens each, on the 4x4x4 blocks, waited for their first record, then for the keys (each a 16-byte piece of
 // 64 lines, in 16 instructions), then for the values, then for q.  Steps before and after (with the requests laid out as they are in
 // the kernel below): 144 sequences of 1280 tokens 70.7 -> 64.0 us, 32 x 32 single heads of 1280 45.4 -> 42.0, one sequence of
-// 131072 24.4 -> 22.8, of 300 11.8 -> 10.9 (there the host's calls take as long by now), 16 of 8k 25.1 -> 24.5, 32 of 32k with 7 heads
+// 131072 24.4 -> 22.8, of 300 11.8 -> 10.9 (of which the host's two calls take 9.7), 16 of 8k 25.1 -> 24.5, 32 of 32k with 7 heads
 // 75.6 -> 72.4.
 struct WindowShare {
   int first, end;  // tokens first .. end - 1, at most 32 and first a multiple of 4; none: end <= first
